@@ -273,7 +273,8 @@ int fem_eval_hessvec(fem_mesh *mesh, const fem_solve_params *params, const doubl
  * every every-th round of solver steps is launched kernel by kernel, each
  * launch with a start and a stop HIP event (hipExtLaunchKernel on the job
  * group's stream: the dispatch's own start and end); the other rounds
- * replay captured graphs as without timing. every = 0 turns timing off.
+ * run as without timing, a launch count of one per solver step of the job
+ * that took the most. every = 0 turns timing off.
  * Counters are cleared on each call. */
 #define FEM_KERNEL_TILE 0
 #define FEM_KERNEL_NODE 1
@@ -410,9 +411,12 @@ int fem_batch_get_kernel_timing(const fem_batch *batch, int32_t kernel, int64_t 
 /* Launches of one timed kernel since timing was turned on (sampled or not). */
 int fem_batch_get_kernel_launches(const fem_batch *batch, int32_t kernel, int64_t *launches);
 
-/* Launch mode: with enable != 0 (the default) each round of kernels is
+/* Launch mode: with enable != 0 (the default) one persistent kernel takes all
+ * solver steps between two host polls, a team of workgroups per job, and
+ * rounds that it does not serve (deterministic sums, two job groups) are
  * captured once per round length into a HIP graph and replayed; 0 launches
- * the kernels one by one. Results are the same either way. */
+ * the tile, node and finalize kernels of each solver step one by one. Results
+ * are the same either way. */
 int fem_set_graphs(fem_mesh *mesh, int32_t enable);
 int fem_batch_set_graphs(fem_batch *batch, int32_t enable);
 

@@ -271,19 +271,164 @@ __device__ __forceinline__ void block_reduce(double (&v)[NS], double &mn) {
     __syncthreads();
 }
 
-// Wavefront sum / min of nb partials in a fixed order: lane l adds partials
-// l, l + 64, ..., then the wavefront tree. Every wavefront that calls it gets
-// the same value (finalize kernel; the node pass's p.q, formed by each of its
-// wavefronts without a block barrier).
-__device__ __forceinline__ double wave_sum_partials(const double *part, int nb) {
-    double v = 0.0;
-    for (int b = threadIdx.x & 63; b < nb; b += 64) v += part[b];
-    return wave_sum(v);
+// ---------------------------------------------------------------------------
+// Job data that workgroups of one launch exchange (COH): in the persistent
+// team kernel other workgroups write the node vectors, tile partials and
+// reduction partials that one reads. Stores write through the CU's vector
+// cache to its XCD's L2; the sc1 bit makes a load pass that cache by (it reads
+// at the L2's rate: 26 TB/s over the chip measured, as without the bit) and
+// makes a store go through the L2 to memory, where other XCDs see it. Vectors
+// go through raw buffer accesses, whose cache bits are an argument, scalars
+// through relaxed agent-scope atomics.
+//   kAlone  one kernel per pass: ordinary loads and stores;
+//   kXcd    all readers and writers on one XCD: sc1 loads, ordinary stores;
+//   kChip   any XCD: sc1 loads and stores.
+// ---------------------------------------------------------------------------
+enum : int { kAlone = 0, kXcd = 1, kChip = 2 };
+constexpr int kAuxSc1 = 16;                // cache-policy argument of the raw buffer loads: sc1
+constexpr int kRsrcFlags = 0x00020000;     // raw buffer, 32-bit data format
+
+// N values of type T of vector i in an array of `count` such vectors.
+template <int COH, int N, typename T, class Ptr>
+__device__ __forceinline__ void ld_vec(Ptr base, int count, int i, T (&out)[N]) {
+    if constexpr (COH == kAlone) {
+#pragma unroll
+        for (int d = 0; d < N; d++) out[d] = base[N * i + d];
+    } else {
+        constexpr int kWords = N * (int)sizeof(T) / 4;
+        const __amdgpu_buffer_rsrc_t rs =
+            __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, count * (kWords * 4), kRsrcFlags);
+        const int off = i * (kWords * 4);
+        uint32_t w[kWords];
+#pragma unroll
+        for (int k = 0; k < kWords; k += 4) {
+            const int left = kWords - k;
+            if (left >= 4) {
+                const auto v = __builtin_amdgcn_raw_buffer_load_b128(rs, off + 4 * k, 0, kAuxSc1);
+                __builtin_memcpy(w + k, &v, 16);
+            } else if (left == 3) {
+                const auto v = __builtin_amdgcn_raw_buffer_load_b96(rs, off + 4 * k, 0, kAuxSc1);
+                __builtin_memcpy(w + k, &v, 12);
+            } else if (left == 2) {
+                const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, off + 4 * k, 0, kAuxSc1);
+                __builtin_memcpy(w + k, &v, 8);
+            } else {
+                w[k] = __builtin_amdgcn_raw_buffer_load_b32(rs, off + 4 * k, 0, kAuxSc1);
+            }
+        }
+        __builtin_memcpy(out, w, sizeof out);
+    }
 }
 
-__device__ __forceinline__ double wave_min_partials(const double *part, int nb) {
+template <int COH, int N, typename T, class Ptr>
+__device__ __forceinline__ void st_vec(Ptr base, int count, int i, const T (&v)[N]) {
+    if constexpr (COH != kChip) {
+#pragma unroll
+        for (int d = 0; d < N; d++) base[N * i + d] = v[d];
+    } else {
+        constexpr int kWords = N * (int)sizeof(T) / 4;
+        typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+        typedef uint32_t u3 __attribute__((ext_vector_type(3)));
+        typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+        const __amdgpu_buffer_rsrc_t rs =
+            __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, count * (kWords * 4), kRsrcFlags);
+        const int off = i * (kWords * 4);
+        uint32_t w[kWords];
+        __builtin_memcpy(w, v, sizeof w);
+#pragma unroll
+        for (int k = 0; k < kWords; k += 4) {
+            const int left = kWords - k;
+            if (left >= 4)
+                __builtin_amdgcn_raw_buffer_store_b128(u4{w[k], w[k + 1], w[k + 2], w[k + 3]}, rs, off + 4 * k, 0, kAuxSc1);
+            else if (left == 3)
+                __builtin_amdgcn_raw_buffer_store_b96(u3{w[k], w[k + 1], w[k + 2]}, rs, off + 4 * k, 0, kAuxSc1);
+            else if (left == 2)
+                __builtin_amdgcn_raw_buffer_store_b64(u2{w[k], w[k + 1]}, rs, off + 4 * k, 0, kAuxSc1);
+            else
+                __builtin_amdgcn_raw_buffer_store_b32(w[k], rs, off + 4 * k, 0, kAuxSc1);
+        }
+    }
+}
+
+template <int COH, class U> __device__ __forceinline__ void st_one(U *p, U v) {
+    if constexpr (COH == kChip)
+        __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else
+        *p = v;
+}
+
+template <int COH, class Ptr> __device__ __forceinline__ void st_flag(Ptr base, int count, int i, bool v) {
+    if constexpr (COH != kChip) {
+        base[i] = v ? 1 : 0;
+    } else {
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, count, kRsrcFlags);
+        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(v ? 1 : 0), rs, i, 0, kAuxSc1);
+    }
+}
+
+template <int COH, class U> __device__ __forceinline__ U ld_one(const U *p) {
+    if constexpr (COH != kAlone)
+        return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else
+        return *p;
+}
+
+template <int COH, class Ptr> __device__ __forceinline__ bool ld_flag(Ptr base, int count, int i) {
+    if constexpr (COH == kAlone) {
+        return base[i] != 0;
+    } else {
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, count, kRsrcFlags);
+        return __builtin_amdgcn_raw_buffer_load_b8(rs, i, 0, kAuxSc1) != 0;
+    }
+}
+
+// A value that all lanes hold alike, as a scalar: the team kernel keeps a
+// job's solver state in LDS, whose loads return vector registers.
+template <int COH> __device__ __forceinline__ int uni(int v) { return COH != kAlone ? __builtin_amdgcn_readfirstlane(v) : v; }
+template <int COH> __device__ __forceinline__ float uni(float v) {
+    return COH != kAlone ? __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))) : v;
+}
+template <int COH> __device__ __forceinline__ double uni(double v) {
+    return COH != kAlone ? __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
+                                  __builtin_amdgcn_readfirstlane(__double2loint(v)))
+               : v;
+}
+
+// Wavefront sums / min of nb partials in a fixed order: lane l adds partials
+// l, l + 64, ..., then the wavefront tree. Every wavefront that calls it gets
+// the same value (finalize kernel; the node pass's p.q, formed by each of its
+// wavefronts without a block barrier). The loads of four partials per lane
+// and stream go out together (absent ones count 0), so a sum over up to 256
+// partials waits for memory once.
+template <int COH, int NS>
+__device__ __forceinline__ void wave_sums_partials(const double *const (&part)[NS], int nb, double (&sum)[NS]) {
+#pragma unroll
+    for (int s = 0; s < NS; s++) sum[s] = 0.0;
+    for (int b = threadIdx.x & 63; b < nb; b += 256) {
+        double a[NS][4];
+#pragma unroll
+        for (int k = 0; k < 4; k++)
+#pragma unroll
+            for (int s = 0; s < NS; s++) a[s][k] = b + 64 * k < nb ? ld_one<COH>(part[s] + b + 64 * k) : 0.0;
+#pragma unroll
+        for (int k = 0; k < 4; k++)
+#pragma unroll
+            for (int s = 0; s < NS; s++) sum[s] += a[s][k];
+    }
+#pragma unroll
+    for (int s = 0; s < NS; s++) sum[s] = wave_sum(sum[s]);
+}
+
+template <int COH = kAlone> __device__ __forceinline__ double wave_sum_partials(const double *part, int nb) {
+    const double *const p[1] = {part};
+    double v[1];
+    wave_sums_partials<COH, 1>(p, nb, v);
+    return v[0];
+}
+
+template <int COH = kAlone> __device__ __forceinline__ double wave_min_partials(const double *part, int nb) {
     double v = INFINITY;
-    for (int b = threadIdx.x; b < nb; b += 64) v = fmin(v, part[b]);
+    for (int b = threadIdx.x & 63; b < nb; b += 64) v = fmin(v, ld_one<COH>(part + b));
     return wave_min(v);
 }
 
@@ -681,15 +826,15 @@ __device__ __forceinline__ void element_nodal(const T S[9], const T Bm[9], T V, 
 }
 
 // ---------------------------------------------------------------------------
-// Indenter signed distance in double precision: value, unit world gradient
+// Indenter signed distance, its centre at c, in double precision: value, unit world gradient
 // and, inside the indenter, the world Hessian (xx yy zz xy xz yz). Medial
 // ties go to the lower axis (x, y, z) and to the radial branch before the
 // axial one.
 // ---------------------------------------------------------------------------
-__device__ inline void sdf_eval(const Indenter &ind, const double x[3], bool want_h, double &phi, double n[3],
-                                double Hw[6]) {
+__device__ inline void sdf_eval(const Indenter &ind, const double c[3], const double x[3], bool want_h, double &phi,
+                                double n[3], double Hw[6]) {
     const double *R = ind.R;
-    const double d0 = x[0] - ind.c[0], d1 = x[1] - ind.c[1], d2 = x[2] - ind.c[2];
+    const double d0 = x[0] - c[0], d1 = x[1] - c[1], d2 = x[2] - c[2];
     double q[3];
 #pragma unroll
     for (int k = 0; k < 3; k++) q[k] = R[k] * d0 + R[3 + k] * d1 + R[6 + k] * d2;
@@ -802,7 +947,7 @@ __device__ inline void sdf_eval(const Indenter &ind, const double x[3], bool wan
 // ---------------------------------------------------------------------------
 __device__ inline void end_step(InstState *s, signed char *hist, int status) {
     s->last_status = status;
-    if (s->step >= 1 && s->step <= kHistSteps) hist[s->step - 1] = (signed char)status;
+    if (hist && s->step >= 1 && s->step <= kHistSteps) hist[s->step - 1] = (signed char)status;
     s->st_g = sqrt(s->gg);
     s->tot_newton += s->st_newton;
     s->tot_cg += s->st_cg;
@@ -834,12 +979,12 @@ __device__ inline void end_step(InstState *s, signed char *hist, int status) {
 }
 
 // Block-level partial sums of a work kernel: thread 0 stores them.
-template <int NS>
+template <int COH = kAlone, int NS>
 __device__ __forceinline__ void store_partials(double *red, int stride, const int (&streams)[NS], int slot,
                                                double (&v)[NS]) {
     if (threadIdx.x == 0)
 #pragma unroll
-        for (int i = 0; i < NS; i++) red[streams[i] * stride + slot] = v[i];
+        for (int i = 0; i < NS; i++) st_one<COH>(red + streams[i] * stride + slot, v[i]);
 }
 
 // LDS of a tile block, shared by the two tile paths (doubles): the element
@@ -909,11 +1054,8 @@ __device__ inline void friction_lag(const InstState *s, const double x[3], doubl
 #pragma unroll
     for (int c = 0; c < 8; c++) fr[c] = 0.0;
     if (s->lag_ok) {
-        Indenter il = s->ind;
-#pragma unroll
-        for (int d = 0; d < 3; d++) il.c[d] = s->c_lag[d];
         double phl, nl[3], Hn[6];
-        sdf_eval(il, x, false, phl, nl, Hn);
+        sdf_eval(s->ind, s->c_lag, x, false, phl, nl, Hn);
         if (phl < 0.0) {
             fr[0] = s->mu_f * s->ind.k * (-phl);
 #pragma unroll
@@ -939,10 +1081,10 @@ __device__ inline void friction_rel(const double fr[8], const double inc[3], dou
 // penalty energy, gradient k phi n and block k n n^T (+ k phi Hess(phi) with
 // the exact contact Hessian) per eligible node.
 // ---------------------------------------------------------------------------
-template <typename T, int LAW, bool DET>
+template <typename T, int LAW, bool DET, int COH = kAlone>
 __device__ __forceinline__ void tile_element(const TopoD<T> &tp, const BufsD<T> &B, const InstState *s, int blk,
                                              T alpha, int contact_full, double *pool) {
-    const T mu = (T)s->mu, lam = (T)s->lam;
+    const T mu = uni<COH>((T)s->mu), lam = uni<COH>((T)s->lam);
     double acc[3] = {0.0, 0.0, INFINITY};   // energy, magnitude, min J
     if (blk < tp.ntile) {
         double *sa = pool;                                    // 9 per entry, FP64 in both precisions
@@ -959,12 +1101,11 @@ __device__ __forceinline__ void tile_element(const TopoD<T> &tp, const BufsD<T> 
         const int sl = (int)threadIdx.x < ne ? tp.ent_slot[e0 + threadIdx.x] : 0;
         if ((int)threadIdx.x < ne) {
             const int gid = tp.ent_node[e0 + threadIdx.x];
+            T uu[3], dd[3] = {(T)0, (T)0, (T)0};
+            ld_vec<COH>(B.u, tp.n, gid, uu);
+            if (alpha != (T)0) ld_vec<COH>(B.dx, tp.n, gid, dd);
 #pragma unroll
-            for (int d = 0; d < 3; d++) {
-                T uu = B.u[3 * gid + d];
-                if (alpha != (T)0) uu = fma_t(alpha, B.dx[3 * gid + d], uu);
-                su[kSw * sl + d] = uu;
-            }
+            for (int d = 0; d < 3; d++) su[kSw * sl + d] = alpha != (T)0 ? fma_t(alpha, dd[d], uu[d]) : uu[d];
             su[kSw * sl + 3] = (T)0;
             if (!DET)
 #pragma unroll
@@ -1026,9 +1167,12 @@ __device__ __forceinline__ void tile_element(const TopoD<T> &tp, const BufsD<T> 
             for (int k = threadIdx.x; k < nk; k += kBlock)
                 tet(k, [&](const int *l, int a, int c, T v) { atomicAdd(sa + 9 * l[a] + c, (double)v); });
             __syncthreads();
-            if ((int)threadIdx.x < ne)
+            if ((int)threadIdx.x < ne) {
+                T out[9];
 #pragma unroll
-                for (int c = 0; c < 9; c++) B.pg[9 * (e0 + threadIdx.x) + c] = (T)sa[9 * sl + c];
+                for (int c = 0; c < 9; c++) out[c] = (T)sa[9 * sl + c];
+                st_vec<COH>(B.pg, tp.nent, e0 + (int)threadIdx.x, out);
+            }
         } else {
             // Deterministic: a chunk of tets stores its contributions, then
             // each entry sums its incident ones in ascending tet order.
@@ -1063,14 +1207,15 @@ __device__ __forceinline__ void tile_element(const TopoD<T> &tp, const BufsD<T> 
         if (j < tp.nc) {
             const int i = tp.cnodes[j];
             double x[3];
+            T ui[3], di[3] = {(T)0, (T)0, (T)0};
+            ld_vec<COH>(B.u, tp.n, i, ui);
+            if (alpha != (T)0) ld_vec<COH>(B.dx, tp.n, i, di);
 #pragma unroll
             for (int d = 0; d < 3; d++) {
-                T ui = B.u[3 * i + d];
-                if (alpha != (T)0) ui = fma_t(alpha, B.dx[3 * i + d], ui);
-                x[d] = tp.X[3 * i + d] + (double)ui;
+                x[d] = tp.X[3 * i + d] + (double)(alpha != (T)0 ? fma_t(alpha, di[d], ui[d]) : ui[d]);
             }
             double phi, nv[3], Hs[6];
-            sdf_eval(s->ind, x, contact_full != 0, phi, nv, Hs);
+            sdf_eval(s->ind, s->ind.c, x, contact_full != 0, phi, nv, Hs);
             double od[9];
 #pragma unroll
             for (int c = 0; c < 9; c++) od[c] = 0.0;
@@ -1087,13 +1232,11 @@ __device__ __forceinline__ void tile_element(const TopoD<T> &tp, const BufsD<T> 
             }
             if (s->mu_f > 0.0) {
                 double fl[8];
-#pragma unroll
-                for (int c = 0; c < 8; c++) fl[c] = B.fr[8 * j + c];
+                ld_vec<COH>(B.fr, tp.nc, j, fl);
                 if (fl[0] > 0.0) {
                     double inc[3], dd[3], gf[3], Hf[6];
 #pragma unroll
-                    for (int d = 0; d < 3; d++)
-                        inc[d] = alpha != (T)0 ? (double)alpha * (double)B.dx[3 * i + d] : 0.0;
+                    for (int d = 0; d < 3; d++) inc[d] = (double)alpha * (double)di[d];
                     friction_rel(fl, inc, dd);
                     const double ef = friction_eval(fl, dd, s->eps_f, gf, Hf);
                     acc[0] += ef;
@@ -1107,12 +1250,14 @@ __device__ __forceinline__ void tile_element(const TopoD<T> &tp, const BufsD<T> 
             // the Hessian-vector passes read a node's contact block only
             // where it is nonzero (most eligible nodes are out of contact)
             bool act = false;
+            T out[9];
 #pragma unroll
             for (int c = 0; c < 9; c++) {
-                B.cp[9 * j + c] = (T)od[c];
-                if (c >= 3) act = act || (T)od[c] != (T)0;
+                out[c] = (T)od[c];
+                if (c >= 3) act = act || out[c] != (T)0;
             }
-            B.cact[j] = act ? 1 : 0;
+            st_vec<COH>(B.cp, tp.nc, j, out);
+            st_flag<COH>(B.cact, tp.nc, j, act);
         }
     }
     double sums[2] = {acc[0], acc[1]};
@@ -1120,7 +1265,7 @@ __device__ __forceinline__ void tile_element(const TopoD<T> &tp, const BufsD<T> 
     block_reduce<2, true>(sums, mn);
     double v[3] = {sums[0], sums[1], mn};
     const int streams[3] = {RS_E, RS_MAG, RS_MINJ};
-    store_partials<3>(B.red, B.red_stride, streams, blk, v);
+    store_partials<COH>(B.red, B.red_stride, streams, blk, v);
 }
 
 // ---------------------------------------------------------------------------
@@ -1131,11 +1276,11 @@ __device__ __forceinline__ void tile_element(const TopoD<T> &tp, const BufsD<T> 
 // p.q is accumulated element by element (and over contact blocks), so alpha
 // is known to the node pass without a pass over q.
 // ---------------------------------------------------------------------------
-template <typename T, int LAW, bool DET>
+template <typename T, int LAW, bool DET, int COH = kAlone>
 __device__ __forceinline__ void tile_hessvec(const TopoD<T> &tp, const BufsD<T> &B, const InstState *s, int blk,
                                              double *pool) {
-    const T beta = (T)s->beta;
-    const T mu = (T)s->mu, lam = (T)s->lam;
+    const T beta = uni<COH>((T)s->beta);
+    const T mu = uni<COH>((T)s->mu), lam = uni<COH>((T)s->lam);
     double acc[1] = {0.0};
     double unused = 0.0;
     if (blk < tp.ntile) {
@@ -1148,7 +1293,7 @@ __device__ __forceinline__ void tile_hessvec(const TopoD<T> &tp, const BufsD<T> 
         const int k0 = tp.tile_tet[t], nk = tp.tile_tet[t + 1] - k0;
         // Implicit steps add (m_i / dt^2) |p_i|^2 to p.q, taken once per node
         // (on its first entry).
-        const double cm = s->mdt2;
+        const double cm = uni<COH>(s->mdt2);
         double pq = 0.0;
         // This thread's first tet record is fetched before the staging
         // barrier, so its latency overlaps the staging loads.
@@ -1158,11 +1303,14 @@ __device__ __forceinline__ void tile_hessvec(const TopoD<T> &tp, const BufsD<T> 
         const int sl = (int)threadIdx.x < ne ? tp.ent_slot[e0 + threadIdx.x] : 0;
         if ((int)threadIdx.x < ne) {
             const int gid = tp.ent_node[e0 + threadIdx.x];
-            T pv[3];
+            T pv[3], uv[3], pp[3], zv[3];
+            ld_vec<COH>(B.u, tp.n, gid, uv);
+            ld_vec<COH>(B.p, tp.n, gid, pp);
+            ld_vec<COH>(B.z, tp.n, gid, zv);
 #pragma unroll
             for (int d = 0; d < 3; d++) {
-                su[kSw * sl + d] = B.u[3 * gid + d];
-                pv[d] = fma_t(beta, B.p[3 * gid + d], B.z[3 * gid + d]);
+                su[kSw * sl + d] = uv[d];
+                pv[d] = fma_t(beta, pp[d], zv[d]);
                 sp[kSw * sl + d] = pv[d];
                 if (!DET) sa[3 * sl + d] = 0.0;
             }
@@ -1207,9 +1355,12 @@ __device__ __forceinline__ void tile_hessvec(const TopoD<T> &tp, const BufsD<T> 
                 tet(k, [&](const int *l, int a, int d, T v) { atomicAdd(sa + 3 * l[a] + d, (double)v); });
             acc[0] = pq;
             __syncthreads();
-            if ((int)threadIdx.x < ne)
+            if ((int)threadIdx.x < ne) {
+                T out[3];
 #pragma unroll
-                for (int d = 0; d < 3; d++) B.pq[3 * (e0 + threadIdx.x) + d] = (T)sa[3 * sl + d];
+                for (int d = 0; d < 3; d++) out[d] = (T)sa[3 * sl + d];
+                st_vec<COH>(B.pq, tp.nent, e0 + (int)threadIdx.x, out);
+            }
         } else {
             // Deterministic: each chunk of kBlock tets stores its nodal
             // vectors, then each entry sums its incident ones in ascending
@@ -1243,12 +1394,15 @@ __device__ __forceinline__ void tile_hessvec(const TopoD<T> &tp, const BufsD<T> 
         }
     } else {
         const int j = (blk - tp.ntile) * kBlock + threadIdx.x;
-        if (j < tp.nc && B.cact[j]) {
-            const T *H = B.cp + 9 * j + 3;
+        if (j < tp.nc && ld_flag<COH>(B.cact, tp.nc, j)) {
+            T c9[9], pp[3], zv[3], pv[3];
             const int i = tp.cnodes[j];
-            T pv[3];
+            ld_vec<COH>(B.cp, tp.nc, j, c9);
+            ld_vec<COH>(B.p, tp.n, i, pp);
+            ld_vec<COH>(B.z, tp.n, i, zv);
+            const T *H = c9 + 3;
 #pragma unroll
-            for (int d = 0; d < 3; d++) pv[d] = fma_t(beta, B.p[3 * i + d], B.z[3 * i + d]);
+            for (int d = 0; d < 3; d++) pv[d] = fma_t(beta, pp[d], zv[d]);
             const T q0 = H[0] * pv[0] + H[3] * pv[1] + H[4] * pv[2];
             const T q1 = H[3] * pv[0] + H[1] * pv[1] + H[5] * pv[2];
             const T q2 = H[4] * pv[0] + H[5] * pv[1] + H[2] * pv[2];
@@ -1257,7 +1411,7 @@ __device__ __forceinline__ void tile_hessvec(const TopoD<T> &tp, const BufsD<T> 
     }
     block_reduce<1, false>(acc, unused);
     const int streams[1] = {RS_PQ};
-    store_partials<1>(B.red, B.red_stride, streams, blk, acc);
+    store_partials<COH>(B.red, B.red_stride, streams, blk, acc);
 }
 
 // ---------------------------------------------------------------------------
@@ -1302,7 +1456,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
 // gradient (m/dt^2)(u - ut), (m/dt^2) I to the node block, and the inertial
 // energy (m/2dt^2)|u - ut|^2 to its own partial sum.
 // ---------------------------------------------------------------------------
-template <typename T, bool FRIC>
+template <typename T, bool FRIC, int COH = kAlone>
 __device__ __forceinline__ void node_init(const TopoD<T> &tp, const BufsD<T> &B, const InstState *s, int blk,
                                           bool apply, bool step_start, int block_jacobi) {
     const T alpha = (T)s->alpha_ls;
@@ -1312,39 +1466,55 @@ __device__ __forceinline__ void node_init(const TopoD<T> &tp, const BufsD<T> &B,
     double unused = 0.0;
     const int i = blk * kBlock + threadIdx.x;
     if (i < tp.n) {
+        T un[3] = {(T)0, (T)0, (T)0};
+        if (apply || dyn) ld_vec<COH>(B.u, tp.n, i, un);
         if (apply) {
+            T dd[3];
+            ld_vec<COH>(B.dx, tp.n, i, dd);
 #pragma unroll
-            for (int d = 0; d < 3; d++) B.u[3 * i + d] = fma_t(alpha, B.dx[3 * i + d], B.u[3 * i + d]);
+            for (int d = 0; d < 3; d++) un[d] = fma_t(alpha, dd[d], un[d]);
+            st_vec<COH>(B.u, tp.n, i, un);
             // contact nodes with friction also accumulate the increment in FP64
             if (FRIC && s->mu_f > 0.0) {
                 const int jc = tp.cidx[i];
-                if (jc >= 0)
+                if (jc >= 0) {
+                    double fl[8];
+                    ld_vec<COH>(B.fr, tp.nc, jc, fl);
 #pragma unroll
-                    for (int d = 0; d < 3; d++) B.fr[8 * jc + 4 + d] += (double)alpha * (double)B.dx[3 * i + d];
+                    for (int d = 0; d < 3; d++) fl[4 + d] += (double)alpha * (double)dd[d];
+                    st_vec<COH>(B.fr, tp.nc, jc, fl);
+                }
             }
         }
         T gsum[9];
 #pragma unroll
         for (int c = 0; c < 9; c++) gsum[c] = (T)0;
         for (int q = tp.node_ent_off[i]; q < tp.node_ent_off[i + 1]; q++) {
-            const T *src = B.pg + 9 * tp.node_ent[q];
+            T src[9];
+            ld_vec<COH>(B.pg, tp.nent, tp.node_ent[q], src);
 #pragma unroll
             for (int c = 0; c < 9; c++) gsum[c] += src[c];
         }
         const int j = tp.cidx[i];
-        if (j >= 0)
+        if (j >= 0) {
+            T src[9];
+            ld_vec<COH>(B.cp, tp.nc, j, src);
 #pragma unroll
-            for (int c = 0; c < 9; c++) gsum[c] += B.cp[9 * j + c];
+            for (int c = 0; c < 9; c++) gsum[c] += src[c];
+        }
         if (dyn && !tp.fixed[i]) {
             const T h = (T)dt;
             const T cm = (T)mdt2 * tp.nvol[i];
             double en = 0.0;
+            T tv[3], vo[3] = {(T)0, (T)0, (T)0};
+            ld_vec<COH>(B.ut, tp.n, i, tv);
+            if (step_start) ld_vec<COH>(B.v, tp.n, i, vo);
 #pragma unroll
             for (int d = 0; d < 3; d++) {
-                const T ui = B.u[3 * i + d];
-                T ti = B.ut[3 * i + d];
+                const T ui = un[d];
+                T ti = tv[d];
                 if (step_start) {
-                    const T vv = B.v[3 * i + d] + (ui - ti) / h;
+                    const T vv = vo[d] + (ui - ti) / h;
                     B.v[3 * i + d] = vv;
                     ti = fma_t(h, vv, ui);
                     B.ut[3 * i + d] = ti;
@@ -1394,16 +1564,15 @@ __device__ __forceinline__ void node_init(const TopoD<T> &tp, const BufsD<T> &B,
 #pragma unroll
         for (int c = 0; c < 6; c++) B.dinv[6 * i + c] = M[c];
 #pragma unroll
-        for (int d = 0; d < 3; d++) {
-            B.r[3 * i + d] = rr[d];
-            B.z[3 * i + d] = zz[d];
-            B.p[3 * i + d] = (T)0;
-            B.dx[3 * i + d] = (T)0;
-        }
+        for (int d = 0; d < 3; d++) B.r[3 * i + d] = rr[d];
+        const T zero[3] = {(T)0, (T)0, (T)0};
+        st_vec<COH>(B.z, tp.n, i, zz);
+        st_vec<COH>(B.p, tp.n, i, zero);
+        st_vec<COH>(B.dx, tp.n, i, zero);
     }
     block_reduce<3, false>(acc, unused);
     const int streams[3] = {RS_GG, RS_IRZ, RS_EN};
-    store_partials<3>(B.red, B.red_stride, streams, blk, acc);
+    store_partials<COH>(B.red, B.red_stride, streams, blk, acc);
 }
 
 // ---------------------------------------------------------------------------
@@ -1417,14 +1586,14 @@ __device__ __forceinline__ void node_init(const TopoD<T> &tp, const BufsD<T> &B,
 // stops (on its first iteration the preconditioned residual becomes the
 // Newton direction). EVAL_HV writes q instead.
 // ---------------------------------------------------------------------------
-template <typename T, bool DYN>
+template <typename T, bool DYN, int COH = kAlone>
 __device__ __forceinline__ void node_update(const TopoD<T> &tp, const BufsD<T> &B, const InstState *s, int blk,
                                             bool eval) {
     // solver scalars and this thread's node data first: their loads are in
     // flight while the block sums the p.q partials
-    const double rz = s->rz;
-    const T beta = (T)s->beta;
-    const int cg_first = s->cg_it == 0;
+    const double rz = uni<COH>(s->rz);
+    const T beta = uni<COH>((T)s->beta);
+    const int cg_first = uni<COH>((int)(s->cg_it == 0));
     const int i = blk * kBlock + threadIdx.x;
     const bool live = i < tp.n;
     T pv[3] = {(T)0, (T)0, (T)0}, qv[3] = {(T)0, (T)0, (T)0}, rv[3] = {(T)0, (T)0, (T)0}, dxv[3] = {(T)0, (T)0, (T)0};
@@ -1437,16 +1606,15 @@ __device__ __forceinline__ void node_update(const TopoD<T> &tp, const BufsD<T> &
         const int4 e4 = tp.node_ent4[i];
         const int j = tp.cidx[i];
         fixed = tp.fixed[i] != 0;
+        T pp[3], zv[3];
+        ld_vec<COH>(B.p, tp.n, i, pp);
+        ld_vec<COH>(B.z, tp.n, i, zv);
 #pragma unroll
-        for (int d = 0; d < 3; d++) pv[d] = fma_t(beta, B.p[3 * i + d], B.z[3 * i + d]);
+        for (int d = 0; d < 3; d++) pv[d] = fma_t(beta, pp[d], zv[d]);
         if (!eval && !fixed) {
-#pragma unroll
-            for (int d = 0; d < 3; d++) {
-                rv[d] = B.r[3 * i + d];
-                dxv[d] = B.dx[3 * i + d];
-            }
-#pragma unroll
-            for (int c = 0; c < 6; c++) M[c] = B.dinv[6 * i + c];
+            ld_vec<COH>(B.r, tp.n, i, rv);
+            ld_vec<COH>(B.dx, tp.n, i, dxv);
+            ld_vec<COH>(B.dinv, tp.n, i, M);
         }
         // the node's tile partials, summed in entry order: the first kGather
         // entries come with the node (their loads are in flight together; an
@@ -1455,22 +1623,27 @@ __device__ __forceinline__ void node_update(const TopoD<T> &tp, const BufsD<T> &
         const int ent[kGather] = {e4.x, e4.y, e4.z, e4.w};
         T part[kGather][3];
 #pragma unroll
-        for (int k = 0; k < kGather; k++)
+        for (int k = 0; k < kGather; k++) {
+            T v[3];
+            ld_vec<COH>(B.pq, tp.nent, ent[k] >= 0 ? ent[k] : 0, v);
 #pragma unroll
-            for (int d = 0; d < 3; d++) {
-                const T v = B.pq[3 * (ent[k] >= 0 ? ent[k] : 0) + d];
-                part[k][d] = ent[k] >= 0 ? v : (T)0;
-            }
+            for (int d = 0; d < 3; d++) part[k][d] = ent[k] >= 0 ? v[d] : (T)0;
+        }
 #pragma unroll
         for (int k = 0; k < kGather; k++)
 #pragma unroll
             for (int d = 0; d < 3; d++) qv[d] += part[k][d];
         if (e4.w >= 0)
-            for (int q = tp.node_ent_off[i] + kGather; q < tp.node_ent_off[i + 1]; q++)
+            for (int q = tp.node_ent_off[i] + kGather; q < tp.node_ent_off[i + 1]; q++) {
+                T v[3];
+                ld_vec<COH>(B.pq, tp.nent, tp.node_ent[q], v);
 #pragma unroll
-                for (int d = 0; d < 3; d++) qv[d] += B.pq[3 * tp.node_ent[q] + d];
-        if (j >= 0 && B.cact[j]) {
-            const T *H = B.cp + 9 * j + 3;
+                for (int d = 0; d < 3; d++) qv[d] += v[d];
+            }
+        if (j >= 0 && ld_flag<COH>(B.cact, tp.nc, j)) {
+            T c9[9];
+            ld_vec<COH>(B.cp, tp.nc, j, c9);
+            const T *H = c9 + 3;
             qv[0] += H[0] * pv[0] + H[3] * pv[1] + H[4] * pv[2];
             qv[1] += H[3] * pv[0] + H[1] * pv[1] + H[5] * pv[2];
             qv[2] += H[4] * pv[0] + H[5] * pv[1] + H[2] * pv[2];
@@ -1481,8 +1654,8 @@ __device__ __forceinline__ void node_update(const TopoD<T> &tp, const BufsD<T> &
             for (int d = 0; d < 3; d++) qv[d] = fma_t(cm, pv[d], qv[d]);
         }
     }
-    const double pq = wave_sum_partials(B.red + RS_PQ * B.red_stride, tp.ntile + tp.ncb);
-    if (blk == 0 && threadIdx.x == 0) B.red[RS_PQN * B.red_stride] = pq;
+    const double pq = wave_sum_partials<COH>(B.red + RS_PQ * B.red_stride, tp.ntile + tp.ncb);
+    if (blk == 0 && threadIdx.x == 0) st_one<COH>((double *)(B.red + RS_PQN * B.red_stride), pq);
     const bool negcurv = !(pq > 0.0);
     const T alpha = negcurv ? (T)0 : (T)(rz / pq);
     double acc[2] = {0.0, 0.0};   // r.z, r.r
@@ -1494,23 +1667,22 @@ __device__ __forceinline__ void node_update(const TopoD<T> &tp, const BufsD<T> &
             if (!fixed) {
 #pragma unroll
                 for (int d = 0; d < 3; d++) {
-                    B.p[3 * i + d] = pv[d];
-                    B.dx[3 * i + d] = fma_t(alpha, pv[d], dxv[d]);
+                    dxv[d] = fma_t(alpha, pv[d], dxv[d]);
                     rv[d] = fma_t(-alpha, qv[d], rv[d]);
                     B.r[3 * i + d] = rv[d];
                 }
+                st_vec<COH>(B.p, tp.n, i, pv);
+                st_vec<COH>(B.dx, tp.n, i, dxv);
                 const T z0 = M[0] * rv[0] + M[3] * rv[1] + M[4] * rv[2];
                 const T z1 = M[3] * rv[0] + M[1] * rv[1] + M[5] * rv[2];
                 const T z2 = M[4] * rv[0] + M[5] * rv[1] + M[2] * rv[2];
-                B.z[3 * i] = z0;
-                B.z[3 * i + 1] = z1;
-                B.z[3 * i + 2] = z2;
+                const T zn[3] = {z0, z1, z2};
+                st_vec<COH>(B.z, tp.n, i, zn);
                 acc[0] = (double)rv[0] * (double)z0 + (double)rv[1] * (double)z1 + (double)rv[2] * (double)z2;
                 acc[1] = (double)rv[0] * (double)rv[0] + (double)rv[1] * (double)rv[1] + (double)rv[2] * (double)rv[2];
             }
         } else if (cg_first) {
-#pragma unroll
-            for (int d = 0; d < 3; d++) B.dx[3 * i + d] = pv[d];
+            st_vec<COH>(B.dx, tp.n, i, pv);
         }
     }
     // per-wavefront partials (kWaves per block), summed by the finalize
@@ -1518,29 +1690,37 @@ __device__ __forceinline__ void node_update(const TopoD<T> &tp, const BufsD<T> &
     acc[1] = wave_sum(acc[1]);
     if ((threadIdx.x & 63) == 0) {
         const int slot = kWaves * blk + (int)(threadIdx.x >> 6);
-        B.red[RS_RZ * B.red_stride + slot] = acc[0];
-        B.red[RS_RR * B.red_stride + slot] = acc[1];
+        st_one<COH>((double *)(B.red + RS_RZ * B.red_stride + slot), acc[0]);
+        st_one<COH>((double *)(B.red + RS_RR * B.red_stride + slot), acc[1]);
     }
 }
 
 // Line-search trial, node part: partial sums of g . dx (first trial of a
 // line search) and, for implicit steps, of the inertial energy
 // (m/2dt^2)|u + alpha dx - ut|^2 at the trial point.
-template <typename T>
+template <typename T, int COH = kAlone>
 __device__ __forceinline__ void node_trial(const TopoD<T> &tp, const BufsD<T> &B, const InstState *s, int blk) {
     double acc[2] = {0.0, 0.0};
     double unused = 0.0;
     const int i = blk * kBlock + threadIdx.x;
     if (i < tp.n) {
-        if (s->need_gd)
+        T dd[3];
+        ld_vec<COH>(B.dx, tp.n, i, dd);
+        if (s->need_gd) {
+            T gv[3];
+            ld_vec<COH>(B.g, tp.n, i, gv);
 #pragma unroll
-            for (int d = 0; d < 3; d++) acc[0] += (double)B.g[3 * i + d] * (double)B.dx[3 * i + d];
+            for (int d = 0; d < 3; d++) acc[0] += (double)gv[d] * (double)dd[d];
+        }
         if (s->dt > 0.0 && !tp.fixed[i]) {
             const T alpha = (T)s->alpha_ls;
+            T un[3], tv[3];
+            ld_vec<COH>(B.u, tp.n, i, un);
+            ld_vec<COH>(B.ut, tp.n, i, tv);
             double en = 0.0;
 #pragma unroll
             for (int d = 0; d < 3; d++) {
-                const T w = fma_t(alpha, B.dx[3 * i + d], B.u[3 * i + d]) - B.ut[3 * i + d];
+                const T w = fma_t(alpha, dd[d], un[d]) - tv[d];
                 en += (double)w * (double)w;
             }
             acc[1] = 0.5 * s->mdt2 * (double)tp.nvol[i] * en;
@@ -1548,7 +1728,7 @@ __device__ __forceinline__ void node_trial(const TopoD<T> &tp, const BufsD<T> &B
     }
     block_reduce<2, false>(acc, unused);
     const int streams[2] = {RS_GD, RS_EN};
-    store_partials<2>(B.red, B.red_stride, streams, blk, acc);
+    store_partials<COH>(B.red, B.red_stride, streams, blk, acc);
 }
 
 // ---------------------------------------------------------------------------
@@ -1558,19 +1738,53 @@ __device__ __forceinline__ void node_trial(const TopoD<T> &tp, const BufsD<T> &B
 // implicit steps; other phases return.
 // ---------------------------------------------------------------------------
 // Friction lag data of the contact-eligible nodes of one node block.
-template <typename T>
+template <typename T, int COH = kAlone>
 __device__ __forceinline__ void node_lag(const TopoD<T> &tp, const BufsD<T> &B, const InstState *s, int blk) {
     const int i = blk * kBlock + threadIdx.x;
     if (i >= tp.n) return;
     const int j = tp.cidx[i];
     if (j < 0) return;
     double x[3], fl[8];
+    T un[3];
+    ld_vec<COH>(B.u, tp.n, i, un);
 #pragma unroll
-    for (int d = 0; d < 3; d++) x[d] = tp.X[3 * i + d] + (double)B.u[3 * i + d];
+    for (int d = 0; d < 3; d++) x[d] = tp.X[3 * i + d] + (double)un[d];
     friction_lag(s, x, fl);
-#pragma unroll
-    for (int c = 0; c < 8; c++) B.fr[8 * j + c] = fl[c];
+    st_vec<COH>(B.fr, tp.nc, j, fl);
 }
+
+// One node block of a job, whatever its phase. view(): the job's descriptors,
+// asked for in each branch so that the team kernel holds only those in use.
+template <typename T, bool FRIC, int COH, class View>
+__device__ __forceinline__ void node_block(View view, const InstState *s, int blk, int block_jacobi) {
+    const int phase = uni<COH>((int)s->phase);
+    if (phase == PH_CG || phase == PH_EVAL_HV) {
+        const auto V = view();
+        // a CG update changes free nodes only: blocks of fixed nodes (numbered
+        // last) have nothing to do; block 0 always runs (it records p.q)
+        if (phase == PH_CG && blk > 0 && blk * kBlock >= V.tp.n_free) return;
+        // the inertial term as a separate instance keeps it out of the
+        // quasi-static CG update
+        if (s->mdt2 > 0.0)
+            node_update<T, true, COH>(V.tp, V.B, s, blk, phase == PH_EVAL_HV);
+        else
+            node_update<T, false, COH>(V.tp, V.B, s, blk, phase == PH_EVAL_HV);
+    } else if (phase == PH_GRAD || phase == PH_EVAL_GRAD || phase == PH_INIT) {
+        const auto V = view();
+        node_init<T, FRIC, COH>(V.tp, V.B, s, blk, phase == PH_INIT && s->apply != 0, phase == PH_GRAD, block_jacobi);
+    } else if (phase == PH_TRIAL && (s->need_gd || s->dt > 0.0)) {
+        const auto V = view();
+        node_trial<T, COH>(V.tp, V.B, s, blk);
+    } else if (FRIC && phase == PH_LAG) {
+        const auto V = view();
+        node_lag<T, COH>(V.tp, V.B, s, blk);
+    }
+}
+
+template <typename T> struct StepView {
+    const TopoD<T> &tp;
+    const BufsD<T> &B;
+};
 
 template <typename T, bool FRIC>
 __global__ __launch_bounds__(kBlock) void k_node(const Topo<T> *topos, const InstBufs<T> *bufs, const int2 *work,
@@ -1582,25 +1796,7 @@ __global__ __launch_bounds__(kBlock) void k_node(const Topo<T> *topos, const Ins
     // are fetched once as uniform (scalar) loads.
     const BufsD<T> B = dev_view(bufs[w.x]);
     const TopoD<T> tp = dev_view(topos[B.topo]);
-    const InstState *s = B.s;
-    const int phase = s->phase;
-    if (phase == PH_CG || phase == PH_EVAL_HV) {
-        // a CG update changes free nodes only: blocks of fixed nodes (numbered
-        // last) have nothing to do; block 0 always runs (it records p.q)
-        if (phase == PH_CG && w.y > 0 && w.y * kBlock >= tp.n_free) return;
-        // the inertial term as a separate instance keeps it out of the
-        // quasi-static CG update
-        if (s->mdt2 > 0.0)
-            node_update<T, true>(tp, B, s, w.y, phase == PH_EVAL_HV);
-        else
-            node_update<T, false>(tp, B, s, w.y, phase == PH_EVAL_HV);
-    }
-    else if (phase == PH_GRAD || phase == PH_EVAL_GRAD || phase == PH_INIT)
-        node_init<T, FRIC>(tp, B, s, w.y, phase == PH_INIT && s->apply != 0, phase == PH_GRAD, P->block_jacobi);
-    else if (phase == PH_TRIAL && (s->need_gd || s->dt > 0.0))
-        node_trial(tp, B, s, w.y);
-    else if (FRIC && phase == PH_LAG)
-        node_lag(tp, B, s, w.y);
+    node_block<T, FRIC, kAlone>([&] { return StepView<T>{tp, B}; }, B.s, w.y, P->block_jacobi);
 }
 
 // Newton test on |g_free| against the load step's first residual, then CG
@@ -1683,27 +1879,25 @@ __device__ inline void start_line_search(InstState *s) {
 //   INIT       Newton test.
 //   EVAL_GRAD, EVAL_HV -> IDLE.
 // ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(64) void k_finalize(const Topo<T> *topos, const InstBufs<T> *bufs, const int *live,
-                                                 int nlive, const SolveParams *P) {
-    if ((int)blockIdx.x >= nlive) return;
-    const BufsD<T> B = dev_view(bufs[live[blockIdx.x]]);
-    const TopoD<T> tp = dev_view(topos[B.topo]);
-    const auto s = B.s;   // global-address-space pointer on the device
+template <typename T, int COH, class StatePtr>
+__device__ __forceinline__ void finalize_wave(const TopoD<T> &tp, const BufsD<T> &B, StatePtr s, signed char *hist,
+                                              const SolveParams *P) {
     const int phase = s->phase;
     const int S = B.red_stride;
     const int nt = tp.ntile + tp.ncb, nn = (tp.n + kBlock - 1) / kBlock;
     if (phase == PH_LAG) {
-        if (threadIdx.x == 0) s->phase = s->after_lag;
+        if ((threadIdx.x & 63) == 0) s->phase = s->after_lag;
         return;
     }
     if (phase == PH_CG || phase == PH_EVAL_HV) {
-        const double pq = B.red[RS_PQN * S];   // the node pass's sum, as it applied it
+        const double pq = ld_one<COH>((const double *)(B.red + RS_PQN * S));   // the node pass's sum, as it applied it
         // the node pass's per-wavefront partials of its blocks with free nodes
         const int ncg = tp.n_free > kBlock ? (tp.n_free + kBlock - 1) / kBlock : 1;
-        const double rz = wave_sum_partials(B.red + RS_RZ * S, kWaves * ncg);
-        const double rr = wave_sum_partials(B.red + RS_RR * S, kWaves * ncg);
-        if (threadIdx.x != 0) return;
+        const double *const part[2] = {B.red + RS_RZ * S, B.red + RS_RR * S};
+        double sums[2];
+        wave_sums_partials<COH, 2>(part, kWaves * ncg, sums);
+        const double rz = sums[0], rr = sums[1];
+        if ((threadIdx.x & 63) != 0) return;
         s->pq = pq;
         if (phase == PH_EVAL_HV) {
             s->phase = PH_IDLE;
@@ -1723,18 +1917,18 @@ __global__ __launch_bounds__(64) void k_finalize(const Topo<T> *topos, const Ins
         if (rr <= s->tol2 || s->cg_it >= P->max_cg) start_line_search(s);
     } else if (phase == PH_GRAD || phase == PH_EVAL_GRAD || phase == PH_TRIAL) {
         // tile partials, plus the nodes' inertial energy of implicit steps
-        const double en = s->dt > 0.0 ? wave_sum_partials(B.red + RS_EN * S, nn) : 0.0;
-        const double E = wave_sum_partials(B.red + RS_E * S, nt) + en;
-        const double mag = wave_sum_partials(B.red + RS_MAG * S, nt) + en;
-        const double mn = wave_min_partials(B.red + RS_MINJ * S, nt);
+        const double en = s->dt > 0.0 ? wave_sum_partials<COH>(B.red + RS_EN * S, nn) : 0.0;
+        const double E = wave_sum_partials<COH>(B.red + RS_E * S, nt) + en;
+        const double mag = wave_sum_partials<COH>(B.red + RS_MAG * S, nt) + en;
+        const double mn = wave_min_partials<COH>(B.red + RS_MINJ * S, nt);
         double gg = 0.0, rz = 0.0, gd = 0.0;
         if (phase != PH_TRIAL) {
-            gg = wave_sum_partials(B.red + RS_GG * S, nn);
-            rz = wave_sum_partials(B.red + RS_IRZ * S, nn);
+            gg = wave_sum_partials<COH>(B.red + RS_GG * S, nn);
+            rz = wave_sum_partials<COH>(B.red + RS_IRZ * S, nn);
         } else if (s->need_gd) {
-            gd = wave_sum_partials(B.red + RS_GD * S, nn);
+            gd = wave_sum_partials<COH>(B.red + RS_GD * S, nn);
         }
-        if (threadIdx.x != 0) return;
+        if ((threadIdx.x & 63) != 0) return;
         const double Et = mn > 0.0 ? E : INFINITY;
         s->st_grad++;
         if (phase != PH_TRIAL) {
@@ -1746,7 +1940,7 @@ __global__ __launch_bounds__(64) void k_finalize(const Topo<T> *topos, const Ins
                 s->gg = gg;
                 s->phase = PH_IDLE;
             } else {
-                newton_test(s, B.hist, P, gg, rz);
+                newton_test(s, hist, P, gg, rz);
             }
             return;
         }
@@ -1763,17 +1957,349 @@ __global__ __launch_bounds__(64) void k_finalize(const Topo<T> *topos, const Ins
             s->apply = 1;
             s->phase = PH_INIT;
         } else if (s->halvings >= P->max_halvings) {
-            end_step(s, B.hist, mn > 0.0 ? ST_NOT_CONVERGED : ST_INVERSION);
+            end_step(s, hist, mn > 0.0 ? ST_NOT_CONVERGED : ST_INVERSION);
         } else {
             s->halvings++;
             s->alpha_ls *= 0.5;
         }
     } else if (phase == PH_INIT) {
-        const double gg = wave_sum_partials(B.red + RS_GG * S, nn);
-        const double rz = wave_sum_partials(B.red + RS_IRZ * S, nn);
-        if (threadIdx.x != 0) return;
-        newton_test(s, B.hist, P, gg, rz);
+        const double gg = wave_sum_partials<COH>(B.red + RS_GG * S, nn);
+        const double rz = wave_sum_partials<COH>(B.red + RS_IRZ * S, nn);
+        if ((threadIdx.x & 63) != 0) return;
+        newton_test(s, hist, P, gg, rz);
     }
+}
+
+template <typename T>
+__global__ __launch_bounds__(64) void k_finalize(const Topo<T> *topos, const InstBufs<T> *bufs, const int *live,
+                                                 int nlive, const SolveParams *P) {
+    if ((int)blockIdx.x >= nlive) return;
+    const BufsD<T> B = dev_view(bufs[live[blockIdx.x]]);
+    const TopoD<T> tp = dev_view(topos[B.topo]);
+    finalize_wave<T, kAlone>(tp, B, B.s, (signed char *)B.hist, P);   // B.s: global-address-space pointer on the device
+}
+
+// ---------------------------------------------------------------------------
+// Persistent team kernel: all solver steps of a job in one launch.
+//
+// A team is W workgroups, on one XCD or (few jobs on large meshes) on several,
+// that advance one job after another: tile
+// pass, team barrier, node pass, team barrier, and the finalize, which every
+// member takes for itself from the same partials in the same order on its own
+// LDS copy of the job's state, so all members take the same transition. Teams
+// are independent of each other: one team's node pass (bound by memory)
+// overlaps another's tile pass (bound by vector arithmetic), no job waits for
+// another's slower pass, and a step of a small job costs two barriers instead
+// of three kernel boundaries.
+//
+// Members of one XCD share its L2, so nothing has to be written back or
+// invalidated at a barrier: an agent-scope fence costs 59 ns per workgroup and
+// barrier, one after another on an XCD (measured; 32 workgroups: 2.8 us).
+// Stores are complete in the L2 once vmcnt is 0, and everything a team-mate
+// may have written is loaded past the CU's vector cache (ld_vec, ld_one).
+// Over several XCDs the stores go through to memory as well (kChip): 2.0 us
+// for a barrier with stores before and loads after it, 0.65 us on one XCD.
+// A workgroup reads the XCD it runs on from the hardware and takes the next
+// place of the teams there, so a team is where its kind needs it however
+// workgroups were dealt; places that stay empty make their team give up at its first meeting,
+// below.
+//
+// Every wait ends. A team first meets: its members are counted in, and a
+// member that has waited kMeetTicks for the rest calls the team off, once and
+// for all, by a bit in the counter that only an incomplete team can get; no
+// job state has been touched by then and the host runs those jobs through the
+// other kernels. A team that has met is resident as a whole, runs the same
+// sequence of barriers in every member, and is never waited for by another
+// team. A barrier that should not come about for kStuckTicks all the same
+// ends the launch and is reported.
+// ---------------------------------------------------------------------------
+struct TeamDesc {
+    int job_off, job_n;         // its jobs in the list
+};
+struct XcdDesc {
+    int team0, nteam, W, pad;   // teams team0 .. team0 + nteam - 1 of W workgroups each, per `span` XCDs
+};
+// Arrivals are counted in groups of kTeamGroup members, the last of a group
+// arriving for it at the team's counter: arrivals at one address are served
+// one after another (28 ns each).
+constexpr int kTeamGroup = 16, kTeamGroups = 16;
+struct alignas(128) TeamLine {
+    unsigned v;
+    char pad[124];
+};
+struct TeamSync {
+    TeamLine flag;                  // 2 * (last complete barrier) + stop, or kCalledOff
+    TeamLine top;                   // arrivals of groups, and the stop request
+    TeamLine group[kTeamGroups];    // arrivals of members
+};
+constexpr int kMaxXcds = 16;
+struct TeamCtl {
+    TeamLine ticket[kMaxXcds];   // places taken, per `span` XCDs
+    TeamLine leave;              // workgroups that have left
+    TeamSync sync[1];            // one per team
+};
+// Counters that only grow; the host takes differences between launches.
+struct TeamStat {
+    unsigned done, calledoff, stuck, steps;
+};
+constexpr unsigned kCalledOff = 0xffffffffu;
+constexpr unsigned kCalledOffBit = 0x80000000u;
+constexpr unsigned kStopUnit = 1u << 24;                    // in the top counter, above any count of arrivals
+constexpr unsigned kArrivals = kStopUnit - 1;
+constexpr unsigned long long kMeetTicks = 20000000ull;      // 0.2 s of the 100 MHz clock
+constexpr unsigned long long kStuckTicks = 2000000000ull;   // 20 s
+
+template <class U> __device__ __forceinline__ U ag_load(const U *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class U> __device__ __forceinline__ void ag_store(U *p, U v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class U> __device__ __forceinline__ U ag_add(U *p, U v) {
+    return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Entry i of a table that the launch does not change, by scalar loads.
+template <class S, class P> __device__ __forceinline__ S ld_table(const P *p, int i) {
+    static_assert(sizeof(S) == sizeof(P) && sizeof(S) % 8 == 0, "table entry");
+    const auto q = (const __attribute__((address_space(4))) unsigned long long *)(p + i);
+    unsigned long long w[sizeof(S) / 8];
+#pragma unroll
+    for (int k = 0; k < (int)(sizeof(S) / 8); k++) w[k] = q[k];
+    S out;
+    __builtin_memcpy(&out, w, sizeof out);
+    return out;
+}
+
+// The descriptors of job `job`, fetched anew at each use: held over a whole
+// step they would take 100 scalar registers, which spill.
+template <typename T> struct JobView {
+    BufsD<T> B;
+    TopoD<T> tp;
+    __device__ __forceinline__ JobView(const Topo<T> *topos, const InstBufs<T> *bufs, int job) {
+        asm volatile("" : "+s"(job));
+        B = ld_table<BufsD<T>>(bufs, job);
+        tp = ld_table<TopoD<T>>(topos, B.topo);
+    }
+};
+
+// Member `rank`'s group among the W members: up to kTeamGroup members arrive
+// at the top counter themselves.
+struct TeamGroup {
+    unsigned index, many, size, many_top;   // its group, groups, members of its group, arrivals at the top
+    __device__ __forceinline__ TeamGroup(unsigned W, unsigned rank) {
+        index = rank / kTeamGroup;
+        many = (W + kTeamGroup - 1) / kTeamGroup;
+        size = index + 1 < many ? kTeamGroup : W - index * kTeamGroup;
+        many_top = many > 1 ? many : W;
+    }
+};
+
+// Barrier number `ph` of a team (the meeting is number 1), in two halves so
+// that loads which do not depend on it can go out in between. Member `rank`'s
+// thread 0 arrives once its workgroup's stores are in the L2. A stop request
+// of member 0 is passed on to all members with the flag.
+__device__ __forceinline__ void team_arrive(TeamSync *ts, unsigned ph, unsigned W, unsigned rank, bool stop) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's stores are in the L2
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const TeamGroup g(W, rank);
+        bool last = true;
+        if (g.many > 1) last = ag_add(&ts->group[g.index].v, 1u) + 1 == ph * g.size;
+        if (stop) ag_add(&ts->top.v, kStopUnit);
+        if (last) {
+            const unsigned now = ag_add(&ts->top.v, 1u) + 1;
+            if ((now & kArrivals) == ph * g.many_top) ag_store(&ts->flag.v, 2 * ph + (now >= kStopUnit ? 1u : 0u));
+        }
+    }
+}
+
+// Returns 0, 1 (stop) or -1 (the barrier did not come about).
+__device__ __forceinline__ int team_wait(TeamSync *ts, unsigned ph, int *sh, TeamStat *stat) {
+    if (threadIdx.x == 0) {
+        unsigned long long t0 = 0;
+        unsigned v;
+        for (unsigned n = 1; (v = ag_load(&ts->flag.v)) < 2 * ph; n++) {
+            __builtin_amdgcn_s_sleep(1);
+            if ((n & 0xfff) == 0) {
+                const unsigned long long now = wall_clock64();
+                if (t0 == 0) {
+                    t0 = now;
+                } else if (now - t0 > kStuckTicks) {
+                    ag_add(&stat->stuck, 1u);
+                    ag_store(&ts->flag.v, kCalledOff);
+                }
+            }
+        }
+        sh[0] = v == kCalledOff ? -1 : (int)(v & 1u);
+    }
+    __syncthreads();
+    const int r = __builtin_amdgcn_readfirstlane(sh[0]);
+    asm volatile("" ::: "memory");
+    return r;
+}
+
+// First meeting of a team (thread 0 of each member): true once all W members
+// are there. It leaves the counters as after barrier 1.
+__device__ __forceinline__ bool team_meet(TeamSync *ts, unsigned W, unsigned rank, TeamStat *stat) {
+    const TeamGroup g(W, rank);
+    bool last = true;
+    if (g.many > 1) last = ag_add(&ts->group[g.index].v, 1u) + 1 == g.size;
+    if (last) {
+        const unsigned now = ag_add(&ts->top.v, 1u) + 1;
+        if (now & kCalledOffBit) return false;
+        if (now == g.many_top) {
+            ag_store(&ts->flag.v, 2u);
+            return true;
+        }
+    }
+    const unsigned long long t0 = wall_clock64();
+    for (;;) {
+        const unsigned v = ag_load(&ts->flag.v);
+        if (v == kCalledOff) return false;
+        if (v >= 2u) return true;
+        __builtin_amdgcn_s_sleep(8);
+        if (wall_clock64() - t0 > kMeetTicks) {
+            unsigned a = ag_load(&ts->top.v);
+            while (a < g.many_top) {   // incomplete and not called off
+                if (__hip_atomic_compare_exchange_strong(&ts->top.v, &a, a | kCalledOffBit, __ATOMIC_RELAXED,
+                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+                    ag_add(&stat->calledoff, 1u);
+                    ag_store(&ts->flag.v, kCalledOff);
+                    return false;
+                }
+            }
+            // complete, or called off by another member: the flag follows
+        }
+    }
+}
+
+__device__ __forceinline__ bool running_phase(int ph) { return ph != PH_IDLE && ph != PH_DONE; }
+
+// LAWS: constitutive laws among the jobs (1 Neo-Hookean, 2 co-rotational, 3
+// both). COH: kXcd, or kChip with teams over `span` XCDs each.
+template <typename T, int LAWS, int COH>
+__global__ __launch_bounds__(kBlock) void k_team(const Topo<T> *topos, const InstBufs<T> *bufs, const int2 *jobs,
+                                                 const TeamDesc *teams, const XcdDesc *xcds, TeamCtl *ctl,
+                                                 TeamStat *stat, const SolveParams *P, int span, int steps,
+                                                 unsigned steps_base, int stop_early, unsigned stop_at) {
+    __shared__ __attribute__((aligned(32))) double pool[TileLds<T, false>::kDoubles];
+    __shared__ InstState S;
+    __shared__ int sh[1];
+    static_assert(sizeof(InstState) % 8 == 0, "copied as 8-byte words");
+    constexpr int kStateWords = sizeof(InstState) / 8;
+    // hardware register 20: XCC_ID, low four bits
+    const int xcd = __builtin_amdgcn_readfirstlane((int)(__builtin_amdgcn_s_getreg(20 | (3 << 11)) & 15u));
+    const XcdDesc X = ld_table<XcdDesc>(xcds, xcd / span);
+    if (threadIdx.x == 0) {
+        int place = (int)ag_add(&ctl->ticket[xcd / span].v, 1u);
+        if (place >= X.nteam * X.W ||
+            !team_meet(&ctl->sync[X.team0 + place / X.W], (unsigned)X.W, (unsigned)(place % X.W), stat))
+            place = -1;
+        sh[0] = place;
+    }
+    __syncthreads();
+    const int place = __builtin_amdgcn_readfirstlane(sh[0]);
+    if (place >= 0) {
+        const int team = X.team0 + place / X.W, rank = place % X.W, W = X.W;
+        const TeamDesc D = ld_table<TeamDesc>(teams, team);
+        TeamSync *ts = &ctl->sync[team];
+        unsigned ph = 1;
+        int most = 0, r = 0;
+        for (int q = 0; q < D.job_n && r >= 0; q++) {
+            const int job = ld_table<int2>(jobs + D.job_off, q).x;
+            // The state as the host or the last launch left it; member 0
+            // writes it back at the end.
+            unsigned long long *ls = (unsigned long long *)&S;
+            int nnb;
+            __syncthreads();
+            {
+                const JobView<T> V(topos, bufs, job);
+                nnb = (V.tp.n + kBlock - 1) / kBlock;
+                const unsigned long long *gs = (const unsigned long long *)(InstState *)V.B.s;
+                for (int k = threadIdx.x; k < kStateWords; k += kBlock) ls[k] = gs[k];
+            }
+            __syncthreads();
+            const bool nh = LAWS == 1 || (LAWS == 3 && uni<kXcd>((int)S.model) == LAW_NH);
+            int c = 0, phase = uni<kXcd>((int)S.phase);
+            bool stop = false;
+            for (; c < steps && running_phase(phase) && !stop; c++) {
+                bool ask = false;
+                if (stop_early && rank == 0 && threadIdx.x == 0) ask = (int)(ag_load(&stat->done) - stop_at) >= 0;
+                if (phase == PH_CG || phase == PH_EVAL_HV) {
+                    const JobView<T> V(topos, bufs, job);
+                    const int ntb = V.tp.ntile + V.tp.ncb;
+                    for (int i = rank; i < ntb; i += W) {
+                        if ((LAWS & 1) && nh)
+                            tile_hessvec<T, LAW_NH, false, COH>(V.tp, V.B, &S, i, pool);
+                        else if (LAWS & 2)
+                            tile_hessvec<T, LAW_CR, false, COH>(V.tp, V.B, &S, i, pool);
+                    }
+                } else if (phase == PH_GRAD || phase == PH_EVAL_GRAD || phase == PH_TRIAL) {
+                    const T alpha = phase == PH_TRIAL ? uni<kXcd>((T)S.alpha_ls) : (T)0;
+                    const JobView<T> V(topos, bufs, job);
+                    const int ntb = V.tp.ntile + V.tp.ncb;
+                    for (int i = rank; i < ntb; i += W) {
+                        if ((LAWS & 1) && nh)
+                            tile_element<T, LAW_NH, false, COH>(V.tp, V.B, &S, i, alpha, P->contact_full, pool);
+                        else if (LAWS & 2)
+                            tile_element<T, LAW_CR, false, COH>(V.tp, V.B, &S, i, alpha, P->contact_full, pool);
+                    }
+                }
+                team_arrive(ts, ++ph, W, rank, ask);
+                r = team_wait(ts, ph, sh, stat);
+                if (r < 0) break;
+                stop = r > 0;
+                for (int i = rank; i < nnb; i += W)
+                    node_block<T, true, COH>([&] { return JobView<T>(topos, bufs, job); }, &S, i, P->block_jacobi);
+                team_arrive(ts, ++ph, W, rank, false);
+                r = team_wait(ts, ph, sh, stat);
+                if (r < 0) break;
+                if (threadIdx.x < 64) {
+                    const JobView<T> V(topos, bufs, job);
+                    finalize_wave<T, COH>(V.tp, V.B, &S, rank == 0 ? (signed char *)V.B.hist : nullptr, P);
+                }
+                __syncthreads();
+                const int next = uni<kXcd>((int)S.phase);
+                // A tile pass right after a trial or gradient would overwrite
+                // the energy partials that slower members still sum.
+                if ((phase == PH_TRIAL || phase == PH_GRAD) && (next == PH_TRIAL || next == PH_GRAD)) {
+                    team_arrive(ts, ++ph, W, rank, false);
+                    r = team_wait(ts, ph, sh, stat);
+                    if (r < 0) break;
+                }
+                phase = next;
+            }
+            most = max(most, c);
+            if (rank == 0 && r >= 0) {
+                if (threadIdx.x == 0 && c > 0 && !running_phase(phase)) ag_add(&stat->done, 1u);
+                const JobView<T> V(topos, bufs, job);
+                unsigned long long *gs = (unsigned long long *)(InstState *)V.B.s;
+                for (int k = threadIdx.x; k < kStateWords; k += kBlock) gs[k] = ls[k];
+            }
+        }
+        if (rank == 0 && threadIdx.x == 0)
+            __hip_atomic_fetch_max(&stat->steps, steps_base + (unsigned)most, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // the last workgroup to leave clears the counters for the next launch
+    if (threadIdx.x == 0 && ag_add(&ctl->leave.v, 1u) == gridDim.x - 1) {
+        for (int x = 0; x < kMaxXcds; x++) {
+            const XcdDesc Y = ld_table<XcdDesc>(xcds, x);
+            for (int t = Y.team0; t < Y.team0 + Y.nteam; t++) {
+                ag_store(&ctl->sync[t].flag.v, 0u);
+                ag_store(&ctl->sync[t].top.v, 0u);
+                for (int g = 0; kTeamGroup * g < Y.W; g++) ag_store(&ctl->sync[t].group[g].v, 0u);
+            }
+            ag_store(&ctl->ticket[x].v, 0u);
+        }
+        ag_store(&ctl->leave.v, 0u);
+    }
+}
+
+// XCD of each workgroup of a small launch (set-up probe: how workgroups are
+// dealt to the XCDs).
+__global__ void k_xcds(unsigned *out) {
+    if (threadIdx.x == 0) out[blockIdx.x] = __builtin_amdgcn_s_getreg(20 | (3 << 11)) & 15u;
 }
 
 // ---------------------------------------------------------------------------
@@ -1812,7 +2338,7 @@ __global__ __launch_bounds__(1024) void k_contact_patch(const Topo<T> *topos, co
             double x[3];
 #pragma unroll
             for (int d = 0; d < 3; d++) x[d] = tp.X[3 * i + d] + (double)B.u[3 * i + d];
-            sdf_eval(ind, x, false, phi, nv, Hs);
+            sdf_eval(ind, ind.c, x, false, phi, nv, Hs);
             act = phi < 0.0;
             if (fric) {
                 double fl[8], Hf[6], dd[3];

@@ -117,6 +117,14 @@ struct JobGroup {
     int tile_off = 0, tile_n = 0, node_off = 0, node_n = 0, live_off = 0, live_n = 0;
 };
 
+// Launch shape of the team kernel for the jobs in the work tables.
+struct TeamPlan {
+    bool tried = false;       // made for the current work tables
+    bool valid = false;       // and the team kernel takes these jobs
+    int blocks = 0, laws = 0;
+    int span = 1;             // XCDs of a team
+};
+
 // Events for the cross-stream order of one captured or launched round.
 constexpr int kRoundEvents = 2 * 64 + 2;
 
@@ -158,8 +166,17 @@ struct fem_batch {
     int capacity = 0;
     std::vector<TopoRec> topos;
     std::vector<InstRec> insts;     // size capacity
-    InstState *d_states = nullptr;
+    InstState *d_states = nullptr;  // capacity states, then the team kernel's TeamStat
     InstState *h_states = nullptr;  // pinned mirror
+    TeamStat stat_seen{};           // counters as of the last launch
+    int xcds = 0, cus = 0;          // of the device; xcds = 0: no team kernel
+    TeamPlan plan;
+    void *d_team = nullptr;         // team, XCD and job tables of the plan
+    size_t team_bytes = 0, team_ctl_bytes = 0;
+    TeamCtl *d_team_ctl = nullptr;
+    const TeamDesc *t_teams = nullptr;
+    const XcdDesc *t_xcds = nullptr;
+    const int2 *t_jobs = nullptr;
     void *d_topos = nullptr, *d_bufs = nullptr;
     int2 *d_work_tile = nullptr, *d_work_node = nullptr;
     int nwork_tile = 0, nwork_node = 0, cap_work_tile = 0, cap_work_node = 0;
@@ -528,7 +545,7 @@ void free_instance(fem_batch *B, int slot) {
     B->tables_dirty = true;
 }
 
-inline bool running_phase(int ph) { return ph != PH_IDLE && ph != PH_DONE; }
+inline bool host_running(int ph) { return ph != PH_IDLE && ph != PH_DONE; }
 
 // Work tables: tile (+ contact) blocks and node blocks of every running
 // instance (as of the host's last view of the states), ordered tile-major so
@@ -545,7 +562,7 @@ int rebuild_tables(fem_batch *B) {
     std::vector<int> members[2];
     for (int i = 0; i < B->capacity; i++) {
         InstRec &R = B->insts[i];
-        R.in_tables = R.live && running_phase(B->h_states[i].phase);
+        R.in_tables = R.live && host_running(B->h_states[i].phase);
         if (!R.in_tables) continue;
         live.push_back(i);
     }
@@ -601,6 +618,7 @@ int rebuild_tables(fem_batch *B) {
         return FEM_OK;
     };
     drop_graphs(B);
+    B->plan.tried = B->plan.valid = false;
     TRY(upload(wt, B->d_work_tile, B->cap_work_tile, B->nwork_tile));
     TRY(upload(wn, B->d_work_node, B->cap_work_node, B->nwork_node));
     B->nlive = (int)live.size();
@@ -646,8 +664,11 @@ int params_to_device(fem_batch *B, const fem_solve_params &P) {
     return sync(B);
 }
 
+// The states and, behind them, the team kernel's counters.
+size_t states_bytes(const fem_batch *B) { return B->capacity * sizeof(InstState) + sizeof(TeamStat); }
+
 int read_states(fem_batch *B) {
-    HIP_TRY(hipMemcpyAsync(B->h_states, B->d_states, B->capacity * sizeof(InstState), hipMemcpyDeviceToHost, B->stream));
+    HIP_TRY(hipMemcpyAsync(B->h_states, B->d_states, states_bytes(B), hipMemcpyDeviceToHost, B->stream));
     return sync(B);
 }
 
@@ -725,7 +746,7 @@ int kernel_variant(fem_batch *B) {
     B->n_law[0] = B->n_law[1] = 0;
     B->n_fric = 0;
     for (int i = 0; i < B->capacity; i++) {
-        if (!B->insts[i].live || !B->insts[i].in_tables || !running_phase(B->h_states[i].phase)) continue;
+        if (!B->insts[i].live || !B->insts[i].in_tables || !host_running(B->h_states[i].phase)) continue;
         B->n_law[B->h_states[i].model == LAW_CR ? 1 : 0]++;
         if (B->h_states[i].mu_f > 0.0) B->n_fric++;
     }
@@ -781,10 +802,152 @@ int launch_round(fem_batch *B, int chunk) {
     return FEM_OK;
 }
 
+// ---------------------------------------------------------------------------
+// Team kernel
+// ---------------------------------------------------------------------------
+constexpr int kTeamSteps = 2048;   // most solver steps of one launch
+
+// f(kernel) with the instance for the laws present and the teams' reach.
+template <typename T, class F> auto with_team_kernel(int laws, int span, F f) {
+    if (span > 1)
+        return laws == 1 ? f(k_team<T, 1, kChip>) : laws == 2 ? f(k_team<T, 2, kChip>) : f(k_team<T, 3, kChip>);
+    return laws == 1 ? f(k_team<T, 1, kXcd>) : laws == 2 ? f(k_team<T, 2, kXcd>) : f(k_team<T, 3, kXcd>);
+}
+
+// A team spans several XCDs only on meshes with more tile and contact blocks
+// than this. On one XCD a solver step of the 50k fingertip (112 blocks, FP64)
+// takes 20 us, its 32 CUs being short of arithmetic, over eight 11.7 us; the 5k
+// one (14 blocks, FP32) takes 7.8 us on one XCD and 9.5 over eight, whose
+// barriers cost 2 us instead of 0.65.
+constexpr int kTeamSpanItems = 64;
+
+// The kernels that record events per launch, sum in a fixed order or split the
+// jobs in two groups are the step kernels; so are launches one by one.
+bool team_usable(const fem_batch *B) {
+    return B->xcds > 0 && B->use_graphs && !B->deterministic && B->groups_opt != 2;
+}
+
+// Deals the running jobs (those in the work tables) to the XCDs' teams and
+// uploads the lists.
+template <typename T>
+int plan_teams(fem_batch *B, int laws) {
+    TeamPlan &plan = B->plan;
+    plan = TeamPlan();
+    plan.tried = true;
+    plan.laws = laws;
+    auto items = [&](int i) { return B->topos[B->insts[i].topo].ntile + B->topos[B->insts[i].topo].ncb; };
+    // largest first, each to the part with the fewest tile blocks
+    auto deal = [&](const std::vector<int> &list, int parts) {
+        std::vector<std::vector<int>> out(parts);
+        std::vector<long long> load(parts, 0);
+        for (int i : list) {
+            const int to = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+            out[to].push_back(i);
+            load[to] += items(i);
+        }
+        return out;
+    };
+    std::vector<int> jobs;
+    for (int i = 0; i < B->capacity; i++)
+        if (B->insts[i].in_tables && host_running(B->h_states[i].phase)) jobs.push_back(i);
+    // the team kernel's buffer accesses have 32-bit byte offsets
+    if (jobs.empty()) return FEM_OK;
+    for (int i : jobs)
+        if ((size_t)B->topos[B->insts[i].topo].nent * 9 * B->elem() > (size_t)std::numeric_limits<int>::max()) return FEM_OK;
+    std::stable_sort(jobs.begin(), jobs.end(), [&](int a, int b) { return items(a) > items(b); });
+    // XCDs of a team: one, unless there are fewer jobs than XCDs and their
+    // meshes have more tiles than one XCD takes at once
+    int span = 1;
+    while (2 * span * (int)jobs.size() <= B->xcds && items(jobs[0]) > kTeamSpanItems) span *= 2;
+    int occ = 0;
+    HIP_TRY(with_team_kernel<T>(laws, span, [&](auto k) {
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, (const void *)k, kBlock, 0);
+    }));
+    const int slots = occ * (B->cus / B->xcds) * span;   // workgroups resident on `span` XCDs
+    if (slots < 1) return FEM_OK;
+    const int places = B->xcds / span;
+    const auto per_xcd = deal(jobs, places);
+    std::vector<TeamDesc> teams;
+    std::vector<XcdDesc> xd(kMaxXcds, XcdDesc{0, 0, 1, 0});
+    std::vector<int2> lv;
+    int need = 0;
+    for (int x = 0; x < places; x++) {
+        const int nj = (int)per_xcd[x].size();
+        if (nj == 0) continue;
+        const int nt = std::min(nj, slots);
+        const auto parts = deal(per_xcd[x], nt);
+        xd[x].team0 = (int)teams.size();
+        xd[x].nteam = nt;
+        int most = 1;
+        for (const std::vector<int> &mem : parts) {
+            TeamDesc D{(int)lv.size(), (int)mem.size()};
+            for (int i : mem) {
+                lv.push_back(make_int2(i, 0));
+                most = std::max(most, items(i));
+            }
+            teams.push_back(D);
+        }
+        xd[x].W = std::max(1, std::min({slots / nt, most, kTeamGroup * kTeamGroups}));
+        need = std::max(need, nt * xd[x].W);
+    }
+    Arena A;
+    const size_t o_t = A.take<TeamDesc>(teams.size()), o_x = A.take<XcdDesc>(xd.size()), o_lv = A.take<int2>(lv.size());
+    if (A.off > B->team_bytes) {
+        if (B->d_team) (void)hipFree(B->d_team);
+        B->d_team = nullptr;
+        B->team_bytes = 0;
+        HIP_TRY(hipMalloc(&B->d_team, A.off));
+        B->team_bytes = A.off;
+    }
+    const size_t ctl = sizeof(TeamCtl) + teams.size() * sizeof(TeamSync);
+    if (ctl > B->team_ctl_bytes) {
+        if (B->d_team_ctl) (void)hipFree(B->d_team_ctl);
+        B->d_team_ctl = nullptr;
+        B->team_ctl_bytes = 0;
+        HIP_TRY(hipMalloc(&B->d_team_ctl, ctl));
+        B->team_ctl_bytes = ctl;
+        HIP_TRY(hipMemsetAsync(B->d_team_ctl, 0, ctl, B->stream));   // the kernel leaves it cleared
+    }
+    std::vector<char> image(A.off);
+    std::memcpy(image.data() + o_t, teams.data(), teams.size() * sizeof(TeamDesc));
+    std::memcpy(image.data() + o_x, xd.data(), xd.size() * sizeof(XcdDesc));
+    std::memcpy(image.data() + o_lv, lv.data(), lv.size() * sizeof(int2));
+    HIP_TRY(hipMemcpyAsync(B->d_team, image.data(), image.size(), hipMemcpyHostToDevice, B->stream));
+    TRY(sync(B));
+    char *base = (char *)B->d_team;
+    B->t_teams = (const TeamDesc *)(base + o_t);
+    B->t_xcds = (const XcdDesc *)(base + o_x);
+    B->t_jobs = (const int2 *)(base + o_lv);
+    plan.span = span;
+    plan.blocks = ceil_div(need, span) * B->xcds;
+    plan.valid = true;
+    return FEM_OK;
+}
+
+// One launch of the team kernel: up to `steps` solver steps of every running
+// job; with stop_after > 0 it hands back once so many jobs have ended.
+template <typename T>
+int launch_teams(fem_batch *B, int steps, int stop_after) {
+    const Topo<T> *tp = (const Topo<T> *)B->d_topos;
+    const InstBufs<T> *bf = (const InstBufs<T> *)B->d_bufs;
+    TeamStat *stat = (TeamStat *)(B->d_states + B->capacity);
+    const SolveParams *P = (const SolveParams *)B->d_params;
+    const dim3 grid(B->plan.blocks), block(kBlock);
+    const int early = stop_after > 0 ? 1 : 0;
+    const unsigned at = B->stat_seen.done + (unsigned)stop_after, s0 = B->stat_seen.steps;
+    with_team_kernel<T>(B->plan.laws, B->plan.span, [&](auto kernel) {
+        kernel<<<grid, block, 0, B->stream>>>(tp, bf, B->t_jobs, B->t_teams, B->t_xcds, B->d_team_ctl, stat, P,
+                                              B->plan.span, steps, s0, early, at);
+        return 0;
+    });
+    return launch_check("k_team");
+}
+
 // Advances every running job until all are done or max_rounds rounds ran.
 template <typename T>
 int run_impl(fem_batch *B, int max_rounds, int *n_running) {
     int rounds = 0, running = 0;
+    bool no_team = false;
     TRY(read_states(B));
     for (;;) {
         running = 0;
@@ -793,7 +956,7 @@ int run_impl(fem_batch *B, int max_rounds, int *n_running) {
         for (int i = 0; i < B->capacity; i++) {
             const InstRec &R = B->insts[i];
             if (!R.live) continue;
-            if (running_phase(B->h_states[i].phase)) {
+            if (host_running(B->h_states[i].phase)) {
                 running++;
                 single = i;
                 missing = missing || !R.in_tables;
@@ -809,6 +972,40 @@ int run_impl(fem_batch *B, int max_rounds, int *n_running) {
         // its current Newton iteration is expected to need (CG iterations of
         // the previous solve, plus the line-search trial and the init).
         int chunk = B->chunk > 0 ? B->chunk : 16;
+        // rounds that record kernel times run the step kernels
+        const bool timing = B->timer.every > 0;
+        bool team = !no_team && team_usable(B) && !(timing && B->timer.rounds % B->timer.every == 0);
+        if (team) {
+            const int laws = kernel_variant(B) & 3;
+            if (!B->plan.tried || B->plan.laws != laws) TRY(plan_teams<T>(B, laws));
+            team = B->plan.valid;
+        }
+        if (team) {
+            // as many rounds in one launch as may run without the host; to the
+            // end, only a quarter of the jobs being done ends a launch early,
+            // so that the others can spread out
+            int n = 1, steps = timing ? chunk : kTeamSteps;
+            if (max_rounds > 0) {
+                n = timing ? 1 : std::max(1, std::min(max_rounds - rounds, kTeamSteps / chunk));
+                steps = n * chunk;
+            }
+            TRY(launch_teams<T>(B, steps, max_rounds > 0 || running <= B->xcds ? 0 : ceil_div(running, 4)));
+            TRY(read_states(B));
+            const TeamStat now = *(const TeamStat *)(B->h_states + B->capacity), was = B->stat_seen;
+            B->stat_seen = now;
+            if (now.stuck != was.stuck) return fail(FEM_E_DEVICE, "a team barrier did not come about");
+            if (timing) {
+                B->timer.rounds++;
+                for (int k = 0; k < KernelTimer::kKinds; k++) B->timer.seen[k] += (long long)(now.steps - was.steps);
+            }
+            // a team that did not meet, or none that moved: the step kernels
+            // take over until the next run
+            no_team = now.calledoff != was.calledoff || now.steps == was.steps;
+            if (!no_team) {
+                rounds += n;
+                continue;
+            }
+        }
         if (running == 1 && B->chunk <= 0) {
             const InstState &s = B->h_states[single];
             const int expect = s.last_cg > 0 ? s.last_cg : 16;
@@ -915,7 +1112,7 @@ void batch_release(fem_batch *B) {
             (void)hipEventDestroy(B->timer.ev[i][1]);
         }
     void *dev[] = {B->d_states, B->d_topos, B->d_bufs, B->d_work_tile, B->d_work_node, B->d_live, B->d_params,
-                   B->patch, B->outbuf};
+                   B->patch, B->outbuf, B->d_team, B->d_team_ctl};
     for (void *p : dev)
         if (p) (void)hipFree(p);
     if (B->h_states) (void)hipHostFree(B->h_states);
@@ -926,6 +1123,37 @@ void batch_release(fem_batch *B) {
     if (B->xev_created)
         for (hipEvent_t e : B->xev) (void)hipEventDestroy(e);
     delete B;
+}
+
+// XCDs of the batch's device, from the ids that the workgroups of a small
+// launch read: found once per device. 0 (no team kernel) if they are not dealt
+// evenly.
+int xcd_count(fem_batch *B) {
+    static int known[kMaxDevices], cus[kMaxDevices];
+    static bool done[kMaxDevices];
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    const int d = B->device;
+    if (!done[d]) {
+        constexpr int kBlocks = 4 * kMaxXcds * 8;
+        unsigned h[kBlocks], *dev = nullptr;
+        HIP_TRY(hipMalloc(&dev, sizeof h));
+        k_xcds<<<kBlocks, 64, 0, B->stream>>>(dev);
+        const bool ok = hipMemcpyAsync(h, dev, sizeof h, hipMemcpyDeviceToHost, B->stream) == hipSuccess &&
+                        hipStreamSynchronize(B->stream) == hipSuccess;
+        (void)hipFree(dev);
+        if (!ok) return fail(FEM_E_DEVICE, "set-up probe failed");
+        int count[kMaxXcds] = {}, n = 0;
+        for (unsigned x : h) count[x & (kMaxXcds - 1)]++;
+        for (int c : count) n += c > 0;
+        bool even = true;
+        for (int x = 0; x < kMaxXcds; x++) even = even && count[x] == (x < n ? kBlocks / n : 0);
+        HIP_TRY(hipDeviceGetAttribute(&cus[d], hipDeviceAttributeMultiprocessorCount, d));
+        known[d] = even && cus[d] % n == 0 ? n : 0;
+        done[d] = true;
+    }
+    B->xcds = known[d];
+    B->cus = cus[d];
+    return FEM_OK;
 }
 
 int batch_create(const fem_config *cfg, int capacity, fem_batch **out) {
@@ -963,15 +1191,16 @@ int batch_create(const fem_config *cfg, int capacity, fem_batch **out) {
         B->xev_created = true;
     }
     const size_t bufs_bytes = (size_t)capacity * std::max(sizeof(InstBufs<float>), sizeof(InstBufs<double>));
-    if (!rc && hipMalloc(&B->d_states, capacity * sizeof(InstState)) != hipSuccess) rc = fail(FEM_E_OOM, "states");
-    if (!rc && hipMemset(B->d_states, 0, capacity * sizeof(InstState)) != hipSuccess) rc = fail(FEM_E_DEVICE, "memset");
+    if (!rc) rc = xcd_count(B);
+    if (!rc && hipMalloc(&B->d_states, states_bytes(B)) != hipSuccess) rc = fail(FEM_E_OOM, "states");
+    if (!rc && hipMemset(B->d_states, 0, states_bytes(B)) != hipSuccess) rc = fail(FEM_E_DEVICE, "memset");
     if (!rc && hipMalloc(&B->d_bufs, bufs_bytes) != hipSuccess) rc = fail(FEM_E_OOM, "views");
     if (!rc && hipMalloc(&B->d_params, sizeof(SolveParams)) != hipSuccess) rc = fail(FEM_E_OOM, "params");
     if (!rc && hipMalloc(&B->d_live, capacity * sizeof(int)) != hipSuccess) rc = fail(FEM_E_OOM, "live list");
-    if (!rc && hipHostMalloc(&B->h_states, capacity * sizeof(InstState)) != hipSuccess) rc = fail(FEM_E_OOM, "pinned");
+    if (!rc && hipHostMalloc(&B->h_states, states_bytes(B)) != hipSuccess) rc = fail(FEM_E_OOM, "pinned");
     if (!rc && hipHostMalloc(&B->h_params, sizeof(SolveParams)) != hipSuccess) rc = fail(FEM_E_OOM, "pinned");
     if (!rc) {
-        std::memset(B->h_states, 0, capacity * sizeof(InstState));
+        std::memset(B->h_states, 0, states_bytes(B));
         std::memset(B->h_params, 0, sizeof(SolveParams));
         rc = stage(B, 4096);
     }

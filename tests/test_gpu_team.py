@@ -1,0 +1,127 @@
+"""The persistent team kernel against the step kernels (runs on an MI355X).
+
+Both run the same passes on the same data; they differ in the order of the
+LDS additions of a tile and, in the last bits, in how the compiler contracts
+the same expressions. So their results are held to the bounds of a job alone
+against the same job in a mixed batch (1e-9 of the largest displacement in
+FP64, 1e-5 in FP32). Sizes: one tile and one node block; node counts around a
+block of 256; meshes on one XCD and over several; more jobs than there are
+teams at once, so that a team takes several.
+"""
+import numpy as np
+import pytest
+
+from paper_2103_16747_amd import fem, workload as W
+
+pytestmark = pytest.mark.gpu
+
+BOUND = {"fp64": 1e-9, "fp32": 1e-5}
+
+
+def rel(u, ref):
+    return float(np.abs(u - ref).max() / max(np.abs(ref).max(), 1e-300))
+
+
+def jobs_on(mesh, count, steps, **kw):
+    out = []
+    for i in range(count):
+        if mesh.name.startswith("fingertip"):
+            ind = W.seat_on_mesh(W.random_indentation(5000 + i, steps=steps), mesh)
+            ind.depth = 4e-5 * steps * (1 + i % 3)
+        else:
+            top, c = mesh.X[:, 2].max(), mesh.X.mean(axis=0)
+            ind = W.Indentation(W.SPHERE, np.array([3e-3]), np.eye(3), np.array([c[0], c[1], top + 3e-3]),
+                                np.array([0.0, 0.0, -1.0]), 5e-5 * steps * (1 + i % 4), steps)
+        for k, v in kw.items():
+            setattr(ind, k, v)
+        out.append(ind)
+    return out
+
+
+def solve(meshes, jobs, precision, graphs, max_rounds=0):
+    b = fem.FemBatch(sum(len(j) for j in jobs), precision)
+    b.set_graphs(graphs)
+    P = b.default_params(newton_rtol=1e-10, cg_rtol=1e-10) if precision == "fp64" else b.default_params()
+    ids = []
+    for m, js in zip(meshes, jobs):
+        mid = b.add_mesh(m.X, m.tets, m.fixed)
+        ids += [b.add_job(mid, ind) for ind in js]
+    while b.run(P, max_rounds=max_rounds):
+        pass
+    res = [(b.displacements(j), b.job_info(j), b.step_status(j)) for j in ids]
+    b.close()
+    return res
+
+
+def compare(a, b, precision):
+    assert len(a) == len(b)
+    for k, ((ua, ia, sa), (ub, ib, sb)) in enumerate(zip(a, b)):
+        assert ia["done"] == 1 and ib["done"] == 1
+        assert np.array_equal(sa, sb), k
+        assert rel(ua, ub) <= BOUND[precision], (k, rel(ua, ub))
+        assert ia["step"] == ib["step"] and ia["steps_ok"] == ib["steps_ok"]
+
+
+CASES = {
+    "one_tet_cell": ((1, 1, 1), 1),       # 6 tets, 8 nodes: one tile, one node block
+    "nodes_255": ((4, 2, 16), 3),         # 5 x 3 x 17 = 255 nodes
+    "nodes_256": ((3, 7, 7), 3),          # 4 x 8 x 8 = 256 nodes
+    "nodes_264": ((2, 3, 21), 2),         # 3 x 4 x 22 = 264 nodes
+    "block": ((8, 8, 8), 9),              # more jobs than XCDs
+}
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("name", list(CASES))
+def test_blocks_match_step_kernels(name, precision):
+    cells, count = CASES[name]
+    print("case", name, precision, flush=True)
+    mesh = W.block_mesh(cells, (0.01, 0.01, 0.01))
+    jobs = [jobs_on(mesh, count, 2)]
+    compare(solve([mesh], jobs, precision, 1), solve([mesh], jobs, precision, 0), precision)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("count", [1, 3, 12])
+def test_fingertip_over_xcds_and_on_one(count, precision):
+    """50k tets: one job's team spans eight XCDs, three jobs' two, twelve one."""
+    print("case", count, precision, flush=True)
+    mesh = W.fingertip_mesh(50000)
+    jobs = [jobs_on(mesh, count, 1)]
+    compare(solve([mesh], jobs, precision, 1), solve([mesh], jobs, precision, 0), precision)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_mixed_laws_friction_and_time_steps(precision):
+    print("case", precision, flush=True)
+    meshes = [W.fingertip_mesh(5000), W.cube_block_mesh()]
+    jobs = [jobs_on(meshes[0], 3, 2, friction=0.5) + jobs_on(meshes[0], 3, 2, model=1),
+            jobs_on(meshes[1], 3, 3, dt=1e-4) + jobs_on(meshes[1], 2, 2, model=1, friction=0.3, dt=1e-4)]
+    compare(solve(meshes, jobs, precision, 1), solve(meshes, jobs, precision, 0), precision)
+
+
+def test_more_jobs_than_teams():
+    """Teams that take several jobs one after another, in whole runs and in
+    rounds that leave every job unfinished in between."""
+    mesh = W.block_mesh((1, 1, 1), (2e-3, 2e-3, 2e-3))
+    jobs = [jobs_on(mesh, 1700, 1)]
+    ref = solve([mesh], jobs, "fp32", 0)
+    print("reference done", flush=True)
+    compare(solve([mesh], jobs, "fp32", 1), ref, "fp32")
+    compare(solve([mesh], jobs, "fp32", 1, max_rounds=1), ref, "fp32")
+
+
+def test_rounds_advance_by_their_steps():
+    """A round is 16 solver steps: CG iterations, trials and inits."""
+    mesh = W.cube_block_mesh()
+    b = fem.FemBatch(2, "fp64")
+    mid = b.add_mesh(mesh.X, mesh.tets, mesh.fixed)
+    ids = [b.add_job(mid, ind) for ind in jobs_on(mesh, 2, 2)]
+    for rounds in (1, 2, 3):
+        before = [b.job_info(j) for j in ids]
+        assert b.run(max_rounds=rounds) == 2
+        for j, old in zip(ids, before):
+            new = b.job_info(j)
+            took = sum(new[k] - old[k] for k in ("hv_products", "grad_passes"))
+            assert 16 * rounds - 2 * (new["newton_iters"] - old["newton_iters"]) - 1 <= took <= 16 * rounds
+    b.close()
