@@ -38,8 +38,8 @@ namespace fem {
 
 constexpr int kBlock = 256;       // 4 wavefronts of 64
 constexpr int kWaves = kBlock / 64;
-constexpr int kGather = 4;        // node pass: tile entries per node held with the node (node_ent4)
-static_assert(kGather == 4, "node_ent4 holds four entries");
+constexpr int kGather = 6;        // node pass: tile entries per node held with the node
+static_assert(kGather == 6, "node_ent4 and node_ent2 hold six entries");
 constexpr int kTileTets = 512;    // tets per tile (2 per thread)
 constexpr int kTileNodes = 256;   // distinct nodes per tile (8-bit local ids)
 static_assert(kTileNodes <= kBlock, "the tile passes stage one entry per thread");
@@ -149,7 +149,8 @@ struct Topo {
     buf_ptr<const TetRec<T>, DEV> rec;              // m, tile order
     buf_ptr<const int, DEV> node_ent_off;           // n + 1
     buf_ptr<const int, DEV> node_ent;               // nent
-    buf_ptr<const int4, DEV> node_ent4;             // n: each node's first kGather entries (-1 past its last)
+    buf_ptr<const int4, DEV> node_ent4;             // n: each node's first kGather entries (-1 past its last):
+    buf_ptr<const int2, DEV> node_ent2;             // four, then two
     buf_ptr<const int, DEV> inc_off;                // nent + 1: each tile entry's incident (tet, slot) pairs
     buf_ptr<const uint16_t, DEV> inc;               // 4 m: (local tet << 2 | slot), ascending tet per entry
     buf_ptr<const uint8_t, DEV> fixed;              // n
@@ -382,6 +383,25 @@ template <int COH, class Ptr> __device__ __forceinline__ bool ld_flag(Ptr base, 
     }
 }
 
+// As ld_vec and ld_flag, and 0 without an access for i < 0.
+template <int COH, int N, typename T, class Ptr>
+__device__ __forceinline__ void ld_vec_or0(Ptr base, int count, int i, T (&out)[N]) {
+    if constexpr (COH == kAlone) {
+        ld_vec<COH>(base, count, i >= 0 ? i : 0, out);
+#pragma unroll
+        for (int d = 0; d < N; d++) out[d] = i >= 0 ? out[d] : (T)0;
+    } else {
+        ld_vec<COH>(base, count, i, out);   // out of the buffer's range: reads 0
+    }
+}
+
+template <int COH, class Ptr> __device__ __forceinline__ bool ld_flag_or0(Ptr base, int count, int i) {
+    if constexpr (COH == kAlone)
+        return i >= 0 && ld_flag<COH>(base, count, i);
+    else
+        return ld_flag<COH>(base, count, i);
+}
+
 // A value that all lanes hold alike, as a scalar: the team kernel keeps a
 // job's solver state in LDS, whose loads return vector registers.
 template <int COH> __device__ __forceinline__ int uni(int v) { return COH != kAlone ? __builtin_amdgcn_readfirstlane(v) : v; }
@@ -447,6 +467,15 @@ template <typename T> __device__ __forceinline__ T abs_t(T x) { return x < (T)0 
 
 template <typename T> __device__ __forceinline__ T safe_recip(T d) {
     return d > (T)0 ? (T)1 / d : (d < (T)0 ? (T)1 / -d : (T)1);
+}
+
+// z = M^-1 r of one node, in one fixed order of operations: the node pass
+// stores z for the tile pass and forms the same bits again from r in the next
+// CG update instead of reading it.
+template <typename T> __device__ __forceinline__ void precond(const T M[6], const T r[3], T z[3]) {
+    z[0] = fma_t(M[4], r[2], fma_t(M[3], r[1], M[0] * r[0]));
+    z[1] = fma_t(M[5], r[2], fma_t(M[1], r[1], M[3] * r[0]));
+    z[2] = fma_t(M[2], r[2], fma_t(M[5], r[1], M[4] * r[0]));
 }
 
 // ---------------------------------------------------------------------------
@@ -998,6 +1027,7 @@ template <typename T, bool DET = false>
 struct TileLds {
     static constexpr int kVec = kSw * kTileNodes * (int)sizeof(T) / 8;
     static constexpr int kElem = DET ? kVec + kDetElemChunk * 36 * (int)sizeof(T) / 8 : 9 * kTileNodes + kVec;
+    static constexpr int kTeamHv = 6 * kTileNodes + 2 * kVec;   // team_hessvec: two halves of sums
     static constexpr int kHv = DET ? 2 * kVec + kBlock * 12 * (int)sizeof(T) / 8 : 3 * kTileNodes + 2 * kVec;
     static constexpr int kDoubles = kElem > kHv ? kElem : kHv;
 };
@@ -1268,6 +1298,48 @@ __device__ __forceinline__ void tile_element(const TopoD<T> &tp, const BufsD<T> 
     store_partials<COH>(B.red, B.red_stride, streams, blk, v);
 }
 
+// Hessian-vector product of one tet from the staged u and p: its LDS slots,
+// nodal vectors and share of p.q; false (nothing) for an inverted tet.
+template <typename T, int LAW>
+__device__ __forceinline__ bool tet_hessvec(const TetWords<T> &rec, const T *su, const T *sp, T mu, T lam, int l[4],
+                                            T f[4][3], T &e_pq) {
+    T wu[4][3], wp[4][3];
+    const ElemGeo<T> geo = unpack_tet(rec, l);
+    load_nodes(su, l, wu);
+    load_nodes(sp, l, wp);
+    T G[9];
+    edge_gradient(wu, geo.Bm, G);
+    const T Jm1 = det_minus_one(G);
+    const T J = (T)1 + Jm1;
+    if (!(J > (T)0)) return false;
+    T dG[9], dP[9];
+    edge_gradient(wp, geo.Bm, dG);
+    Law<T, LAW>::hessvec(G, Jm1, J, dG, mu, lam, dP);
+    element_nodal(dP, geo.Bm, geo.V, f);
+    e_pq = (T)0;
+#pragma unroll
+    for (int a = 0; a < 4; a++) e_pq += wp[a][0] * f[a][0] + wp[a][1] * f[a][1] + wp[a][2] * f[a][2];
+    return true;
+}
+
+// Share of contact slot j in p.q: p . (contact block) p.
+template <typename T, int COH>
+__device__ __forceinline__ double contact_hessvec(const TopoD<T> &tp, const BufsD<T> &B, int j, T beta) {
+    if (j >= tp.nc || !ld_flag<COH>(B.cact, tp.nc, j)) return 0.0;
+    T c9[9], pp[3], zv[3], pv[3];
+    const int i = tp.cnodes[j];
+    ld_vec<COH>(B.cp, tp.nc, j, c9);
+    ld_vec<COH>(B.p, tp.n, i, pp);
+    ld_vec<COH>(B.z, tp.n, i, zv);
+    const T *H = c9 + 3;
+#pragma unroll
+    for (int d = 0; d < 3; d++) pv[d] = fma_t(beta, pp[d], zv[d]);
+    const T q0 = H[0] * pv[0] + H[3] * pv[1] + H[4] * pv[2];
+    const T q1 = H[3] * pv[0] + H[1] * pv[1] + H[5] * pv[2];
+    const T q2 = H[4] * pv[0] + H[5] * pv[1] + H[2] * pv[2];
+    return (double)(pv[0] * q0 + pv[1] * q1 + pv[2] * q2);
+}
+
 // ---------------------------------------------------------------------------
 // Hessian-vector product of one tile block (phases CG, EVAL_HV): q = H p with
 // p = z + beta p_prev formed while staging (the node pass forms the same
@@ -1297,8 +1369,8 @@ __device__ __forceinline__ void tile_hessvec(const TopoD<T> &tp, const BufsD<T> 
         double pq = 0.0;
         // This thread's first tet record is fetched before the staging
         // barrier, so its latency overlaps the staging loads.
-        TetWords<T> tw;
-        if ((int)threadIdx.x < nk) fetch_tet(tp, k0 + (int)threadIdx.x, tw);
+        TetWords<T> rec;
+        if ((int)threadIdx.x < nk) fetch_tet(tp, k0 + (int)threadIdx.x, rec);
         // entry threadIdx.x (ne <= kTileNodes <= kBlock), staged at its slot
         const int sl = (int)threadIdx.x < ne ? tp.ent_slot[e0 + threadIdx.x] : 0;
         if ((int)threadIdx.x < ne) {
@@ -1324,30 +1396,13 @@ __device__ __forceinline__ void tile_hessvec(const TopoD<T> &tp, const BufsD<T> 
         // One tet: its p.q into pq and its nodal vectors to put(l, a, d, value).
         auto tet = [&](int k, auto &&put) {
             int l[4];
-            if (k != (int)threadIdx.x) fetch_tet(tp, k0 + k, tw);
-            const ElemGeo<T> geo = unpack_tet(tw, l);
-            T wu[4][3], wp[4][3];
-            load_nodes(su, l, wu);
-            load_nodes(sp, l, wp);
-            T G[9];
-            edge_gradient(wu, geo.Bm, G);
-            const T Jm1 = det_minus_one(G);
-            const T J = (T)1 + Jm1;
-            if (!(J > (T)0)) return;
-            T dG[9];
-            edge_gradient(wp, geo.Bm, dG);
-            T dP[9];
-            Law<T, LAW>::hessvec(G, Jm1, J, dG, mu, lam, dP);
-            T f[4][3];
-            element_nodal(dP, geo.Bm, geo.V, f);
-            T e_pq = (T)0;
+            T f[4][3], e_pq;
+            if (k != (int)threadIdx.x) fetch_tet(tp, k0 + k, rec);
+            if (!tet_hessvec<T, LAW>(rec, su, sp, mu, lam, l, f, e_pq)) return;
 #pragma unroll
-            for (int a = 0; a < 4; a++) {
-                put(l, a, 0, f[a][0]);
-                put(l, a, 1, f[a][1]);
-                put(l, a, 2, f[a][2]);
-                e_pq += wp[a][0] * f[a][0] + wp[a][1] * f[a][1] + wp[a][2] * f[a][2];
-            }
+            for (int a = 0; a < 4; a++)
+#pragma unroll
+                for (int d = 0; d < 3; d++) put(l, a, d, f[a][d]);
             pq += (double)e_pq;
         };
         if constexpr (!DET) {
@@ -1393,21 +1448,7 @@ __device__ __forceinline__ void tile_hessvec(const TopoD<T> &tp, const BufsD<T> 
                 for (int d = 0; d < 3; d++) B.pq[3 * (e0 + threadIdx.x) + d] = (T)qa[d];
         }
     } else {
-        const int j = (blk - tp.ntile) * kBlock + threadIdx.x;
-        if (j < tp.nc && ld_flag<COH>(B.cact, tp.nc, j)) {
-            T c9[9], pp[3], zv[3], pv[3];
-            const int i = tp.cnodes[j];
-            ld_vec<COH>(B.cp, tp.nc, j, c9);
-            ld_vec<COH>(B.p, tp.n, i, pp);
-            ld_vec<COH>(B.z, tp.n, i, zv);
-            const T *H = c9 + 3;
-#pragma unroll
-            for (int d = 0; d < 3; d++) pv[d] = fma_t(beta, pp[d], zv[d]);
-            const T q0 = H[0] * pv[0] + H[3] * pv[1] + H[4] * pv[2];
-            const T q1 = H[3] * pv[0] + H[1] * pv[1] + H[5] * pv[2];
-            const T q2 = H[4] * pv[0] + H[5] * pv[1] + H[2] * pv[2];
-            acc[0] = (double)(pv[0] * q0 + pv[1] * q1 + pv[2] * q2);
-        }
+        acc[0] = contact_hessvec<T, COH>(tp, B, (blk - tp.ntile) * kBlock + (int)threadIdx.x, beta);
     }
     block_reduce<1, false>(acc, unused);
     const int streams[1] = {RS_PQ};
@@ -1552,9 +1593,7 @@ __device__ __forceinline__ void node_init(const TopoD<T> &tp, const BufsD<T> &B,
             }
 #pragma unroll
             for (int d2 = 0; d2 < 3; d2++) rr[d2] = -gsum[d2];
-            zz[0] = M[0] * rr[0] + M[3] * rr[1] + M[4] * rr[2];
-            zz[1] = M[3] * rr[0] + M[1] * rr[1] + M[5] * rr[2];
-            zz[2] = M[4] * rr[0] + M[5] * rr[1] + M[2] * rr[2];
+            precond(M, rr, zz);
 #pragma unroll
             for (int d2 = 0; d2 < 3; d2++) {
                 acc[0] += (double)rr[d2] * (double)rr[d2];
@@ -1586,61 +1625,68 @@ __device__ __forceinline__ void node_init(const TopoD<T> &tp, const BufsD<T> &B,
 // stops (on its first iteration the preconditioned residual becomes the
 // Newton direction). EVAL_HV writes q instead.
 // ---------------------------------------------------------------------------
-template <typename T, bool DYN, int COH = kAlone>
-__device__ __forceinline__ void node_update(const TopoD<T> &tp, const BufsD<T> &B, const InstState *s, int blk,
-                                            bool eval) {
-    // solver scalars and this thread's node data first: their loads are in
-    // flight while the block sums the p.q partials
-    const double rz = uni<COH>(s->rz);
-    const T beta = uni<COH>((T)s->beta);
-    const int cg_first = uni<COH>((int)(s->cg_it == 0));
-    const int i = blk * kBlock + threadIdx.x;
-    const bool live = i < tp.n;
-    T pv[3] = {(T)0, (T)0, (T)0}, qv[3] = {(T)0, (T)0, (T)0}, rv[3] = {(T)0, (T)0, (T)0}, dxv[3] = {(T)0, (T)0, (T)0};
-    T M[6] = {(T)0, (T)0, (T)0, (T)0, (T)0, (T)0};
-    bool fixed = true;
-    if (live) {
-        // every load that depends only on i is issued first (r, dx and the
-        // block inverse after the fixed flag: fixed nodes are numbered last,
-        // so the test is uniform across almost every wavefront)
-        const int4 e4 = tp.node_ent4[i];
-        const int j = tp.cidx[i];
-        fixed = tp.fixed[i] != 0;
-        T pp[3], zv[3];
+// One node's part of a CG update: request() asks for what depends on the node
+// alone, gather() for its tile partials, form() completes q and p, apply()
+// follows once alpha is known. Lanes past the last node repeat it.
+template <typename T> struct NodeCg {
+    int i, j;
+    bool live;                     // a free node (free nodes are numbered first)
+    int4 e4;
+    int2 e2;
+    T pp[3], zv[3], rv[3], dxv[3], M[6];
+    T part[kGather][3];
+    bool act;
+    T pv[3], qv[3];
+
+    template <int COH, bool EVAL>
+    __device__ __forceinline__ void request(const TopoD<T> &tp, const BufsD<T> &B, int node) {
+        i = min(node, tp.n - 1);
+        live = node < (EVAL ? tp.n : tp.n_free);
+        e4 = tp.node_ent4[i];
+        e2 = tp.node_ent2[i];
+        j = tp.cidx[i];
         ld_vec<COH>(B.p, tp.n, i, pp);
-        ld_vec<COH>(B.z, tp.n, i, zv);
-#pragma unroll
-        for (int d = 0; d < 3; d++) pv[d] = fma_t(beta, pp[d], zv[d]);
-        if (!eval && !fixed) {
+        if constexpr (EVAL) {
+            ld_vec<COH>(B.z, tp.n, i, zv);
+        } else {
             ld_vec<COH>(B.r, tp.n, i, rv);
             ld_vec<COH>(B.dx, tp.n, i, dxv);
             ld_vec<COH>(B.dinv, tp.n, i, M);
         }
-        // the node's tile partials, summed in entry order: the first kGather
-        // entries come with the node (their loads are in flight together; an
-        // absent entry, -1, reads entry 0 and is dropped), the rest from the
-        // node -> entry lists (1.92 entries per node on the 50k fingertip)
-        const int ent[kGather] = {e4.x, e4.y, e4.z, e4.w};
-        T part[kGather][3];
+    }
+
+    // The node's tile partials: the first kGather entries come with the node,
+    // their loads in flight together; an absent one (-1) reads nothing and
+    // counts 0.
+    template <int COH> __device__ __forceinline__ void gather(const TopoD<T> &tp, const BufsD<T> &B) {
+        const int ent[kGather] = {e4.x, e4.y, e4.z, e4.w, e2.x, e2.y};
 #pragma unroll
-        for (int k = 0; k < kGather; k++) {
-            T v[3];
-            ld_vec<COH>(B.pq, tp.nent, ent[k] >= 0 ? ent[k] : 0, v);
+        for (int k = 0; k < kGather; k++) ld_vec_or0<COH>(B.pq, tp.nent, ent[k], part[k]);
+        act = ld_flag_or0<COH>(B.cact, tp.nc, j);
+    }
+
+    template <bool DYN, int COH, bool EVAL>
+    __device__ __forceinline__ void form(const TopoD<T> &tp, const BufsD<T> &B, const InstState *s, T beta) {
+        if constexpr (!EVAL) precond(M, rv, zv);
 #pragma unroll
-            for (int d = 0; d < 3; d++) part[k][d] = ent[k] >= 0 ? v[d] : (T)0;
+        for (int d = 0; d < 3; d++) {
+            pv[d] = fma_t(beta, pp[d], zv[d]);
+            qv[d] = (T)0;
         }
+        // summed in entry order; the rest from the node -> entry lists (1 % of
+        // the nodes of the 50k fingertip)
 #pragma unroll
         for (int k = 0; k < kGather; k++)
 #pragma unroll
             for (int d = 0; d < 3; d++) qv[d] += part[k][d];
-        if (e4.w >= 0)
+        if (e2.y >= 0)
             for (int q = tp.node_ent_off[i] + kGather; q < tp.node_ent_off[i + 1]; q++) {
                 T v[3];
                 ld_vec<COH>(B.pq, tp.nent, tp.node_ent[q], v);
 #pragma unroll
                 for (int d = 0; d < 3; d++) qv[d] += v[d];
             }
-        if (j >= 0 && ld_flag<COH>(B.cact, tp.nc, j)) {
+        if (act) {
             T c9[9];
             ld_vec<COH>(B.cp, tp.nc, j, c9);
             const T *H = c9 + 3;
@@ -1648,23 +1694,19 @@ __device__ __forceinline__ void node_update(const TopoD<T> &tp, const BufsD<T> &
             qv[1] += H[3] * pv[0] + H[1] * pv[1] + H[5] * pv[2];
             qv[2] += H[4] * pv[0] + H[5] * pv[1] + H[2] * pv[2];
         }
-        if (DYN && !fixed) {
+        if (DYN && i < tp.n_free) {
             const T cm = (T)s->mdt2 * tp.nvol[i];
 #pragma unroll
             for (int d = 0; d < 3; d++) qv[d] = fma_t(cm, pv[d], qv[d]);
         }
     }
-    const double pq = wave_sum_partials<COH>(B.red + RS_PQ * B.red_stride, tp.ntile + tp.ncb);
-    if (blk == 0 && threadIdx.x == 0) st_one<COH>((double *)(B.red + RS_PQN * B.red_stride), pq);
-    const bool negcurv = !(pq > 0.0);
-    const T alpha = negcurv ? (T)0 : (T)(rz / pq);
-    double acc[2] = {0.0, 0.0};   // r.z, r.r
-    if (live) {
-        if (eval) {
-#pragma unroll
-            for (int d = 0; d < 3; d++) B.qout[3 * i + d] = qv[d];
-        } else if (!negcurv) {
-            if (!fixed) {
+
+    // acc: r.z and r.r
+    template <int COH>
+    __device__ __forceinline__ void apply(const TopoD<T> &tp, const BufsD<T> &B, T alpha, bool negcurv, int cg_first,
+                                          double (&acc)[2]) {
+        if (!negcurv) {
+            if (live) {
 #pragma unroll
                 for (int d = 0; d < 3; d++) {
                     dxv[d] = fma_t(alpha, pv[d], dxv[d]);
@@ -1673,17 +1715,39 @@ __device__ __forceinline__ void node_update(const TopoD<T> &tp, const BufsD<T> &
                 }
                 st_vec<COH>(B.p, tp.n, i, pv);
                 st_vec<COH>(B.dx, tp.n, i, dxv);
-                const T z0 = M[0] * rv[0] + M[3] * rv[1] + M[4] * rv[2];
-                const T z1 = M[3] * rv[0] + M[1] * rv[1] + M[5] * rv[2];
-                const T z2 = M[4] * rv[0] + M[5] * rv[1] + M[2] * rv[2];
-                const T zn[3] = {z0, z1, z2};
+                T zn[3];
+                precond(M, rv, zn);
                 st_vec<COH>(B.z, tp.n, i, zn);
-                acc[0] = (double)rv[0] * (double)z0 + (double)rv[1] * (double)z1 + (double)rv[2] * (double)z2;
-                acc[1] = (double)rv[0] * (double)rv[0] + (double)rv[1] * (double)rv[1] + (double)rv[2] * (double)rv[2];
+                acc[0] += (double)rv[0] * (double)zn[0] + (double)rv[1] * (double)zn[1] + (double)rv[2] * (double)zn[2];
+                acc[1] += (double)rv[0] * (double)rv[0] + (double)rv[1] * (double)rv[1] + (double)rv[2] * (double)rv[2];
             }
-        } else if (cg_first) {
+        } else if (cg_first && live) {
             st_vec<COH>(B.dx, tp.n, i, pv);
         }
+    }
+};
+
+template <typename T, bool DYN, bool EVAL, int COH = kAlone>
+__device__ __forceinline__ void node_update(const TopoD<T> &tp, const BufsD<T> &B, const InstState *s, int blk, int npq) {
+    // solver scalars and this thread's node data first: their loads are in
+    // flight while the block sums the p.q partials
+    const double rz = uni<COH>(s->rz);
+    const T beta = uni<COH>((T)s->beta);
+    const int cg_first = uni<COH>((int)(s->cg_it == 0));
+    double acc[2] = {0.0, 0.0};   // r.z, r.r
+    NodeCg<T> c;
+    c.template request<COH, EVAL>(tp, B, blk * kBlock + (int)threadIdx.x);
+    c.template gather<COH>(tp, B);
+    c.template form<DYN, COH, EVAL>(tp, B, s, beta);
+    const double pq = wave_sum_partials<COH>(B.red + RS_PQ * B.red_stride, npq);
+    if (blk == 0 && threadIdx.x == 0) st_one<COH>((double *)(B.red + RS_PQN * B.red_stride), pq);
+    if constexpr (EVAL) {
+        if (c.live)
+#pragma unroll
+            for (int d = 0; d < 3; d++) B.qout[3 * c.i + d] = c.qv[d];
+    } else {
+        const bool negcurv = !(pq > 0.0);
+        c.template apply<COH>(tp, B, negcurv ? (T)0 : (T)(rz / pq), negcurv, cg_first, acc);
     }
     // per-wavefront partials (kWaves per block), summed by the finalize
     acc[0] = wave_sum(acc[0]);
@@ -1694,6 +1758,10 @@ __device__ __forceinline__ void node_update(const TopoD<T> &tp, const BufsD<T> &
         st_one<COH>((double *)(B.red + RS_RR * B.red_stride + slot), acc[1]);
     }
 }
+
+// Node blocks that a CG update works on: those with free nodes (numbered
+// first); block 0 always, it records p.q.
+__device__ __forceinline__ int cg_blocks(int n_free) { return n_free > kBlock ? (n_free + kBlock - 1) / kBlock : 1; }
 
 // Line-search trial, node part: partial sums of g . dx (first trial of a
 // line search) and, for implicit steps, of the inertial energy
@@ -1755,20 +1823,25 @@ __device__ __forceinline__ void node_lag(const TopoD<T> &tp, const BufsD<T> &B, 
 
 // One node block of a job, whatever its phase. view(): the job's descriptors,
 // asked for in each branch so that the team kernel holds only those in use.
+// npq: partials of p.q (0: one per tile and contact block).
 template <typename T, bool FRIC, int COH, class View>
-__device__ __forceinline__ void node_block(View view, const InstState *s, int blk, int block_jacobi) {
+__device__ __forceinline__ void node_block(View view, const InstState *s, int blk, int npq, int block_jacobi) {
     const int phase = uni<COH>((int)s->phase);
     if (phase == PH_CG || phase == PH_EVAL_HV) {
         const auto V = view();
+        // (the team kernel's CG updates go through team_update)
         // a CG update changes free nodes only: blocks of fixed nodes (numbered
         // last) have nothing to do; block 0 always runs (it records p.q)
         if (phase == PH_CG && blk > 0 && blk * kBlock >= V.tp.n_free) return;
-        // the inertial term as a separate instance keeps it out of the
-        // quasi-static CG update
-        if (s->mdt2 > 0.0)
-            node_update<T, true, COH>(V.tp, V.B, s, blk, phase == PH_EVAL_HV);
+        // the inertial term and the evaluation as separate instances keep them
+        // out of the quasi-static CG update
+        const int np = npq ? npq : V.tp.ntile + V.tp.ncb;
+        if (phase == PH_EVAL_HV)
+            node_update<T, true, true, COH>(V.tp, V.B, s, blk, np);
+        else if (s->mdt2 > 0.0)
+            node_update<T, true, false, COH>(V.tp, V.B, s, blk, np);
         else
-            node_update<T, false, COH>(V.tp, V.B, s, blk, phase == PH_EVAL_HV);
+            node_update<T, false, false, COH>(V.tp, V.B, s, blk, np);
     } else if (phase == PH_GRAD || phase == PH_EVAL_GRAD || phase == PH_INIT) {
         const auto V = view();
         node_init<T, FRIC, COH>(V.tp, V.B, s, blk, phase == PH_INIT && s->apply != 0, phase == PH_GRAD, block_jacobi);
@@ -1796,7 +1869,7 @@ __global__ __launch_bounds__(kBlock) void k_node(const Topo<T> *topos, const Ins
     // are fetched once as uniform (scalar) loads.
     const BufsD<T> B = dev_view(bufs[w.x]);
     const TopoD<T> tp = dev_view(topos[B.topo]);
-    node_block<T, FRIC, kAlone>([&] { return StepView<T>{tp, B}; }, B.s, w.y, P->block_jacobi);
+    node_block<T, FRIC, kAlone>([&] { return StepView<T>{tp, B}; }, B.s, w.y, 0, P->block_jacobi);
 }
 
 // Newton test on |g_free| against the load step's first residual, then CG
@@ -1879,9 +1952,11 @@ __device__ inline void start_line_search(InstState *s) {
 //   INIT       Newton test.
 //   EVAL_GRAD, EVAL_HV -> IDLE.
 // ---------------------------------------------------------------------------
+// W: in the team kernel the members of the team, each of which leaves one
+// partial per wavefront of the CG sums.
 template <typename T, int COH, class StatePtr>
 __device__ __forceinline__ void finalize_wave(const TopoD<T> &tp, const BufsD<T> &B, StatePtr s, signed char *hist,
-                                              const SolveParams *P) {
+                                              const SolveParams *P, int W) {
     const int phase = s->phase;
     const int S = B.red_stride;
     const int nt = tp.ntile + tp.ncb, nn = (tp.n + kBlock - 1) / kBlock;
@@ -1892,7 +1967,7 @@ __device__ __forceinline__ void finalize_wave(const TopoD<T> &tp, const BufsD<T>
     if (phase == PH_CG || phase == PH_EVAL_HV) {
         const double pq = ld_one<COH>((const double *)(B.red + RS_PQN * S));   // the node pass's sum, as it applied it
         // the node pass's per-wavefront partials of its blocks with free nodes
-        const int ncg = tp.n_free > kBlock ? (tp.n_free + kBlock - 1) / kBlock : 1;
+        const int ncg = min(cg_blocks(tp.n_free), W);
         const double *const part[2] = {B.red + RS_RZ * S, B.red + RS_RR * S};
         double sums[2];
         wave_sums_partials<COH, 2>(part, kWaves * ncg, sums);
@@ -1976,7 +2051,7 @@ __global__ __launch_bounds__(64) void k_finalize(const Topo<T> *topos, const Ins
     if ((int)blockIdx.x >= nlive) return;
     const BufsD<T> B = dev_view(bufs[live[blockIdx.x]]);
     const TopoD<T> tp = dev_view(topos[B.topo]);
-    finalize_wave<T, kAlone>(tp, B, B.s, (signed char *)B.hist, P);   // B.s: global-address-space pointer on the device
+    finalize_wave<T, kAlone>(tp, B, B.s, (signed char *)B.hist, P, 0x7fffffff);   // B.s: global-address-space pointer on the device
 }
 
 // ---------------------------------------------------------------------------
@@ -2174,6 +2249,157 @@ __device__ __forceinline__ bool team_meet(TeamSync *ts, unsigned W, unsigned ran
     }
 }
 
+// Word i of a table that the launch does not change, by a scalar load.
+__device__ __forceinline__ int ld_int(glob_ptr<const int> p, int i) {
+    return ((const __attribute__((address_space(4))) int *)(const int *)p)[i];
+}
+
+// Entries and tets of one tile.
+template <typename T> struct TileSpan {
+    int e0, ne, k0, nk;
+    __device__ __forceinline__ TileSpan(const TopoD<T> &tp, int t) {
+        e0 = ld_int(tp.tile_ent, t);
+        ne = ld_int(tp.tile_ent, t + 1) - e0;
+        k0 = ld_int(tp.tile_tet, t);
+        nk = ld_int(tp.tile_tet, t + 1) - k0;
+    }
+};
+
+// Hessian-vector pass of one team member: tile blocks rank, rank + W, ... of
+// its job, then contact blocks. The arithmetic is tile_hessvec's. A member
+// walks several tiles (20 for a job of the 50k fingertip among 256) and would
+// wait for memory three times in each: everything the next tile needs is
+// therefore requested while the current one's tets are computed, its node
+// vectors behind the first and second tet, each tet record behind the other
+// tet. These requests are unconditional (past the last tile they repeat it),
+// since the compiler's wait after a branch counts as if none had been made
+// and would wait for them too. The LDS sums alternate between two halves, so
+// two block barriers per tile are enough, and p.q is summed over all of the
+// member's blocks before it is reduced and stored as one partial.
+template <typename T, int LAW, int COH>
+__device__ __forceinline__ void team_hessvec(const TopoD<T> &tp, const BufsD<T> &B, const InstState *s, int rank, int W,
+                                             double *pool) {
+    static_assert(kTileTets == 2 * kBlock, "two tets per thread");
+    const T beta = uni<COH>((T)s->beta);
+    const T mu = uni<COH>((T)s->mu), lam = uni<COH>((T)s->lam);
+    const double cm = uni<COH>(s->mdt2);
+    T *su = (T *)(pool + 6 * kTileNodes), *sp = su + kSw * kTileNodes;
+    const int tid = threadIdx.x;
+    double pq = 0.0;
+    if (rank < tp.ntile) {
+        int half = 0;
+        TileSpan<T> cur(tp, rank);
+        int gid = tp.ent_node[cur.e0 + min(tid, cur.ne - 1)], sl = tp.ent_slot[cur.e0 + min(tid, cur.ne - 1)];
+        TetWords<T> r0, r1;
+        fetch_tet(tp, cur.k0 + min(tid, cur.nk - 1), r0);
+        T uv[3], pp[3], zv[3];
+        ld_vec<COH>(B.u, tp.n, gid, uv);
+        ld_vec<COH>(B.p, tp.n, gid, pp);
+        ld_vec<COH>(B.z, tp.n, gid, zv);
+        fetch_tet(tp, cur.k0 + min(tid + kBlock, cur.nk - 1), r1);
+        for (int t = rank;;) {
+            double *sa = pool + half;
+            const int tn = t + W;
+            const bool more = tn < tp.ntile;
+            const TileSpan<T> nxt(tp, more ? tn : t);
+            const int en = nxt.e0 + min(tid, nxt.ne - 1);
+            const int gidn = tp.ent_node[en], sln = tp.ent_slot[en];
+            if (tid < cur.ne) {
+                T pv[3];
+#pragma unroll
+                for (int d = 0; d < 3; d++) {
+                    pv[d] = fma_t(beta, pp[d], zv[d]);
+                    su[kSw * sl + d] = uv[d];
+                    sp[kSw * sl + d] = pv[d];
+                    sa[3 * sl + d] = 0.0;
+                }
+                if (cm > 0.0 && tp.owner[cur.e0 + tid])
+                    pq += cm * (double)tp.nvol[gid] *
+                          ((double)pv[0] * (double)pv[0] + (double)pv[1] * (double)pv[1] + (double)pv[2] * (double)pv[2]);
+            }
+            __syncthreads();
+            ld_vec<COH>(B.u, tp.n, gidn, uv);
+            ld_vec<COH>(B.p, tp.n, gidn, pp);
+            ld_vec<COH>(B.z, tp.n, gidn, zv);
+            auto tet = [&](const TetWords<T> &rec) {
+                int l[4];
+                T f[4][3], e_pq;
+                if (!tet_hessvec<T, LAW>(rec, su, sp, mu, lam, l, f, e_pq)) return;
+#pragma unroll
+                for (int a = 0; a < 4; a++)
+#pragma unroll
+                    for (int d = 0; d < 3; d++) atomicAdd(sa + 3 * l[a] + d, (double)f[a][d]);
+                pq += (double)e_pq;
+            };
+            if (tid < cur.nk) tet(r0);
+            fetch_tet(tp, nxt.k0 + min(tid, nxt.nk - 1), r0);
+            if (tid + kBlock < cur.nk) tet(r1);
+            fetch_tet(tp, nxt.k0 + min(tid + kBlock, nxt.nk - 1), r1);
+            __syncthreads();
+            if (tid < cur.ne) {
+                T out[3];
+#pragma unroll
+                for (int d = 0; d < 3; d++) out[d] = (T)sa[3 * sl + d];
+                st_vec<COH>(B.pq, tp.nent, cur.e0 + tid, out);
+            }
+            if (!more) break;
+            half = 3 * kTileNodes - half;
+            t = tn;
+            cur = nxt;
+            gid = gidn;
+            sl = sln;
+        }
+    }
+    // contact blocks follow the tiles in the members' turn
+    int i0 = rank;
+    if (i0 < tp.ntile) i0 += (tp.ntile - i0 + W - 1) / W * W;
+    for (int i = i0; i < tp.ntile + tp.ncb; i += W) pq += contact_hessvec<T, COH>(tp, B, (i - tp.ntile) * kBlock + tid, beta);
+    double acc[1] = {pq}, unused = 0.0;
+    block_reduce<1, false>(acc, unused);
+    const int streams[1] = {RS_PQ};
+    store_partials<COH>(B.red, B.red_stride, streams, rank, acc);
+}
+
+// CG update of one team member: node blocks rank, rank + W, ... with p.q
+// formed once and the sums of r.z and r.r taken over all of them.
+template <typename T, bool DYN, int COH>
+__device__ __forceinline__ void team_update(const TopoD<T> &tp, const BufsD<T> &B, const InstState *s, int rank, int W) {
+    const double rz = uni<COH>(s->rz);
+    const T beta = uni<COH>((T)s->beta);
+    const int cg_first = uni<COH>((int)(s->cg_it == 0));
+    const int nb = cg_blocks(tp.n_free);
+    if (rank >= nb) return;
+    double acc[2] = {0.0, 0.0};
+    const double *const part[1] = {B.red + RS_PQ * B.red_stride};
+    NodeCg<T> c;
+    c.template request<COH, false>(tp, B, rank * kBlock + (int)threadIdx.x);
+    double sum[1];
+    wave_sums_partials<COH, 1>(part, min(W, tp.ntile + tp.ncb), sum);
+    const double pq = uni<COH>(sum[0]);
+    const bool negcurv = !(pq > 0.0);
+    const T alpha = negcurv ? (T)0 : (T)(rz / pq);
+    for (int blk = rank;;) {
+        // the next block's node data are requested behind this block's gather
+        const bool more = blk + W < nb;
+        c.template gather<COH>(tp, B);
+        NodeCg<T> n;
+        n.template request<COH, false>(tp, B, (more ? blk + W : blk) * kBlock + (int)threadIdx.x);
+        c.template form<DYN, COH, false>(tp, B, s, beta);
+        c.template apply<COH>(tp, B, alpha, negcurv, cg_first, acc);
+        if (!more) break;
+        blk += W;
+        c = n;
+    }
+    if (rank == 0 && threadIdx.x == 0) st_one<COH>((double *)(B.red + RS_PQN * B.red_stride), pq);
+    acc[0] = wave_sum(acc[0]);
+    acc[1] = wave_sum(acc[1]);
+    if ((threadIdx.x & 63) == 0) {
+        const int slot = kWaves * rank + (int)(threadIdx.x >> 6);
+        st_one<COH>((double *)(B.red + RS_RZ * B.red_stride + slot), acc[0]);
+        st_one<COH>((double *)(B.red + RS_RR * B.red_stride + slot), acc[1]);
+    }
+}
+
 __device__ __forceinline__ bool running_phase(int ph) { return ph != PH_IDLE && ph != PH_DONE; }
 
 // LAWS: constitutive laws among the jobs (1 Neo-Hookean, 2 co-rotational, 3
@@ -2183,7 +2409,8 @@ __global__ __launch_bounds__(kBlock) void k_team(const Topo<T> *topos, const Ins
                                                  const TeamDesc *teams, const XcdDesc *xcds, TeamCtl *ctl,
                                                  TeamStat *stat, const SolveParams *P, int span, int steps,
                                                  unsigned steps_base, int stop_early, unsigned stop_at) {
-    __shared__ __attribute__((aligned(32))) double pool[TileLds<T, false>::kDoubles];
+    using Lds = TileLds<T, false>;
+    __shared__ __attribute__((aligned(32))) double pool[Lds::kDoubles > Lds::kTeamHv ? Lds::kDoubles : Lds::kTeamHv];
     __shared__ InstState S;
     __shared__ int sh[1];
     static_assert(sizeof(InstState) % 8 == 0, "copied as 8-byte words");
@@ -2211,11 +2438,12 @@ __global__ __launch_bounds__(kBlock) void k_team(const Topo<T> *topos, const Ins
             // The state as the host or the last launch left it; member 0
             // writes it back at the end.
             unsigned long long *ls = (unsigned long long *)&S;
-            int nnb;
+            int nnb, blocks;   // node blocks; tile and contact blocks
             __syncthreads();
             {
                 const JobView<T> V(topos, bufs, job);
                 nnb = (V.tp.n + kBlock - 1) / kBlock;
+                blocks = V.tp.ntile + V.tp.ncb;
                 const unsigned long long *gs = (const unsigned long long *)(InstState *)V.B.s;
                 for (int k = threadIdx.x; k < kStateWords; k += kBlock) ls[k] = gs[k];
             }
@@ -2228,13 +2456,10 @@ __global__ __launch_bounds__(kBlock) void k_team(const Topo<T> *topos, const Ins
                 if (stop_early && rank == 0 && threadIdx.x == 0) ask = (int)(ag_load(&stat->done) - stop_at) >= 0;
                 if (phase == PH_CG || phase == PH_EVAL_HV) {
                     const JobView<T> V(topos, bufs, job);
-                    const int ntb = V.tp.ntile + V.tp.ncb;
-                    for (int i = rank; i < ntb; i += W) {
-                        if ((LAWS & 1) && nh)
-                            tile_hessvec<T, LAW_NH, false, COH>(V.tp, V.B, &S, i, pool);
-                        else if (LAWS & 2)
-                            tile_hessvec<T, LAW_CR, false, COH>(V.tp, V.B, &S, i, pool);
-                    }
+                    if ((LAWS & 1) && nh)
+                        team_hessvec<T, LAW_NH, COH>(V.tp, V.B, &S, rank, W, pool);
+                    else if (LAWS & 2)
+                        team_hessvec<T, LAW_CR, COH>(V.tp, V.B, &S, rank, W, pool);
                 } else if (phase == PH_GRAD || phase == PH_EVAL_GRAD || phase == PH_TRIAL) {
                     const T alpha = phase == PH_TRIAL ? uni<kXcd>((T)S.alpha_ls) : (T)0;
                     const JobView<T> V(topos, bufs, job);
@@ -2250,14 +2475,23 @@ __global__ __launch_bounds__(kBlock) void k_team(const Topo<T> *topos, const Ins
                 r = team_wait(ts, ph, sh, stat);
                 if (r < 0) break;
                 stop = r > 0;
-                for (int i = rank; i < nnb; i += W)
-                    node_block<T, true, COH>([&] { return JobView<T>(topos, bufs, job); }, &S, i, P->block_jacobi);
+                if (phase == PH_CG) {
+                    const JobView<T> V(topos, bufs, job);
+                    if (S.mdt2 > 0.0)
+                        team_update<T, true, COH>(V.tp, V.B, &S, rank, W);
+                    else
+                        team_update<T, false, COH>(V.tp, V.B, &S, rank, W);
+                } else {
+                    for (int i = rank; i < nnb; i += W)
+                        node_block<T, true, COH>([&] { return JobView<T>(topos, bufs, job); }, &S, i, min(W, blocks),
+                                                 P->block_jacobi);
+                }
                 team_arrive(ts, ++ph, W, rank, false);
                 r = team_wait(ts, ph, sh, stat);
                 if (r < 0) break;
                 if (threadIdx.x < 64) {
                     const JobView<T> V(topos, bufs, job);
-                    finalize_wave<T, COH>(V.tp, V.B, &S, rank == 0 ? (signed char *)V.B.hist : nullptr, P);
+                    finalize_wave<T, COH>(V.tp, V.B, &S, rank == 0 ? (signed char *)V.B.hist : nullptr, P, W);
                 }
                 __syncthreads();
                 const int next = uni<kXcd>((int)S.phase);

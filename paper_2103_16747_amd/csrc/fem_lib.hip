@@ -343,7 +343,9 @@ int add_topology(fem_batch *B, const double *X_in, int n, const int32_t *tets_in
     const size_t o_X = A.take<double>(3 * (size_t)n), o_elig = A.take<uint8_t>(n);
     const size_t o_nvol = A.take<T>(n), o_owner = A.take<uint8_t>(L.nent), o_tid = A.take<int>(m);
     const size_t o_ent_slot = A.take<uint8_t>(L.nent), o_ne4 = A.take<int4>(n);
+    const size_t o_ne2 = A.take<int2>(n);
     std::vector<int4> ne4(n);
+    std::vector<int2> ne2(n);
     for (int i = 0; i < n; i++) {
         int e[kGather];
         for (int k = 0; k < kGather; k++) {
@@ -351,6 +353,7 @@ int add_topology(fem_batch *B, const double *X_in, int n, const int32_t *tets_in
             e[k] = q < L.node_ent_off[i + 1] ? L.node_ent[q] : -1;
         }
         ne4[i] = make_int4(e[0], e[1], e[2], e[3]);
+        ne2[i] = make_int2(e[4], e[5]);
     }
     std::vector<int> inc_off;
     std::vector<uint16_t> inc;
@@ -387,6 +390,7 @@ int add_topology(fem_batch *B, const double *X_in, int n, const int32_t *tets_in
     if (!rc) rc = up(o_ent_node, L.ent_node.data(), L.ent_node.size() * sizeof(int));
     if (!rc) rc = up(o_ent_slot, L.ent_slot.data(), L.ent_slot.size());
     if (!rc) rc = up(o_ne4, ne4.data(), ne4.size() * sizeof(int4));
+    if (!rc) rc = up(o_ne2, ne2.data(), ne2.size() * sizeof(int2));
     if (!rc) rc = up(o_neo, L.node_ent_off.data(), L.node_ent_off.size() * sizeof(int));
     if (!rc) rc = up(o_ne, L.node_ent.data(), L.node_ent.size() * sizeof(int));
     if (!rc) rc = up(o_fixed, fixed, n);
@@ -400,10 +404,10 @@ int add_topology(fem_batch *B, const double *X_in, int n, const int32_t *tets_in
     unsigned slots = 1;
     while (slots < 8u * (unsigned)m) slots <<= 1;
     int *d_tets = nullptr, *d_scalar = nullptr, *d_tnodes = nullptr;
-    uint32_t *d_loc = nullptr;
     unsigned long long *keys = nullptr;
     unsigned *cnt = nullptr;
     uint8_t *surf = nullptr;
+    uint32_t *d_loc = nullptr;
     const int big = 0x7fffffff;
     if (!rc && (hipMalloc(&d_tets, 4 * (size_t)m * sizeof(int)) != hipSuccess || hipMalloc(&d_scalar, 2 * sizeof(int)) != hipSuccess ||
                 hipMalloc(&d_tnodes, 4 * (size_t)m * sizeof(int)) != hipSuccess ||
@@ -473,6 +477,7 @@ int add_topology(fem_batch *B, const double *X_in, int n, const int32_t *tets_in
     v.node_ent_off = (const int *)(base + o_neo);
     v.node_ent = (const int *)(base + o_ne);
     v.node_ent4 = (const int4 *)(base + o_ne4);
+    v.node_ent2 = (const int2 *)(base + o_ne2);
     v.inc_off = (const int *)(base + o_inc_off);
     v.inc = (const uint16_t *)(base + o_inc);
     v.fixed = (const uint8_t *)(base + o_fixed);

@@ -57,7 +57,9 @@ def compare(a, b, precision):
     assert len(a) == len(b)
     for k, ((ua, ia, sa), (ub, ib, sb)) in enumerate(zip(a, b)):
         assert ia["done"] == 1 and ib["done"] == 1
-        assert np.array_equal(sa, sb), k
+        # ended or failed; whether a step that ends at the rounding floor is
+        # reported as such hangs on the residual's last bits
+        assert np.array_equal(np.minimum(sa, 0), np.minimum(sb, 0)), (k, sa, sb)
         assert rel(ua, ub) <= BOUND[precision], (k, rel(ua, ub))
         assert ia["step"] == ib["step"] and ia["steps_ok"] == ib["steps_ok"]
 
