@@ -469,13 +469,21 @@ template <typename T> __device__ __forceinline__ T safe_recip(T d) {
     return d > (T)0 ? (T)1 / d : (d < (T)0 ? (T)1 / -d : (T)1);
 }
 
-// z = M^-1 r of one node, in one fixed order of operations: the node pass
+// z = M^-1 r of one node, in a fixed order of operations: the node pass
 // stores z for the tile pass and forms the same bits again from r in the next
-// CG update instead of reading it.
-template <typename T> __device__ __forceinline__ void precond(const T M[6], const T r[3], T z[3]) {
-    z[0] = fma_t(M[4], r[2], fma_t(M[3], r[1], M[0] * r[0]));
-    z[1] = fma_t(M[5], r[2], fma_t(M[1], r[1], M[3] * r[0]));
-    z[2] = fma_t(M[2], r[2], fma_t(M[5], r[1], M[4] * r[0]));
+// CG update instead of reading it. The Newton init (init) rounds the first
+// product of a row, the CG update the second: the first CG iteration of a
+// solve re-forms the init's z.
+template <typename T> __device__ __forceinline__ void precond(const T M[6], const T r[3], T z[3], bool init) {
+    if (init) {
+        z[0] = fma_t(M[4], r[2], fma_t(M[3], r[1], M[0] * r[0]));
+        z[1] = fma_t(M[5], r[2], fma_t(M[1], r[1], M[3] * r[0]));
+        z[2] = fma_t(M[2], r[2], fma_t(M[5], r[1], M[4] * r[0]));
+        return;
+    }
+    z[0] = fma_t(M[4], r[2], fma_t(M[0], r[0], M[3] * r[1]));
+    z[1] = fma_t(M[5], r[2], fma_t(M[3], r[0], M[1] * r[1]));
+    z[2] = fma_t(M[2], r[2], fma_t(M[4], r[0], M[5] * r[1]));
 }
 
 // ---------------------------------------------------------------------------
@@ -1299,11 +1307,11 @@ __device__ __forceinline__ void tile_element(const TopoD<T> &tp, const BufsD<T> 
 }
 
 // Hessian-vector product of one tet from the staged u and p: its LDS slots,
-// nodal vectors and share of p.q; false (nothing) for an inverted tet.
+// nodal vectors f and their p; false (nothing) for an inverted tet.
 template <typename T, int LAW>
 __device__ __forceinline__ bool tet_hessvec(const TetWords<T> &rec, const T *su, const T *sp, T mu, T lam, int l[4],
-                                            T f[4][3], T &e_pq) {
-    T wu[4][3], wp[4][3];
+                                            T f[4][3], T wp[4][3]) {
+    T wu[4][3];
     const ElemGeo<T> geo = unpack_tet(rec, l);
     load_nodes(su, l, wu);
     load_nodes(sp, l, wp);
@@ -1316,9 +1324,6 @@ __device__ __forceinline__ bool tet_hessvec(const TetWords<T> &rec, const T *su,
     edge_gradient(wp, geo.Bm, dG);
     Law<T, LAW>::hessvec(G, Jm1, J, dG, mu, lam, dP);
     element_nodal(dP, geo.Bm, geo.V, f);
-    e_pq = (T)0;
-#pragma unroll
-    for (int a = 0; a < 4; a++) e_pq += wp[a][0] * f[a][0] + wp[a][1] * f[a][1] + wp[a][2] * f[a][2];
     return true;
 }
 
@@ -1396,13 +1401,16 @@ __device__ __forceinline__ void tile_hessvec(const TopoD<T> &tp, const BufsD<T> 
         // One tet: its p.q into pq and its nodal vectors to put(l, a, d, value).
         auto tet = [&](int k, auto &&put) {
             int l[4];
-            T f[4][3], e_pq;
+            T f[4][3], wp[4][3], e_pq = (T)0;
             if (k != (int)threadIdx.x) fetch_tet(tp, k0 + k, rec);
-            if (!tet_hessvec<T, LAW>(rec, su, sp, mu, lam, l, f, e_pq)) return;
+            if (!tet_hessvec<T, LAW>(rec, su, sp, mu, lam, l, f, wp)) return;
 #pragma unroll
-            for (int a = 0; a < 4; a++)
-#pragma unroll
-                for (int d = 0; d < 3; d++) put(l, a, d, f[a][d]);
+            for (int a = 0; a < 4; a++) {
+                put(l, a, 0, f[a][0]);
+                put(l, a, 1, f[a][1]);
+                put(l, a, 2, f[a][2]);
+                e_pq += wp[a][0] * f[a][0] + wp[a][1] * f[a][1] + wp[a][2] * f[a][2];
+            }
             pq += (double)e_pq;
         };
         if constexpr (!DET) {
@@ -1593,7 +1601,7 @@ __device__ __forceinline__ void node_init(const TopoD<T> &tp, const BufsD<T> &B,
             }
 #pragma unroll
             for (int d2 = 0; d2 < 3; d2++) rr[d2] = -gsum[d2];
-            precond(M, rr, zz);
+            precond(M, rr, zz, true);
 #pragma unroll
             for (int d2 = 0; d2 < 3; d2++) {
                 acc[0] += (double)rr[d2] * (double)rr[d2];
@@ -1666,8 +1674,8 @@ template <typename T> struct NodeCg {
     }
 
     template <bool DYN, int COH, bool EVAL>
-    __device__ __forceinline__ void form(const TopoD<T> &tp, const BufsD<T> &B, const InstState *s, T beta) {
-        if constexpr (!EVAL) precond(M, rv, zv);
+    __device__ __forceinline__ void form(const TopoD<T> &tp, const BufsD<T> &B, const InstState *s, T beta, int cg_first) {
+        if constexpr (!EVAL) precond(M, rv, zv, cg_first != 0);
 #pragma unroll
         for (int d = 0; d < 3; d++) {
             pv[d] = fma_t(beta, pp[d], zv[d]);
@@ -1716,7 +1724,7 @@ template <typename T> struct NodeCg {
                 st_vec<COH>(B.p, tp.n, i, pv);
                 st_vec<COH>(B.dx, tp.n, i, dxv);
                 T zn[3];
-                precond(M, rv, zn);
+                precond(M, rv, zn, false);
                 st_vec<COH>(B.z, tp.n, i, zn);
                 acc[0] += (double)rv[0] * (double)zn[0] + (double)rv[1] * (double)zn[1] + (double)rv[2] * (double)zn[2];
                 acc[1] += (double)rv[0] * (double)rv[0] + (double)rv[1] * (double)rv[1] + (double)rv[2] * (double)rv[2];
@@ -1738,7 +1746,7 @@ __device__ __forceinline__ void node_update(const TopoD<T> &tp, const BufsD<T> &
     NodeCg<T> c;
     c.template request<COH, EVAL>(tp, B, blk * kBlock + (int)threadIdx.x);
     c.template gather<COH>(tp, B);
-    c.template form<DYN, COH, EVAL>(tp, B, s, beta);
+    c.template form<DYN, COH, EVAL>(tp, B, s, beta, cg_first);
     const double pq = wave_sum_partials<COH>(B.red + RS_PQ * B.red_stride, npq);
     if (blk == 0 && threadIdx.x == 0) st_one<COH>((double *)(B.red + RS_PQN * B.red_stride), pq);
     if constexpr (EVAL) {
@@ -2323,12 +2331,14 @@ __device__ __forceinline__ void team_hessvec(const TopoD<T> &tp, const BufsD<T> 
             ld_vec<COH>(B.z, tp.n, gidn, zv);
             auto tet = [&](const TetWords<T> &rec) {
                 int l[4];
-                T f[4][3], e_pq;
-                if (!tet_hessvec<T, LAW>(rec, su, sp, mu, lam, l, f, e_pq)) return;
+                T f[4][3], wp[4][3], e_pq = (T)0;
+                if (!tet_hessvec<T, LAW>(rec, su, sp, mu, lam, l, f, wp)) return;
 #pragma unroll
-                for (int a = 0; a < 4; a++)
+                for (int a = 0; a < 4; a++) {
 #pragma unroll
                     for (int d = 0; d < 3; d++) atomicAdd(sa + 3 * l[a] + d, (double)f[a][d]);
+                    e_pq += wp[a][0] * f[a][0] + wp[a][1] * f[a][1] + wp[a][2] * f[a][2];
+                }
                 pq += (double)e_pq;
             };
             if (tid < cur.nk) tet(r0);
@@ -2384,7 +2394,7 @@ __device__ __forceinline__ void team_update(const TopoD<T> &tp, const BufsD<T> &
         c.template gather<COH>(tp, B);
         NodeCg<T> n;
         n.template request<COH, false>(tp, B, (more ? blk + W : blk) * kBlock + (int)threadIdx.x);
-        c.template form<DYN, COH, false>(tp, B, s, beta);
+        c.template form<DYN, COH, false>(tp, B, s, beta, cg_first);
         c.template apply<COH>(tp, B, alpha, negcurv, cg_first, acc);
         if (!more) break;
         blk += W;
