@@ -388,13 +388,11 @@ int fem_batch_get_contact_patch(fem_batch *batch, int32_t job_id, int32_t *ids, 
 
 /* fem_batch_get_contact_patch for callers that cannot allocate device memory
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc): the same result in the same caller arrays, with the kernel's
- * staging in a static device array of the library (about 1.2 MB per device,
- * held until the process ends) instead of a buffer the batch allocates. It
- * calls no hipMalloc or hipFree and allocates no host memory either: the
- * entries are ordered in the caller's arrays. Every call on one device shares
- * that array, so calls that overlap on one device (from several threads or
- * batches) race and must be serialised by the caller. Limits and errors, in
+ * hipMalloc): the same result in the same caller arrays. It calls no hipMalloc,
+ * hipHostMalloc or hipFree and allocates no host memory: the kernel writes to
+ * pinned memory that the batch sets up with each mesh (36 bytes per
+ * contact-eligible node of the largest), and the entries are ordered in the
+ * caller's arrays. Limits and errors, in
  * addition to those of fem_batch_get_contact_patch: FEM_E_INVALID if the
  * job's mesh has more than FEM_NOALLOC_MAX_CONTACT contact-eligible nodes, or
  * if f or phi is requested without ids (the ids order the entries);

@@ -2547,95 +2547,117 @@ __global__ void k_xcds(unsigned *out) {
 }
 
 // ---------------------------------------------------------------------------
-// Contact patch of one instance at its current state: one block walks the
-// eligible nodes in ascending order and compacts those that carry a contact
-// force, phi < 0 or friction from the lag state (ordered scan): ids, forces
-// on the skin -k min(0, phi) n minus the friction gradient, phi, count and
-// FP64 resultant.
+// Contact patch of one instance at its current state, written straight to
+// pinned host memory (no copies after the kernel): one thread per eligible
+// node, each block compacting its nodes that carry a contact force, phi < 0 or
+// friction from the lag state, into its own segment of the lists (in eligible
+// order): ids, forces on the skin -k min(0, phi) n minus the friction
+// gradient, phi; and its count and FP64 resultant into its head. With lists =
+// false only the heads. The signed distance takes some hundred FP64
+// instructions a node, so the nodes are spread over as many CUs as there are
+// blocks: 47 us for a count and resultant of 3757 nodes when one block walked
+// them and two copies followed.
 // ---------------------------------------------------------------------------
+struct PatchHead {
+    double F[3];
+    int count, pad;
+};
+
 template <typename T>
-__global__ __launch_bounds__(1024) void k_contact_patch(const Topo<T> *topos, const InstBufs<T> *bufs, int inst,
-                                                          int *ids, double *f, double *phi_out, int *count,
-                                                          double *Ftot) {
-    __shared__ int wave_cnt[16];
-    __shared__ double wave_f[16][3];
-    __shared__ int base_s;
-    __shared__ double F_s[3];
+__global__ __launch_bounds__(kBlock) void k_contact_patch(const Topo<T> *topos, const InstBufs<T> *bufs, int inst,
+                                                          PatchHead *heads, int *ids, double *f, double *phi_out,
+                                                          bool lists) {
+    __shared__ int wave_cnt[kWaves];
+    __shared__ double wave_f[kWaves][3];
     const BufsD<T> B = dev_view(bufs[inst]);
     const TopoD<T> tp = dev_view(topos[B.topo]);
-    const Indenter ind = B.s->ind;
-    const bool fric = B.s->mu_f > 0.0;
-    const double eps_f = B.s->eps_f;
-    if (threadIdx.x == 0) {
-        base_s = 0;
-        F_s[0] = F_s[1] = F_s[2] = 0.0;
+    const InstState *s = B.s;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int j = blockIdx.x * kBlock + threadIdx.x;
+    double phi = 0.0, nv[3] = {0.0, 0.0, 0.0}, Hs[6], gf[3] = {0.0, 0.0, 0.0};
+    int i = -1;
+    bool act = false;
+    if (j < tp.nc) {
+        i = tp.cnodes[j];
+        double x[3];
+#pragma unroll
+        for (int d = 0; d < 3; d++) x[d] = tp.X[3 * i + d] + (double)B.u[3 * i + d];
+        sdf_eval(s->ind, s->ind.c, x, false, phi, nv, Hs);
+        act = phi < 0.0;
+        if (s->mu_f > 0.0) {
+            double fl[8], Hf[6], dd[3];
+            const double zero[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+            for (int c = 0; c < 8; c++) fl[c] = B.fr[8 * j + c];
+            if (fl[0] > 0.0) {
+                friction_rel(fl, zero, dd);
+                friction_eval(fl, dd, s->eps_f, gf, Hf);
+                act = true;
+            }
+        }
+    }
+    double fv[3];
+#pragma unroll
+    for (int d = 0; d < 3; d++) fv[d] = act ? (phi < 0.0 ? -s->ind.k * phi * nv[d] : 0.0) - gf[d] : 0.0;
+    const unsigned long long mask = __ballot(act);
+    double sf[3];
+#pragma unroll
+    for (int d = 0; d < 3; d++) sf[d] = wave_sum(fv[d]);
+    if (lane == 0) {
+        wave_cnt[w] = __popcll(mask);
+#pragma unroll
+        for (int d = 0; d < 3; d++) wave_f[w][d] = sf[d];
     }
     __syncthreads();
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    for (int start = 0; start < tp.nc; start += 1024) {
-        const int j = start + threadIdx.x;
-        double phi = 0.0, nv[3] = {0.0, 0.0, 0.0}, Hs[6], gf[3] = {0.0, 0.0, 0.0};
-        int i = -1;
-        bool act = false;
-        if (j < tp.nc) {
-            i = tp.cnodes[j];
-            double x[3];
+    if (lists && act) {
+        size_t slot = (size_t)blockIdx.x * kBlock + __popcll(mask & ((1ull << lane) - 1ull));
+        for (int k = 0; k < w; k++) slot += wave_cnt[k];
+        ids[slot] = i;
+        phi_out[slot] = phi;
 #pragma unroll
-            for (int d = 0; d < 3; d++) x[d] = tp.X[3 * i + d] + (double)B.u[3 * i + d];
-            sdf_eval(ind, ind.c, x, false, phi, nv, Hs);
-            act = phi < 0.0;
-            if (fric) {
-                double fl[8], Hf[6], dd[3];
-                const double zero[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-                for (int c = 0; c < 8; c++) fl[c] = B.fr[8 * j + c];
-                if (fl[0] > 0.0) {
-                    friction_rel(fl, zero, dd);
-                    friction_eval(fl, dd, eps_f, gf, Hf);
-                    act = true;
-                }
-            }
-        }
-        double fv[3];
-#pragma unroll
-        for (int d = 0; d < 3; d++) fv[d] = act ? (phi < 0.0 ? -ind.k * phi * nv[d] : 0.0) - gf[d] : 0.0;
-        const unsigned long long mask = __ballot(act);
-        const int before = __popcll(mask & ((1ull << lane) - 1ull));
-        double sf[3];
-#pragma unroll
-        for (int d = 0; d < 3; d++) sf[d] = wave_sum(fv[d]);
-        if (lane == 0) {
-            wave_cnt[w] = __popcll(mask);
-#pragma unroll
-            for (int d = 0; d < 3; d++) wave_f[w][d] = sf[d];
-        }
-        __syncthreads();
-        int off = base_s;
-        for (int k = 0; k < w; k++) off += wave_cnt[k];
-        if (act) {
-            const int slot = off + before;
-            ids[slot] = i;
-            phi_out[slot] = phi;
-#pragma unroll
-            for (int d = 0; d < 3; d++) f[3 * slot + d] = fv[d];
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            int tot = 0;
-            for (int k = 0; k < 16; k++) {
-                tot += wave_cnt[k];
-#pragma unroll
-                for (int d = 0; d < 3; d++) F_s[d] += wave_f[k][d];
-            }
-            base_s += tot;
-        }
-        __syncthreads();
+        for (int d = 0; d < 3; d++) f[3 * slot + d] = fv[d];
     }
     if (threadIdx.x == 0) {
-        *count = base_s;
+        PatchHead h{};
+        for (int k = 0; k < kWaves; k++) {
+            h.count += wave_cnt[k];
 #pragma unroll
-        for (int d = 0; d < 3; d++) Ftot[d] = F_s[d];
+            for (int d = 0; d < 3; d++) h.F[d] += wave_f[k][d];
+        }
+        heads[blockIdx.x] = h;
     }
+}
+
+// ---------------------------------------------------------------------------
+// Node vectors between the device's numbering and the caller's, with pinned
+// host memory in the path precision on the caller's side: consecutive threads
+// touch consecutive host addresses, and device[c] is the device id of the
+// caller's node c.
+// ---------------------------------------------------------------------------
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_export_nodes(const int *device, const T *src, T *host, int n) {
+    const int q = blockIdx.x * kBlock + threadIdx.x;
+    if (q >= 3 * n) return;
+    const int c = q / 3;
+    host[q] = src[3 * device[c] + (q - 3 * c)];
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_import_nodes(const int *device, const T *host, T *dst, int n) {
+    const int q = blockIdx.x * kBlock + threadIdx.x;
+    if (q >= 3 * n) return;
+    const int c = q / 3;
+    dst[3 * device[c] + (q - 3 * c)] = host[q];
+}
+
+// A job back at rest: zero displacement, velocity and predictor, and its new
+// state from pinned host memory (one launch for three fills and a copy).
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_restart(T *u, T *v, T *ut, int n3, InstState *s, const InstState *from) {
+    const int q = blockIdx.x * kBlock + threadIdx.x;
+    if (q < n3) u[q] = v[q] = ut[q] = (T)0;
+    constexpr int kWords = sizeof(InstState) / 8;
+    if (q < kWords) ((unsigned long long *)s)[q] = ((const unsigned long long *)from)[q];
 }
 
 // ---------------------------------------------------------------------------
@@ -2713,7 +2735,8 @@ __global__ __launch_bounds__(kBlock) void k_tet_stress(const Topo<T> *topos, con
     }
 }
 
-// max_i |u_i| and mean_i |u_i| of one instance (one block, FP64 sums).
+// max_i |u_i| and mean_i |u_i| of one instance (one block, FP64 sums; out in
+// pinned host memory).
 template <typename T>
 __global__ __launch_bounds__(1024) void k_disp_stats(const Topo<T> *topos, const InstBufs<T> *bufs, int inst,
                                                      double *out) {

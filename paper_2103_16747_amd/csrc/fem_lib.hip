@@ -28,23 +28,12 @@
 using namespace fem;
 using namespace fem_layout;
 
-// Staging of fem_batch_get_contact_patch_noalloc: the resultant (4 doubles),
-// the contact count, then per contact node its force (3 doubles), phi and
-// device node id, for at most FEM_NOALLOC_MAX_CONTACT contact-eligible
-// nodes. Each device holds its own copy for the life of the process.
-constexpr size_t kNoAllocBytes = 64 + (size_t)FEM_NOALLOC_MAX_CONTACT * (4 * sizeof(double) + sizeof(int));
-static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
-
 namespace {
 
 thread_local std::string g_last_error;
 
-// Device address of `scratch` per device ordinal, resolved once per device
-// by fem_batch_create with that device current (the host-side symbol is not
-// a device address).
 constexpr int kMaxDevices = 64;
-std::mutex g_scratch_mu;
-void *g_scratch_ptr[kMaxDevices] = {};
+std::mutex g_device_mu;   // set-up facts found once per device
 
 int fail(int code, const std::string &msg) {
     g_last_error = msg;
@@ -131,6 +120,7 @@ constexpr int kRoundEvents = 2 * 64 + 2;
 struct TopoRec {
     int n = 0, n_free = 0, m = 0, ntile = 0, nent = 0, nc = 0, ncb = 0;
     std::vector<int> perm;     // device node id -> caller's node id (node_order())
+    const int *d_inv = nullptr;   // device: caller's node id -> device node id
     // order of the mesh's tile-pass and node-pass blocks in the work tables
     // (spread_order())
     std::vector<int> tile_cols, node_cols;
@@ -143,6 +133,7 @@ struct TopoRec {
 struct InstRec {
     bool live = false;
     bool in_tables = false;   // has blocks in the current work tables
+    long long restarted = -1; // fem_batch::syncs when a restart was enqueued
     int topo = -1;
     void *arena = nullptr;
     InstBufs<float> b32{};
@@ -187,9 +178,10 @@ struct fem_batch {
     SolveParams *d_params = nullptr;
     SolveParams *h_params = nullptr;
     bool tables_dirty = true;
-    void *patch = nullptr;
-    size_t patch_bytes = 0;
-    void *outbuf = nullptr;                 // stress / statistics outputs
+    long long syncs = 0;                    // stream synchronisations so far
+    void *h_patch = nullptr;                // pinned: contact patches, for the largest mesh
+    size_t patch_slots = 0;
+    void *outbuf = nullptr;                 // stress outputs
     size_t outbuf_bytes = 0;
     void *h_stage = nullptr;
     size_t h_stage_bytes = 0;
@@ -224,18 +216,6 @@ namespace {
 
 int set_device(const fem_batch *B) {
     HIP_TRY(hipSetDevice(B->device));
-    return FEM_OK;
-}
-
-// With `device` current: the device address of `scratch` on it, once.
-int resolve_scratch(int device) {
-    if (device < 0 || device >= kMaxDevices) return fail(FEM_E_INVALID, "device ordinal beyond the scratch table");
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    if (g_scratch_ptr[device]) return FEM_OK;
-    void *ptr = nullptr;
-    HIP_TRY(hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)));
-    if (!ptr) return fail(FEM_E_DEVICE, "no device address for the static scratch");
-    g_scratch_ptr[device] = ptr;
     return FEM_OK;
 }
 
@@ -288,7 +268,34 @@ void timer_harvest(fem_batch *B) {
 
 int sync(fem_batch *B) {
     HIP_TRY(hipStreamSynchronize(B->stream));
+    B->syncs++;
     if (B->timer.used) timer_harvest(B);
+    return FEM_OK;
+}
+
+// Pinned staging of the contact patch kernel for `slots` contact slots: a head
+// per block, then forces (3 per slot), phi and device node ids. Set up with
+// each mesh, so that reading a patch allocates nothing.
+struct PatchStage {
+    PatchHead *heads;
+    double *f, *phi;
+    int *ids;
+    explicit PatchStage(const fem_batch *B) {
+        heads = (PatchHead *)B->h_patch;
+        f = (double *)(heads + B->patch_slots / kBlock);
+        phi = f + 3 * B->patch_slots;
+        ids = (int *)(phi + B->patch_slots);
+    }
+};
+
+int patch_stage(fem_batch *B, size_t slots) {
+    if (slots <= B->patch_slots) return FEM_OK;
+    // the old one goes last: the meshes that are there keep theirs if this fails
+    void *mem = nullptr;
+    HIP_TRY(hipHostMalloc(&mem, slots / kBlock * sizeof(PatchHead) + slots * (4 * sizeof(double) + sizeof(int))));
+    if (B->h_patch) (void)hipHostFree(B->h_patch);
+    B->h_patch = mem;
+    B->patch_slots = slots;
     return FEM_OK;
 }
 
@@ -343,7 +350,7 @@ int add_topology(fem_batch *B, const double *X_in, int n, const int32_t *tets_in
     const size_t o_X = A.take<double>(3 * (size_t)n), o_elig = A.take<uint8_t>(n);
     const size_t o_nvol = A.take<T>(n), o_owner = A.take<uint8_t>(L.nent), o_tid = A.take<int>(m);
     const size_t o_ent_slot = A.take<uint8_t>(L.nent), o_ne4 = A.take<int4>(n);
-    const size_t o_ne2 = A.take<int2>(n);
+    const size_t o_ne2 = A.take<int2>(n), o_inv = A.take<int>(n);
     std::vector<int4> ne4(n);
     std::vector<int2> ne2(n);
     for (int i = 0; i < n; i++) {
@@ -391,6 +398,7 @@ int add_topology(fem_batch *B, const double *X_in, int n, const int32_t *tets_in
     if (!rc) rc = up(o_ent_slot, L.ent_slot.data(), L.ent_slot.size());
     if (!rc) rc = up(o_ne4, ne4.data(), ne4.size() * sizeof(int4));
     if (!rc) rc = up(o_ne2, ne2.data(), ne2.size() * sizeof(int2));
+    if (!rc) rc = up(o_inv, inv.data(), inv.size() * sizeof(int));
     if (!rc) rc = up(o_neo, L.node_ent_off.data(), L.node_ent_off.size() * sizeof(int));
     if (!rc) rc = up(o_ne, L.node_ent.data(), L.node_ent.size() * sizeof(int));
     if (!rc) rc = up(o_fixed, fixed, n);
@@ -453,6 +461,11 @@ int add_topology(fem_batch *B, const double *X_in, int n, const int32_t *tets_in
     }
     R.nc = host[1];
     R.ncb = ceil_div(R.nc, kBlock);
+    rc = patch_stage(B, (size_t)R.ncb * kBlock);
+    if (rc) {
+        (void)hipFree(R.arena);
+        return rc;
+    }
     R.n_free = n_free;
     R.tile_cols = spread_order(R.ntile, R.ncb);
     {
@@ -460,6 +473,7 @@ int add_topology(fem_batch *B, const double *X_in, int n, const int32_t *tets_in
         const int nb = ceil_div(n, kBlock), ncg = n_free > kBlock ? ceil_div(n_free, kBlock) : 1;
         R.node_cols = spread_order(ncg, nb - ncg);
     }
+    R.d_inv = (const int *)(base + o_inv);
     R.elig = (uint8_t *)(base + o_elig);
     Topo<T> &v = topo_view<T>(R);
     v.n = n;
@@ -1032,37 +1046,41 @@ int run(fem_batch *B, int max_rounds, int *n_running) {
 // ---------------------------------------------------------------------------
 // Host <-> device node vectors in the batch precision
 // ---------------------------------------------------------------------------
-// Node vectors (n x 3) between the caller's numbering and the device's
-// (perm[device id] = caller id), converted to the batch precision.
-int upload_nodes(fem_batch *B, const std::vector<int> &perm, void *dst, const double *src) {
-    const size_t n = perm.size();
-    TRY(stage(B, std::max<size_t>(3 * n * 8, 64)));
+// Node vectors (n x 3) between the caller's numbering and the device's,
+// converted to and from the batch precision on the host in the caller's order.
+int upload_nodes(fem_batch *B, int topo, void *dst, const double *src) {
+    const TopoRec &tp = B->topos[topo];
+    const size_t n3 = 3 * (size_t)tp.n;
+    TRY(stage(B, std::max<size_t>(n3 * 8, 64)));
+    const int blocks = ceil_div((long long)n3, kBlock);
     if (B->precision == FEM_PREC_FP32) {
         float *h = (float *)B->h_stage;
-        for (size_t i = 0; i < n; i++)
-            for (int d = 0; d < 3; d++) h[3 * i + d] = (float)src[3 * (size_t)perm[i] + d];
+        for (size_t q = 0; q < n3; q++) h[q] = (float)src[q];
+        k_import_nodes<float><<<blocks, kBlock, 0, B->stream>>>(tp.d_inv, h, (float *)dst, tp.n);
     } else {
-        double *h = (double *)B->h_stage;
-        for (size_t i = 0; i < n; i++)
-            for (int d = 0; d < 3; d++) h[3 * i + d] = src[3 * (size_t)perm[i] + d];
+        std::memcpy(B->h_stage, src, n3 * sizeof(double));
+        k_import_nodes<double><<<blocks, kBlock, 0, B->stream>>>(tp.d_inv, (const double *)B->h_stage, (double *)dst, tp.n);
     }
-    HIP_TRY(hipMemcpyAsync(dst, B->h_stage, 3 * n * B->elem(), hipMemcpyHostToDevice, B->stream));
+    TRY(launch_check("k_import_nodes"));
     return sync(B);
 }
 
-int download_nodes(fem_batch *B, const std::vector<int> &perm, double *dst, const void *src) {
-    const size_t n = perm.size();
-    TRY(stage(B, std::max<size_t>(3 * n * 8, 64)));
-    HIP_TRY(hipMemcpyAsync(B->h_stage, src, 3 * n * B->elem(), hipMemcpyDeviceToHost, B->stream));
+int download_nodes(fem_batch *B, int topo, double *dst, const void *src) {
+    const TopoRec &tp = B->topos[topo];
+    const size_t n3 = 3 * (size_t)tp.n;
+    TRY(stage(B, std::max<size_t>(n3 * 8, 64)));
+    const int blocks = ceil_div((long long)n3, kBlock);
+    if (B->precision == FEM_PREC_FP32)
+        k_export_nodes<float><<<blocks, kBlock, 0, B->stream>>>(tp.d_inv, (const float *)src, (float *)B->h_stage, tp.n);
+    else
+        k_export_nodes<double><<<blocks, kBlock, 0, B->stream>>>(tp.d_inv, (const double *)src, (double *)B->h_stage, tp.n);
+    TRY(launch_check("k_export_nodes"));
     TRY(sync(B));
     if (B->precision == FEM_PREC_FP32) {
         const float *h = (const float *)B->h_stage;
-        for (size_t i = 0; i < n; i++)
-            for (int d = 0; d < 3; d++) dst[3 * (size_t)perm[i] + d] = (double)h[3 * i + d];
+        for (size_t q = 0; q < n3; q++) dst[q] = (double)h[q];
     } else {
-        const double *h = (const double *)B->h_stage;
-        for (size_t i = 0; i < n; i++)
-            for (int d = 0; d < 3; d++) dst[3 * (size_t)perm[i] + d] = h[3 * i + d];
+        std::memcpy(dst, B->h_stage, n3 * sizeof(double));
     }
     return FEM_OK;
 }
@@ -1085,17 +1103,17 @@ void *inst_ptr(fem_batch *B, int slot, int which) {
 // numbering: the stored velocity plus the update the next step would make,
 // v + (u - ut) / dt (zero for quasi-static jobs).
 int download_velocity(fem_batch *B, int slot, double *v) {
-    const std::vector<int> &perm = B->topos[B->insts[slot].topo].perm;
-    const size_t n = perm.size();
+    const int topo = B->insts[slot].topo;
+    const size_t n = (size_t)B->topos[topo].n;
     const double dt = B->h_states[slot].dt;
     if (!(dt > 0.0)) {
         std::fill(v, v + 3 * n, 0.0);
         return FEM_OK;
     }
     std::vector<double> u(3 * n), ut(3 * n);
-    TRY(download_nodes(B, perm, v, inst_ptr(B, slot, V_V)));
-    TRY(download_nodes(B, perm, u.data(), inst_ptr(B, slot, V_U)));
-    TRY(download_nodes(B, perm, ut.data(), inst_ptr(B, slot, V_UT)));
+    TRY(download_nodes(B, topo, v, inst_ptr(B, slot, V_V)));
+    TRY(download_nodes(B, topo, u.data(), inst_ptr(B, slot, V_U)));
+    TRY(download_nodes(B, topo, ut.data(), inst_ptr(B, slot, V_UT)));
     for (size_t q = 0; q < 3 * n; q++) v[q] += (u[q] - ut[q]) / dt;
     return FEM_OK;
 }
@@ -1117,12 +1135,13 @@ void batch_release(fem_batch *B) {
             (void)hipEventDestroy(B->timer.ev[i][1]);
         }
     void *dev[] = {B->d_states, B->d_topos, B->d_bufs, B->d_work_tile, B->d_work_node, B->d_live, B->d_params,
-                   B->patch, B->outbuf, B->d_team, B->d_team_ctl};
+                   B->outbuf, B->d_team, B->d_team_ctl};
     for (void *p : dev)
         if (p) (void)hipFree(p);
     if (B->h_states) (void)hipHostFree(B->h_states);
     if (B->h_params) (void)hipHostFree(B->h_params);
     if (B->h_stage) (void)hipHostFree(B->h_stage);
+    if (B->h_patch) (void)hipHostFree(B->h_patch);
     if (B->own_stream && B->stream) (void)hipStreamDestroy(B->stream);
     if (B->stream2) (void)hipStreamDestroy(B->stream2);
     if (B->xev_created)
@@ -1136,7 +1155,7 @@ void batch_release(fem_batch *B) {
 int xcd_count(fem_batch *B) {
     static int known[kMaxDevices], cus[kMaxDevices];
     static bool done[kMaxDevices];
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    std::lock_guard<std::mutex> lock(g_device_mu);
     const int d = B->device;
     if (!done[d]) {
         constexpr int kBlocks = 4 * kMaxXcds * 8;
@@ -1177,7 +1196,7 @@ int batch_create(const fem_config *cfg, int capacity, fem_batch **out) {
     B->capacity = capacity;
     B->insts.resize(capacity);
     int rc = set_device(B);
-    if (!rc) rc = resolve_scratch(B->device);
+    if (!rc && B->device >= kMaxDevices) rc = fail(FEM_E_INVALID, "device ordinal beyond the device table");
     if (!rc) {
         if (c.stream) {
             B->stream = (hipStream_t)c.stream;
@@ -1342,111 +1361,48 @@ void fill_step_info(const InstState &s, int m, fem_step_info *info) {
     info->tet_updates = (int64_t)m * (int64_t)(s.st_grad + s.st_hv);
 }
 
-// Staging of the contact patch kernel in a buffer of `cap` contact slots:
-// resultant (4 doubles), count, then forces (3 cap doubles), phi (cap
-// doubles) and device node ids (cap ints).
-struct PatchStage {
-    double *F, *f, *phi;
-    int *count, *ids;
-    PatchStage(void *base, size_t cap) {
-        char *b = (char *)base;
-        F = (double *)b;
-        count = (int *)(b + 32);
-        f = (double *)(b + 64);
-        phi = f + 3 * cap;
-        ids = (int *)(phi + cap);
+// Runs the contact patch kernel of one instance and adds up its blocks' heads
+// in block order.
+int contact_patch_launch(fem_batch *B, int slot, bool lists, int *count, double Ft[3]) {
+    const int blocks = B->topos[B->insts[slot].topo].ncb;
+    const PatchStage st(B);
+    if (blocks > 0) {
+        if (B->precision == FEM_PREC_FP32)
+            k_contact_patch<float><<<blocks, kBlock, 0, B->stream>>>((const Topo<float> *)B->d_topos,
+                                                                     (const InstBufs<float> *)B->d_bufs, slot, st.heads,
+                                                                     st.ids, st.f, st.phi, lists);
+        else
+            k_contact_patch<double><<<blocks, kBlock, 0, B->stream>>>((const Topo<double> *)B->d_topos,
+                                                                      (const InstBufs<double> *)B->d_bufs, slot,
+                                                                      st.heads, st.ids, st.f, st.phi, lists);
+        TRY(launch_check("k_contact_patch"));
     }
-};
-
-// Runs the contact patch kernel of one instance into `st` and reads the
-// count and resultant back (the kernel writes every slot it reports and
-// clears the count and resultant itself).
-int contact_patch_launch(fem_batch *B, int slot, const PatchStage &st, int *count, double Ft[3]) {
-    if (B->precision == FEM_PREC_FP32)
-        k_contact_patch<float><<<1, 1024, 0, B->stream>>>((const Topo<float> *)B->d_topos,
-                                                            (const InstBufs<float> *)B->d_bufs, slot, st.ids, st.f,
-                                                            st.phi, st.count, st.F);
-    else
-        k_contact_patch<double><<<1, 1024, 0, B->stream>>>((const Topo<double> *)B->d_topos,
-                                                             (const InstBufs<double> *)B->d_bufs, slot, st.ids, st.f,
-                                                             st.phi, st.count, st.F);
-    TRY(launch_check("k_contact_patch"));
-    HIP_TRY(hipMemcpyAsync(count, st.count, sizeof(int), hipMemcpyDeviceToHost, B->stream));
-    HIP_TRY(hipMemcpyAsync(Ft, st.F, 3 * sizeof(double), hipMemcpyDeviceToHost, B->stream));
-    return sync(B);
-}
-
-int contact_patch_impl(fem_batch *B, int slot, int32_t *ids, double *f, double *phi, int32_t capacity,
-                       int32_t *n_contact, double F_total[3]) {
-    const int n = B->topos[B->insts[slot].topo].n;
-    const size_t need = 64 + (size_t)n * (sizeof(int) + 4 * sizeof(double)) + 256;
-    if (B->patch_bytes < need) {
-        if (B->patch) (void)hipFree(B->patch);
-        B->patch = nullptr;
-        B->patch_bytes = 0;
-        HIP_TRY(hipMalloc(&B->patch, need));
-        B->patch_bytes = need;
-    }
-    if (B->tables_dirty) TRY(B->precision == FEM_PREC_FP32 ? rebuild_tables<float>(B) : rebuild_tables<double>(B));
-    const PatchStage st(B->patch, (size_t)n);
-    double *d_f = st.f, *d_phi = st.phi;
-    int *d_ids = st.ids;
-    int count = 0;
-    double Ft[3];
-    TRY(contact_patch_launch(B, slot, st, &count, Ft));
-    *n_contact = count;
-    if (F_total) std::memcpy(F_total, Ft, sizeof Ft);
-    if (capacity < count) return fail(FEM_E_BUFFER, "capacity below the contact count");
-    if (count > 0 && (ids || f || phi)) {
-        // Device node ids -> caller ids, listed in ascending caller order.
-        std::vector<int> hid(count);
-        std::vector<double> hf(3 * (size_t)count), hphi(count);
-        HIP_TRY(hipMemcpyAsync(hid.data(), d_ids, count * sizeof(int), hipMemcpyDeviceToHost, B->stream));
-        HIP_TRY(hipMemcpyAsync(hf.data(), d_f, 3 * (size_t)count * sizeof(double), hipMemcpyDeviceToHost, B->stream));
-        HIP_TRY(hipMemcpyAsync(hphi.data(), d_phi, count * sizeof(double), hipMemcpyDeviceToHost, B->stream));
-        TRY(sync(B));
-        const std::vector<int> &perm = B->topos[B->insts[slot].topo].perm;
-        std::vector<int> idx(count);
-        for (int k = 0; k < count; k++) idx[k] = k;
-        std::sort(idx.begin(), idx.end(), [&](int a, int b) { return perm[hid[a]] < perm[hid[b]]; });
-        for (int k = 0; k < count; k++) {
-            const int src = idx[k];
-            if (ids) ids[k] = perm[hid[src]];
-            if (f)
-                for (int d = 0; d < 3; d++) f[3 * (size_t)k + d] = hf[3 * (size_t)src + d];
-            if (phi) phi[k] = hphi[src];
-        }
+    TRY(sync(B));
+    *count = 0;
+    for (int d = 0; d < 3; d++) Ft[d] = 0.0;
+    for (int b = 0; b < blocks; b++) {
+        *count += st.heads[b].count;
+        for (int d = 0; d < 3; d++) Ft[d] += st.heads[b].F[d];
     }
     return FEM_OK;
 }
 
-// The contact patch staged in the device's static scratch: the same kernel
-// and the same caller-visible result as contact_patch_impl, with the caller's
-// arrays as the only host storage (the device ids are mapped to caller ids
-// and the entries ordered by a heap sort in place).
-int contact_patch_noalloc_impl(fem_batch *B, int slot, int32_t *ids, double *f, double *phi, int32_t capacity,
-                               int32_t *n_contact, double F_total[3]) {
+// The patch's entries in ascending caller order in the caller's arrays (ids
+// may be null with f and phi null). The blocks' segments are emptied into the
+// arrays, the device ids mapped to caller ids and the entries ordered by a
+// heap sort in place, so nothing is allocated.
+void contact_patch_entries(fem_batch *B, int slot, int32_t *ids, double *f, double *phi) {
     const TopoRec &tp = B->topos[B->insts[slot].topo];
-    if (tp.nc > FEM_NOALLOC_MAX_CONTACT)
-        return fail(FEM_E_INVALID, "mesh has " + std::to_string(tp.nc) + " contact-eligible nodes, above the " +
-                                       std::to_string(FEM_NOALLOC_MAX_CONTACT) + " the static scratch holds");
-    if (B->tables_dirty) return fail(FEM_E_STATE, "jobs changed since the last fem_batch_run (run the batch first)");
-    if ((f || phi) && !ids) return fail(FEM_E_INVALID, "ids is needed to order f and phi");
-    void *base = g_scratch_ptr[B->device];
-    if (!base) return fail(FEM_E_STATE, "static scratch not resolved on this device");
-    const PatchStage st(base, (size_t)FEM_NOALLOC_MAX_CONTACT);
+    const PatchStage st(B);
     int count = 0;
-    double Ft[3];
-    TRY(contact_patch_launch(B, slot, st, &count, Ft));
-    *n_contact = count;
-    if (F_total) std::memcpy(F_total, Ft, sizeof Ft);
-    if (capacity < count) return fail(FEM_E_BUFFER, "capacity below the contact count");
-    if (count == 0 || !ids) return FEM_OK;
-    HIP_TRY(hipMemcpyAsync(ids, st.ids, count * sizeof(int), hipMemcpyDeviceToHost, B->stream));
-    if (f) HIP_TRY(hipMemcpyAsync(f, st.f, 3 * (size_t)count * sizeof(double), hipMemcpyDeviceToHost, B->stream));
-    if (phi) HIP_TRY(hipMemcpyAsync(phi, st.phi, count * sizeof(double), hipMemcpyDeviceToHost, B->stream));
-    TRY(sync(B));
-    for (int k = 0; k < count; k++) ids[k] = tp.perm[ids[k]];
+    for (int b = 0; b < tp.ncb; b++)
+        for (int e = 0; e < st.heads[b].count; e++, count++) {
+            const size_t q = (size_t)b * kBlock + e;
+            ids[count] = tp.perm[st.ids[q]];
+            if (f)
+                for (int d = 0; d < 3; d++) f[3 * (size_t)count + d] = st.f[3 * q + d];
+            if (phi) phi[count] = st.phi[q];
+        }
     auto swap_entries = [&](int a, int b) {
         std::swap(ids[a], ids[b]);
         if (f)
@@ -1468,6 +1424,39 @@ int contact_patch_noalloc_impl(fem_batch *B, int slot, int32_t *ids, double *f, 
         swap_entries(0, end);
         sift_down(0, end);
     }
+}
+
+int contact_patch_impl(fem_batch *B, int slot, int32_t *ids, double *f, double *phi, int32_t capacity,
+                       int32_t *n_contact, double F_total[3]) {
+    if (B->tables_dirty) TRY(B->precision == FEM_PREC_FP32 ? rebuild_tables<float>(B) : rebuild_tables<double>(B));
+    int count = 0;
+    double Ft[3];
+    TRY(contact_patch_launch(B, slot, capacity > 0 && (ids || f || phi), &count, Ft));
+    *n_contact = count;
+    if (F_total) std::memcpy(F_total, Ft, sizeof Ft);
+    if (capacity < count) return fail(FEM_E_BUFFER, "capacity below the contact count");
+    if (count == 0 || !(ids || f || phi)) return FEM_OK;
+    std::vector<int32_t> order;   // the ids order the entries, asked for or not
+    if (!ids) order.resize(count);
+    contact_patch_entries(B, slot, ids ? ids : order.data(), f, phi);
+    return FEM_OK;
+}
+
+int contact_patch_noalloc_impl(fem_batch *B, int slot, int32_t *ids, double *f, double *phi, int32_t capacity,
+                               int32_t *n_contact, double F_total[3]) {
+    const TopoRec &tp = B->topos[B->insts[slot].topo];
+    if (tp.nc > FEM_NOALLOC_MAX_CONTACT)
+        return fail(FEM_E_INVALID, "mesh has " + std::to_string(tp.nc) + " contact-eligible nodes, above the limit of " +
+                                       std::to_string(FEM_NOALLOC_MAX_CONTACT));
+    if (B->tables_dirty) return fail(FEM_E_STATE, "jobs changed since the last fem_batch_run (run the batch first)");
+    if ((f || phi) && !ids) return fail(FEM_E_INVALID, "ids is needed to order f and phi");
+    int count = 0;
+    double Ft[3];
+    TRY(contact_patch_launch(B, slot, ids && capacity > 0, &count, Ft));
+    *n_contact = count;
+    if (F_total) std::memcpy(F_total, Ft, sizeof Ft);
+    if (capacity < count) return fail(FEM_E_BUFFER, "capacity below the contact count");
+    if (count > 0 && ids) contact_patch_entries(B, slot, ids, f, phi);
     return FEM_OK;
 }
 
@@ -1512,8 +1501,8 @@ int tet_stress_impl(fem_batch *B, int slot, double *sigma, double *vm, int64_t c
 
 int disp_stats_impl(fem_batch *B, int slot, double *max_norm, double *mean_norm) {
     if (B->tables_dirty) TRY(B->precision == FEM_PREC_FP32 ? rebuild_tables<float>(B) : rebuild_tables<double>(B));
-    TRY(outbuf(B, 2 * sizeof(double)));
-    double *d = (double *)B->outbuf, h[2];
+    TRY(stage(B, 2 * sizeof(double)));
+    double *d = (double *)B->h_stage;
     if (B->precision == FEM_PREC_FP32)
         k_disp_stats<float><<<1, 1024, 0, B->stream>>>((const Topo<float> *)B->d_topos,
                                                        (const InstBufs<float> *)B->d_bufs, slot, d);
@@ -1521,10 +1510,9 @@ int disp_stats_impl(fem_batch *B, int slot, double *max_norm, double *mean_norm)
         k_disp_stats<double><<<1, 1024, 0, B->stream>>>((const Topo<double> *)B->d_topos,
                                                         (const InstBufs<double> *)B->d_bufs, slot, d);
     TRY(launch_check("k_disp_stats"));
-    HIP_TRY(hipMemcpyAsync(h, d, sizeof h, hipMemcpyDeviceToHost, B->stream));
     TRY(sync(B));
-    if (max_norm) *max_norm = h[0];
-    if (mean_norm) *mean_norm = h[1];
+    if (max_norm) *max_norm = d[0];
+    if (mean_norm) *mean_norm = d[1];
     return FEM_OK;
 }
 
@@ -1664,7 +1652,7 @@ int fem_get_displacements(const fem_mesh *M, double *u, int64_t capacity) {
     if (!M || !u) return fail(FEM_E_INVALID, "null argument");
     if (capacity < 3LL * M->n) return fail(FEM_E_BUFFER, "capacity below 3 n");
     TRY(set_device(M->batch));
-    return download_nodes(M->batch, M->batch->topos[0].perm, u, inst_ptr(M->batch, 0, V_U));
+    return download_nodes(M->batch, 0, u, inst_ptr(M->batch, 0, V_U));
 }
 
 int fem_set_displacements(fem_mesh *M, const double *u, int64_t count) {
@@ -1674,7 +1662,7 @@ int fem_set_displacements(fem_mesh *M, const double *u, int64_t count) {
     for (int64_t i = 0; i < count; i++)
         if (!is_finite(u[i])) return fail(FEM_E_INVALID, "non-finite displacement");
     TRY(set_device(M->batch));
-    TRY(upload_nodes(M->batch, M->batch->topos[0].perm, inst_ptr(M->batch, 0, V_U), u));
+    TRY(upload_nodes(M->batch, 0, inst_ptr(M->batch, 0, V_U), u));
     // The predictor follows, so the stored velocity is kept as it is.
     HIP_TRY(hipMemcpyAsync(inst_ptr(M->batch, 0, V_UT), inst_ptr(M->batch, 0, V_U), 3 * (size_t)M->n * M->batch->elem(),
                            hipMemcpyDeviceToDevice, M->batch->stream));
@@ -1727,7 +1715,7 @@ int fem_set_velocities(fem_mesh *M, const double *v, int64_t count) {
     for (int64_t i = 0; i < count; i++)
         if (!is_finite(v[i])) return fail(FEM_E_INVALID, "non-finite velocity");
     TRY(set_device(M->batch));
-    TRY(upload_nodes(M->batch, M->batch->topos[0].perm, inst_ptr(M->batch, 0, V_V), v));
+    TRY(upload_nodes(M->batch, 0, inst_ptr(M->batch, 0, V_V), v));
     HIP_TRY(hipMemcpyAsync(inst_ptr(M->batch, 0, V_UT), inst_ptr(M->batch, 0, V_U), 3 * (size_t)M->n * M->batch->elem(),
                            hipMemcpyDeviceToDevice, M->batch->stream));
     return sync(M->batch);
@@ -1787,7 +1775,7 @@ int fem_eval_gradient(fem_mesh *M, double *g, int64_t capacity, double *energy, 
     TRY(run(B, 2, nullptr));
     if (energy) *energy = B->h_states[0].E;
     if (min_J) *min_J = B->h_states[0].minJ;
-    if (g) return download_nodes(B, B->topos[0].perm, g, inst_ptr(B, 0, V_G));
+    if (g) return download_nodes(B, 0, g, inst_ptr(B, 0, V_G));
     return FEM_OK;
 }
 
@@ -1815,14 +1803,14 @@ int fem_eval_hessvec(fem_mesh *M, const fem_solve_params *params, const double *
     TRY(run(B, 2, nullptr));
     // q = H v through the CG kernels with z = v, p_prev = 0, beta = 0.
     std::vector<double> zeros(3 * (size_t)M->n, 0.0);
-    TRY(upload_nodes(B, B->topos[0].perm, inst_ptr(B, 0, V_Z), v));
-    TRY(upload_nodes(B, B->topos[0].perm, inst_ptr(B, 0, V_P), zeros.data()));
+    TRY(upload_nodes(B, 0, inst_ptr(B, 0, V_Z), v));
+    TRY(upload_nodes(B, 0, inst_ptr(B, 0, V_P), zeros.data()));
     TRY(read_states(B));
     B->h_states[0].beta = 0.0;
     B->h_states[0].phase = PH_EVAL_HV;
     TRY(write_state(B, 0));
     TRY(run(B, 2, nullptr));
-    return download_nodes(B, B->topos[0].perm, q, inst_ptr(B, 0, V_Q));
+    return download_nodes(B, 0, q, inst_ptr(B, 0, V_Q));
 }
 
 int fem_set_kernel_timing(fem_mesh *M, int32_t every) {
@@ -1903,17 +1891,25 @@ int fem_batch_restart_job(fem_batch *B, int32_t job_id, double E, double nu, con
         return fail(FEM_E_INVALID, "unknown constitutive model");
     TRY(check_friction(job->friction, job->friction_eps));
     TRY(set_device(B));
-    const int n = B->topos[B->insts[job_id].topo].n;
-    for (int which : {V_U, V_V, V_UT})
-        HIP_TRY(hipMemsetAsync(inst_ptr(B, job_id, which), 0, 3 * (size_t)n * B->elem(), B->stream));
+    const int n3 = 3 * B->topos[B->insts[job_id].topo].n;
+    // an earlier restart may not have read its state yet
+    if (B->insts[job_id].restarted == B->syncs) TRY(sync(B));
+    B->insts[job_id].restarted = B->syncs;
     const int hint = B->h_states[job_id].last_cg;
     init_job_state(B->h_states[job_id], E, nu, ind, job->c0, job->direction, job->depth, job->steps, job->dt,
                    job->density, job->model, job_friction(job));
     B->h_states[job_id].last_cg = hint;
     // Stream-ordered before any later kernel or state read; the pinned source
-    // slot is not written again until the host has synchronised.
-    HIP_TRY(hipMemcpyAsync(B->d_states + job_id, B->h_states + job_id, sizeof(InstState), hipMemcpyHostToDevice,
-                           B->stream));
+    // slot is not written again until the host has synchronised (above).
+    const int blocks = ceil_div(std::max<long long>(n3, sizeof(InstState) / 8), kBlock);
+    if (B->precision == FEM_PREC_FP32) {
+        const InstBufs<float> &b = B->insts[job_id].b32;
+        k_restart<float><<<blocks, kBlock, 0, B->stream>>>(b.u, b.v, b.ut, n3, B->d_states + job_id, B->h_states + job_id);
+    } else {
+        const InstBufs<double> &b = B->insts[job_id].b64;
+        k_restart<double><<<blocks, kBlock, 0, B->stream>>>(b.u, b.v, b.ut, n3, B->d_states + job_id, B->h_states + job_id);
+    }
+    TRY(launch_check("k_restart"));
     return FEM_OK;
 }
 
@@ -2041,7 +2037,7 @@ int fem_batch_get_displacements(fem_batch *B, int32_t job, double *u, int64_t ca
     const int n = B->topos[B->insts[job].topo].n;
     if (capacity < 3LL * n) return fail(FEM_E_BUFFER, "capacity below 3 n");
     TRY(set_device(B));
-    return download_nodes(B, B->topos[B->insts[job].topo].perm, u, inst_ptr(B, job, V_U));
+    return download_nodes(B, B->insts[job].topo, u, inst_ptr(B, job, V_U));
 }
 
 int fem_batch_get_contact_patch(fem_batch *B, int32_t job, int32_t *ids, double *f, double *phi, int32_t capacity,

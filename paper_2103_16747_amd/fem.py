@@ -225,7 +225,7 @@ def fem_step(h, params: fem_solve_params | None = None) -> dict:
 
 
 def fem_get_displacements(h, n: int) -> np.ndarray:
-    u = np.zeros((n, 3))
+    u = np.empty((n, 3))
     _check(load().fem_get_displacements(h, _dp(u), u.size))
     return u
 
@@ -236,8 +236,8 @@ def fem_set_displacements(h, u):
 
 
 def fem_get_tet_stress(h, m: int):
-    sig = np.zeros((m, 6))
-    vm = np.zeros(m)
+    sig = np.empty((m, 6))
+    vm = np.empty(m)
     _check(load().fem_get_tet_stress(h, _dp(sig), _dp(vm), m))
     return sig, vm
 
@@ -249,8 +249,8 @@ def fem_get_displacement_stats(h):
 
 
 def fem_batch_get_tet_stress(h, job: int, m: int):
-    sig = np.zeros((m, 6))
-    vm = np.zeros(m)
+    sig = np.empty((m, 6))
+    vm = np.empty(m)
     _check(load().fem_batch_get_tet_stress(h, int(job), _dp(sig), _dp(vm), m))
     return sig, vm
 
@@ -266,7 +266,7 @@ def fem_set_dynamics(h, dt: float):
 
 
 def fem_get_velocities(h, n: int) -> np.ndarray:
-    v = np.zeros((n, 3))
+    v = np.empty((n, 3))
     _check(load().fem_get_velocities(h, _dp(v), v.size))
     return v
 
@@ -300,7 +300,7 @@ def fem_get_mesh_info(h):
 
 
 def fem_eval_gradient(h, n: int):
-    g = np.zeros((n, 3))
+    g = np.empty((n, 3))
     e, mj = C.c_double(), C.c_double()
     _check(load().fem_eval_gradient(h, _dp(g), g.size, C.byref(e), C.byref(mj)))
     return g, e.value, mj.value
@@ -515,13 +515,13 @@ def fem_batch_job_step_status(h, job: int) -> np.ndarray:
 
 
 def fem_batch_get_displacements(h, job: int, n: int) -> np.ndarray:
-    u = np.zeros((n, 3))
+    u = np.empty((n, 3))
     _check(load().fem_batch_get_displacements(h, int(job), _dp(u), u.size))
     return u
 
 
 def fem_batch_get_velocities(h, job: int, n: int) -> np.ndarray:
-    v = np.zeros((n, 3))
+    v = np.empty((n, 3))
     _check(load().fem_batch_get_velocities(h, int(job), _dp(v), v.size))
     return v
 
