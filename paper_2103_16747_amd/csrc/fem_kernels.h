@@ -2288,6 +2288,10 @@ template <typename T, int LAW, int COH>
 __device__ __forceinline__ void team_hessvec(const TopoD<T> &tp, const BufsD<T> &B, const InstState *s, int rank, int W,
                                              double *pool) {
     static_assert(kTileTets == 2 * kBlock, "two tets per thread");
+    // A team may be larger than this mesh's list (jobs on larger meshes share
+    // it): a member without an item has no slot among the partials, whose
+    // stride is the mesh's.
+    if (rank >= tp.ntile + tp.ncb) return;
     const T beta = uni<COH>((T)s->beta);
     const T mu = uni<COH>((T)s->mu), lam = uni<COH>((T)s->lam);
     const double cm = uni<COH>(s->mdt2);

@@ -105,6 +105,18 @@ def test_mixed_laws_friction_and_time_steps(precision):
     compare(solve(meshes, jobs, precision, 1), solve(meshes, jobs, precision, 0), precision)
 
 
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_meshes_smaller_than_the_team_they_share(precision):
+    """Jobs of one cell, 5k and 20k tets on every XCD: the larger meshes set
+    the team's size, so most members have no tile of the small ones, whose
+    partial sums have fewer slots (4 and 24) than the team has members; behind
+    the smallest one's lie its velocities, which its time steps read."""
+    print("case", precision, flush=True)
+    meshes = [W.block_mesh((1, 1, 1), (2e-3, 2e-3, 2e-3)), W.fingertip_mesh(5000), W.fingertip_mesh(20000)]
+    jobs = [jobs_on(meshes[0], 10, 3, dt=1e-4), jobs_on(meshes[1], 10, 2), jobs_on(meshes[2], 10, 1)]
+    compare(solve(meshes, jobs, precision, 1), solve(meshes, jobs, precision, 0), precision)
+
+
 def test_more_jobs_than_teams():
     """Teams that take several jobs one after another, in whole runs and in
     rounds that leave every job unfinished in between."""
