@@ -2116,14 +2116,18 @@ struct TeamSync {
     TeamLine group[kTeamGroups];    // arrivals of members
 };
 constexpr int kMaxXcds = 16;
-struct TeamCtl {
-    TeamLine ticket[kMaxXcds];   // places taken, per `span` XCDs
-    TeamLine leave;              // workgroups that have left
-    TeamSync sync[1];            // one per team
-};
 // Counters that only grow; the host takes differences between launches.
 struct TeamStat {
     unsigned done, calledoff, stuck, steps;
+};
+struct TeamCtl {
+    TeamLine ticket[kMaxXcds];   // places taken, per `span` XCDs
+    TeamLine leave;              // workgroups that have left
+    // the host's mirror of the states and of TeamStat (pinned); here, not in
+    // the arguments, which would hold scalar registers throughout
+    InstState *mirror;
+    TeamStat *stat_mirror;
+    TeamSync sync[1];            // one per team
 };
 constexpr unsigned kCalledOff = 0xffffffffu;
 constexpr unsigned kCalledOffBit = 0x80000000u;
@@ -2523,14 +2527,23 @@ __global__ __launch_bounds__(kBlock) void k_team(const Topo<T> *topos, const Ins
                 if (threadIdx.x == 0 && c > 0 && !running_phase(phase)) ag_add(&stat->done, 1u);
                 const JobView<T> V(topos, bufs, job);
                 unsigned long long *gs = (unsigned long long *)(InstState *)V.B.s;
-                for (int k = threadIdx.x; k < kStateWords; k += kBlock) gs[k] = ls[k];
+                unsigned long long *hs = (unsigned long long *)(ctl->mirror + job);
+                for (int k = threadIdx.x; k < kStateWords; k += kBlock) gs[k] = hs[k] = ls[k];
             }
         }
         if (rank == 0 && threadIdx.x == 0)
             __hip_atomic_fetch_max(&stat->steps, steps_base + (unsigned)most, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    // the last workgroup to leave clears the counters for the next launch
+    // the last workgroup to leave hands the launch's counters to the host
+    // (this thread's own additions to them have arrived before it leaves) and
+    // clears the teams' for the next launch
+    if (threadIdx.x == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if (threadIdx.x == 0 && ag_add(&ctl->leave.v, 1u) == gridDim.x - 1) {
+        TeamStat *stat_mirror = ctl->stat_mirror;
+        stat_mirror->done = ag_load(&stat->done);
+        stat_mirror->calledoff = ag_load(&stat->calledoff);
+        stat_mirror->stuck = ag_load(&stat->stuck);
+        stat_mirror->steps = ag_load(&stat->steps);
         for (int x = 0; x < kMaxXcds; x++) {
             const XcdDesc Y = ld_table<XcdDesc>(xcds, x);
             for (int t = Y.team0; t < Y.team0 + Y.nteam; t++) {
@@ -2646,12 +2659,23 @@ __global__ __launch_bounds__(kBlock) void k_export_nodes(const int *device, cons
     host[q] = src[3 * device[c] + (q - 3 * c)];
 }
 
+// also: a second vector that takes the same values (also_zero: zeros), or null.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_import_nodes(const int *device, const T *host, T *dst, int n) {
+__global__ __launch_bounds__(kBlock) void k_import_nodes(const int *device, const T *host, T *dst, T *also,
+                                                         bool also_zero, int n) {
     const int q = blockIdx.x * kBlock + threadIdx.x;
     if (q >= 3 * n) return;
-    const int c = q / 3;
-    dst[3 * device[c] + (q - 3 * c)] = host[q];
+    const int c = q / 3, to = 3 * device[c] + (q - 3 * c);
+    const T v = host[q];
+    dst[to] = v;
+    if (also) also[to] = also_zero ? (T)0 : v;
+}
+
+// A job's state from pinned host memory.
+__global__ void k_put_state(InstState *s, const InstState *from) {
+    constexpr int kWords = sizeof(InstState) / 8;
+    for (int q = threadIdx.x; q < kWords; q += blockDim.x)
+        ((unsigned long long *)s)[q] = ((const unsigned long long *)from)[q];
 }
 
 // A job back at rest: zero displacement, velocity and predictor, and its new

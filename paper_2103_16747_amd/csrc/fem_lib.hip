@@ -133,7 +133,7 @@ struct TopoRec {
 struct InstRec {
     bool live = false;
     bool in_tables = false;   // has blocks in the current work tables
-    long long restarted = -1; // fem_batch::syncs when a restart was enqueued
+    long long sent = -1;      // fem_batch::syncs when a kernel that reads the mirror's state was enqueued
     int topo = -1;
     void *arena = nullptr;
     InstBufs<float> b32{};
@@ -179,6 +179,9 @@ struct fem_batch {
     SolveParams *h_params = nullptr;
     bool tables_dirty = true;
     long long syncs = 0;                    // stream synchronisations so far
+    bool params_there = false;     // d_params holds *h_params (or will, in stream order)
+    long long params_sent = -1;    // `syncs` when they were sent
+    bool work_built = false;       // the step kernels' work tables are those of the running jobs
     void *h_patch = nullptr;                // pinned: contact patches, for the largest mesh
     size_t patch_slots = 0;
     void *outbuf = nullptr;                 // stress outputs
@@ -566,25 +569,52 @@ void free_instance(fem_batch *B, int slot) {
 
 inline bool host_running(int ph) { return ph != PH_IDLE && ph != PH_DONE; }
 
-// Work tables: tile (+ contact) blocks and node blocks of every running
-// instance (as of the host's last view of the states), ordered tile-major so
-// one tile of consecutive instances is processed back to back (on one XCD,
-// see logical_block()), the tiles of each mesh taken in spread_order(), so
-// that every XCD's share holds its share of the heavy blocks. Finished instances are left out, so their blocks
-// cost nothing; one made to run again (restart) is put back by the next run.
+// The running instances (as of the host's last view of the states) as the
+// next rounds take them; finished ones are left out, so their blocks cost
+// nothing, and one made to run again (restart) is put back by the next run.
 // Mesh and buffer descriptors are uploaded again only after a structural
-// change (mesh or job added or removed).
+// change (mesh or job added or removed). The step kernels' tables follow when
+// a round of theirs is launched.
 template <typename T>
 int rebuild_tables(fem_batch *B) {
-    std::vector<int2> wt, wn;
-    std::vector<int> live;
-    std::vector<int> members[2];
+    B->nwork_tile = 0;
     for (int i = 0; i < B->capacity; i++) {
         InstRec &R = B->insts[i];
         R.in_tables = R.live && host_running(B->h_states[i].phase);
-        if (!R.in_tables) continue;
-        live.push_back(i);
+        if (R.in_tables) B->nwork_tile += B->topos[R.topo].ntile + B->topos[R.topo].ncb;
     }
+    B->work_built = false;
+    B->plan.tried = B->plan.valid = false;
+    if (B->tables_dirty) {
+        std::vector<Topo<T>> tv;
+        for (TopoRec &R : B->topos) tv.push_back(topo_view<T>(R));
+        TRY(sync(B));
+        if (B->d_topos) (void)hipFree(B->d_topos);
+        B->d_topos = nullptr;
+        HIP_TRY(hipMalloc(&B->d_topos, std::max<size_t>(tv.size(), 1) * sizeof(Topo<T>)));
+        if (!tv.empty())
+            HIP_TRY(hipMemcpyAsync(B->d_topos, tv.data(), tv.size() * sizeof(Topo<T>), hipMemcpyHostToDevice, B->stream));
+        std::vector<InstBufs<T>> bv(B->capacity);
+        for (int i = 0; i < B->capacity; i++) bv[i] = inst_view<T>(B->insts[i]);
+        HIP_TRY(hipMemcpyAsync(B->d_bufs, bv.data(), bv.size() * sizeof(InstBufs<T>), hipMemcpyHostToDevice, B->stream));
+        TRY(sync(B));
+        drop_graphs(B);   // they hold the descriptors' addresses
+    }
+    B->tables_dirty = false;
+    return FEM_OK;
+}
+
+// Work tables of the step kernels: tile (+ contact) blocks and node blocks of
+// every instance that rebuild_tables() took, ordered tile-major so
+// one tile of consecutive instances is processed back to back (on one XCD,
+// see logical_block()), the tiles of each mesh taken in spread_order(), so
+// that every XCD's share holds its share of the heavy blocks.
+int build_work(fem_batch *B) {
+    std::vector<int2> wt, wn;
+    std::vector<int> live;
+    std::vector<int> members[2];
+    for (int i = 0; i < B->capacity; i++)
+        if (B->insts[i].in_tables) live.push_back(i);
     // Two groups only on request (on the 256-job fingertip batch they run
     // within the run-to-run spread of one group, the node pass of one group
     // taking wave slots from the other's tile pass): jobs dealt to the group
@@ -637,34 +667,22 @@ int rebuild_tables(fem_batch *B) {
         return FEM_OK;
     };
     drop_graphs(B);
-    B->plan.tried = B->plan.valid = false;
     TRY(upload(wt, B->d_work_tile, B->cap_work_tile, B->nwork_tile));
     TRY(upload(wn, B->d_work_node, B->cap_work_node, B->nwork_node));
     B->nlive = (int)live.size();
     if (!live.empty())
         HIP_TRY(hipMemcpyAsync(B->d_live, live.data(), live.size() * sizeof(int), hipMemcpyHostToDevice, B->stream));
-    if (B->tables_dirty) {
-        std::vector<Topo<T>> tv;
-        for (TopoRec &R : B->topos) tv.push_back(topo_view<T>(R));
-        TRY(sync(B));
-        if (B->d_topos) (void)hipFree(B->d_topos);
-        B->d_topos = nullptr;
-        HIP_TRY(hipMalloc(&B->d_topos, std::max<size_t>(tv.size(), 1) * sizeof(Topo<T>)));
-        if (!tv.empty())
-            HIP_TRY(hipMemcpyAsync(B->d_topos, tv.data(), tv.size() * sizeof(Topo<T>), hipMemcpyHostToDevice, B->stream));
-        std::vector<InstBufs<T>> bv(B->capacity);
-        for (int i = 0; i < B->capacity; i++) bv[i] = inst_view<T>(B->insts[i]);
-        HIP_TRY(hipMemcpyAsync(B->d_bufs, bv.data(), bv.size() * sizeof(InstBufs<T>), hipMemcpyHostToDevice, B->stream));
-        TRY(sync(B));
-    } else {
-        TRY(sync(B));
-    }
-    B->tables_dirty = false;
+    TRY(sync(B));
+    B->work_built = true;
     return FEM_OK;
 }
 
+// Uploaded when they differ from what the device has; the copy is ordered
+// before the kernels that read them, and its source is not written again
+// before the host has waited for it.
 int params_to_device(fem_batch *B, const fem_solve_params &P) {
-    SolveParams &d = *B->h_params;
+    SolveParams d;
+    std::memset(&d, 0, sizeof d);
     d.newton_rtol = P.newton_rtol;
     d.newton_atol = P.newton_atol;
     d.cg_rtol = P.cg_rtol;
@@ -679,8 +697,14 @@ int params_to_device(fem_batch *B, const fem_solve_params &P) {
     d.block_jacobi = P.precond == FEM_PRECOND_BLOCK ? 1 : 0;
     d.contact_full = P.contact_hessian ? 1 : 0;
     d.max_halvings = P.max_halvings;
+    if (B->params_there && std::memcmp(&d, B->h_params, sizeof d) == 0) return FEM_OK;
+    if (B->params_sent == B->syncs) TRY(sync(B));
+    std::memcpy(B->h_params, &d, sizeof d);
+    B->params_there = false;
     HIP_TRY(hipMemcpyAsync(B->d_params, B->h_params, sizeof(SolveParams), hipMemcpyHostToDevice, B->stream));
-    return sync(B);
+    B->params_there = true;
+    B->params_sent = B->syncs;
+    return FEM_OK;
 }
 
 // The states and, behind them, the team kernel's counters.
@@ -694,6 +718,18 @@ int read_states(fem_batch *B) {
 int write_state(fem_batch *B, int slot) {
     HIP_TRY(hipMemcpyAsync(B->d_states + slot, B->h_states + slot, sizeof(InstState), hipMemcpyHostToDevice, B->stream));
     return sync(B);
+}
+
+// Before the host writes a slot's mirror: a kernel that takes the state from
+// it may be pending.
+int settle_state(fem_batch *B, int slot) { return B->insts[slot].sent == B->syncs ? sync(B) : FEM_OK; }
+
+// write_state without a wait of its own, for a call that waits for the stream
+// before it returns.
+int send_state(fem_batch *B, int slot) {
+    B->insts[slot].sent = B->syncs;
+    k_put_state<<<1, 64, 0, B->stream>>>(B->d_states + slot, B->h_states + slot);
+    return launch_check("k_put_state");
 }
 
 // One solver step of one job group on stream st: a tile pass (one launch per
@@ -780,6 +816,7 @@ int kernel_variant(fem_batch *B) {
 // into the graph here); the others replay graphs as without timing.
 template <typename T>
 int launch_round(fem_batch *B, int chunk) {
+    if (!B->work_built) TRY(build_work(B));
     if (pad8(B->nwork_tile) == 0 || pad8(B->nwork_node) == 0 || B->nlive == 0) return FEM_OK;
     const int variant = kernel_variant(B);
     KernelTimer &tm = B->timer;
@@ -926,6 +963,11 @@ int plan_teams(fem_batch *B, int laws) {
         HIP_TRY(hipMalloc(&B->d_team_ctl, ctl));
         B->team_ctl_bytes = ctl;
         HIP_TRY(hipMemsetAsync(B->d_team_ctl, 0, ctl, B->stream));   // the kernel leaves it cleared
+        TeamCtl head{};   // all zero but the mirror
+        head.mirror = B->h_states;
+        head.stat_mirror = (TeamStat *)(B->h_states + B->capacity);
+        HIP_TRY(hipMemcpyAsync(B->d_team_ctl, &head, sizeof head, hipMemcpyHostToDevice, B->stream));
+        TRY(sync(B));
     }
     std::vector<char> image(A.off);
     std::memcpy(image.data() + o_t, teams.data(), teams.size() * sizeof(TeamDesc));
@@ -944,7 +986,8 @@ int plan_teams(fem_batch *B, int laws) {
 }
 
 // One launch of the team kernel: up to `steps` solver steps of every running
-// job; with stop_after > 0 it hands back once so many jobs have ended.
+// job; with stop_after > 0 it hands back once so many jobs have ended. The
+// kernel writes the states and counters to the host's mirror as well.
 template <typename T>
 int launch_teams(fem_batch *B, int steps, int stop_after) {
     const Topo<T> *tp = (const Topo<T> *)B->d_topos;
@@ -967,7 +1010,7 @@ template <typename T>
 int run_impl(fem_batch *B, int max_rounds, int *n_running) {
     int rounds = 0, running = 0;
     bool no_team = false;
-    TRY(read_states(B));
+    // the mirror of the states is current: every launch ends with its update
     for (;;) {
         running = 0;
         int single = -1, dead = 0;
@@ -1009,7 +1052,7 @@ int run_impl(fem_batch *B, int max_rounds, int *n_running) {
                 steps = n * chunk;
             }
             TRY(launch_teams<T>(B, steps, max_rounds > 0 || running <= B->xcds ? 0 : ceil_div(running, 4)));
-            TRY(read_states(B));
+            TRY(sync(B));
             const TeamStat now = *(const TeamStat *)(B->h_states + B->capacity), was = B->stat_seen;
             B->stat_seen = now;
             if (now.stuck != was.stuck) return fail(FEM_E_DEVICE, "a team barrier did not come about");
@@ -1048,7 +1091,8 @@ int run(fem_batch *B, int max_rounds, int *n_running) {
 // ---------------------------------------------------------------------------
 // Node vectors (n x 3) between the caller's numbering and the device's,
 // converted to and from the batch precision on the host in the caller's order.
-int upload_nodes(fem_batch *B, int topo, void *dst, const double *src) {
+// With `also`, a second vector takes the same values, or zeros (also_zero).
+int upload_nodes(fem_batch *B, int topo, void *dst, const double *src, void *also = nullptr, bool also_zero = false) {
     const TopoRec &tp = B->topos[topo];
     const size_t n3 = 3 * (size_t)tp.n;
     TRY(stage(B, std::max<size_t>(n3 * 8, 64)));
@@ -1056,10 +1100,11 @@ int upload_nodes(fem_batch *B, int topo, void *dst, const double *src) {
     if (B->precision == FEM_PREC_FP32) {
         float *h = (float *)B->h_stage;
         for (size_t q = 0; q < n3; q++) h[q] = (float)src[q];
-        k_import_nodes<float><<<blocks, kBlock, 0, B->stream>>>(tp.d_inv, h, (float *)dst, tp.n);
+        k_import_nodes<float><<<blocks, kBlock, 0, B->stream>>>(tp.d_inv, h, (float *)dst, (float *)also, also_zero, tp.n);
     } else {
         std::memcpy(B->h_stage, src, n3 * sizeof(double));
-        k_import_nodes<double><<<blocks, kBlock, 0, B->stream>>>(tp.d_inv, (const double *)B->h_stage, (double *)dst, tp.n);
+        k_import_nodes<double><<<blocks, kBlock, 0, B->stream>>>(tp.d_inv, (const double *)B->h_stage, (double *)dst,
+                                                                 (double *)also, also_zero, tp.n);
     }
     TRY(launch_check("k_import_nodes"));
     return sync(B);
@@ -1629,12 +1674,13 @@ int fem_step(fem_mesh *M, const fem_solve_params *params, fem_step_info *info) {
     fem_batch *B = M->batch;
     TRY(set_device(B));
     TRY(params_to_device(B, P));
+    TRY(settle_state(B, 0));
     const double zero[3] = {0.0, 0.0, 0.0};
     const int hint = B->h_states[0].last_cg;
     init_job_state(B->h_states[0], M->E, M->nu, M->ind, M->ind.c, zero, 0.0, 1, M->dt, M->density, M->model,
                    M->friction);
     B->h_states[0].last_cg = hint;
-    TRY(write_state(B, 0));
+    TRY(send_state(B, 0));
     TRY(run(B, 0, nullptr));
     // the state reached is the next step's friction lag state
     M->friction.lag_ok = 1;
@@ -1662,14 +1708,12 @@ int fem_set_displacements(fem_mesh *M, const double *u, int64_t count) {
     for (int64_t i = 0; i < count; i++)
         if (!is_finite(u[i])) return fail(FEM_E_INVALID, "non-finite displacement");
     TRY(set_device(M->batch));
-    TRY(upload_nodes(M->batch, 0, inst_ptr(M->batch, 0, V_U), u));
     // The predictor follows, so the stored velocity is kept as it is.
-    HIP_TRY(hipMemcpyAsync(inst_ptr(M->batch, 0, V_UT), inst_ptr(M->batch, 0, V_U), 3 * (size_t)M->n * M->batch->elem(),
-                           hipMemcpyDeviceToDevice, M->batch->stream));
+    TRY(upload_nodes(M->batch, 0, inst_ptr(M->batch, 0, V_U), u, inst_ptr(M->batch, 0, V_UT)));
     // u at the current indenter pose becomes the friction lag state
     M->friction.lag_ok = M->have_indenter ? 1 : 0;
     for (int d = 0; d < 3; d++) M->friction.c_lag[d] = M->ind.c[d];
-    return sync(M->batch);
+    return FEM_OK;
 }
 
 int fem_set_friction(fem_mesh *M, double mu_f, double eps) {
@@ -1704,8 +1748,13 @@ int fem_get_velocities(const fem_mesh *Mc, double *v, int64_t capacity) {
     if (capacity < 3LL * Mc->n) return fail(FEM_E_BUFFER, "capacity below 3 n");
     fem_mesh *M = const_cast<fem_mesh *>(Mc);
     TRY(set_device(M->batch));
-    M->batch->h_states[0].dt = M->dt;
-    return download_velocity(M->batch, 0, v);
+    double &dt = M->batch->h_states[0].dt;   // the mirror's, for this call
+    TRY(settle_state(M->batch, 0));
+    const double kept = dt;
+    dt = M->dt;
+    const int rc = download_velocity(M->batch, 0, v);
+    dt = kept;
+    return rc;
 }
 
 int fem_set_velocities(fem_mesh *M, const double *v, int64_t count) {
@@ -1730,9 +1779,9 @@ int fem_get_contact_patch(const fem_mesh *Mc, int32_t *ids, double *f, double *p
     fem_batch *B = M->batch;
     TRY(set_device(B));
     // The patch is evaluated at the handle's current indenter pose.
-    TRY(read_states(B));
+    TRY(settle_state(B, 0));
     B->h_states[0].ind = M->ind;
-    TRY(write_state(B, 0));
+    TRY(send_state(B, 0));
     return contact_patch_impl(B, 0, ids, f, phi, capacity, n_contact, F_total);
 }
 
@@ -1765,13 +1814,14 @@ int fem_eval_gradient(fem_mesh *M, double *g, int64_t capacity, double *energy, 
     fem_solve_params P;
     fem_default_params(&P, B->precision);
     TRY(params_to_device(B, P));
+    TRY(settle_state(B, 0));
     const double zero[3] = {0.0, 0.0, 0.0};
     init_job_state(B->h_states[0], M->E, M->nu, M->ind, M->ind.c, zero, 0.0, 1, M->dt, M->density, M->model,
                    M->friction);
     // with friction, the node pass forms the lag data first
     B->h_states[0].after_lag = PH_EVAL_GRAD;
     B->h_states[0].phase = M->friction.mu_f > 0.0 ? PH_LAG : PH_EVAL_GRAD;
-    TRY(write_state(B, 0));
+    TRY(send_state(B, 0));
     TRY(run(B, 2, nullptr));
     if (energy) *energy = B->h_states[0].E;
     if (min_J) *min_J = B->h_states[0].minJ;
@@ -1793,22 +1843,20 @@ int fem_eval_hessvec(fem_mesh *M, const fem_solve_params *params, const double *
     TRY(check_params(P));
     TRY(set_device(B));
     TRY(params_to_device(B, P));
+    TRY(settle_state(B, 0));
     const double zero[3] = {0.0, 0.0, 0.0};
     init_job_state(B->h_states[0], M->E, M->nu, M->ind, M->ind.c, zero, 0.0, 1, M->dt, M->density, M->model,
                    M->friction);
     // with friction, the node pass forms the lag data first
     B->h_states[0].after_lag = PH_EVAL_GRAD;
     B->h_states[0].phase = M->friction.mu_f > 0.0 ? PH_LAG : PH_EVAL_GRAD;
-    TRY(write_state(B, 0));
+    TRY(send_state(B, 0));
     TRY(run(B, 2, nullptr));
     // q = H v through the CG kernels with z = v, p_prev = 0, beta = 0.
-    std::vector<double> zeros(3 * (size_t)M->n, 0.0);
-    TRY(upload_nodes(B, 0, inst_ptr(B, 0, V_Z), v));
-    TRY(upload_nodes(B, 0, inst_ptr(B, 0, V_P), zeros.data()));
-    TRY(read_states(B));
+    TRY(upload_nodes(B, 0, inst_ptr(B, 0, V_Z), v, inst_ptr(B, 0, V_P), true));
     B->h_states[0].beta = 0.0;
     B->h_states[0].phase = PH_EVAL_HV;
-    TRY(write_state(B, 0));
+    TRY(send_state(B, 0));
     TRY(run(B, 2, nullptr));
     return download_nodes(B, 0, q, inst_ptr(B, 0, V_Q));
 }
@@ -1892,9 +1940,8 @@ int fem_batch_restart_job(fem_batch *B, int32_t job_id, double E, double nu, con
     TRY(check_friction(job->friction, job->friction_eps));
     TRY(set_device(B));
     const int n3 = 3 * B->topos[B->insts[job_id].topo].n;
-    // an earlier restart may not have read its state yet
-    if (B->insts[job_id].restarted == B->syncs) TRY(sync(B));
-    B->insts[job_id].restarted = B->syncs;
+    TRY(settle_state(B, job_id));
+    B->insts[job_id].sent = B->syncs;
     const int hint = B->h_states[job_id].last_cg;
     init_job_state(B->h_states[job_id], E, nu, ind, job->c0, job->direction, job->depth, job->steps, job->dt,
                    job->density, job->model, job_friction(job));
@@ -1992,12 +2039,12 @@ int fem_get_tet_stress(const fem_mesh *M, double *sigma, double *von_mises, int6
     if (!M->have_material) return fail(FEM_E_STATE, "set the material first");
     TRY(set_device(M->batch));
     // the material and law of the handle, as the next step would use them
-    TRY(read_states(M->batch));
+    TRY(settle_state(M->batch, 0));
     InstState &s = M->batch->h_states[0];
     s.mu = M->E / (2.0 * (1.0 + M->nu));
     s.lam = M->E * M->nu / ((1.0 + M->nu) * (1.0 - 2.0 * M->nu));
     s.model = M->model;
-    TRY(write_state(M->batch, 0));
+    TRY(send_state(M->batch, 0));
     return tet_stress_impl(M->batch, 0, sigma, von_mises, capacity);
 }
 
