@@ -1702,7 +1702,7 @@ template <typename T> struct NodeCg {
             qv[1] += H[3] * pv[0] + H[1] * pv[1] + H[5] * pv[2];
             qv[2] += H[4] * pv[0] + H[5] * pv[1] + H[2] * pv[2];
         }
-        if (DYN && i < tp.n_free) {
+        if (DYN && s->mdt2 > 0.0 && i < tp.n_free) {
             const T cm = (T)s->mdt2 * tp.nvol[i];
 #pragma unroll
             for (int d = 0; d < 3; d++) qv[d] = fma_t(cm, pv[d], qv[d]);
@@ -2379,9 +2379,17 @@ __device__ __forceinline__ void team_hessvec(const TopoD<T> &tp, const BufsD<T> 
 }
 
 // CG update of one team member: node blocks rank, rank + W, ... with p.q
-// formed once and the sums of r.z and r.r taken over all of them.
-template <typename T, bool DYN, int COH>
-__device__ __forceinline__ void team_update(const TopoD<T> &tp, const BufsD<T> &B, const InstState *s, int rank, int W) {
+// formed once and the sums of r.z and r.r taken over all of them. c: the first
+// block, requested before the barrier: its r, dx, p and M^-1 are this thread's
+// own, the lists the mesh's. A small team's step is a chain of latencies, and
+// this takes one out: load steps of the 3072-tet block 14.5 -> 13.7 ms (FP64),
+// 5k tets 1.56 -> 1.48 ms (FP32), 50k 12.0 -> 11.4 ms (FP64); members of batches
+// with several blocks each neither gain nor lose. The same for the tile pass's
+// first records would hold them over the finalize: 161 registers for 106 and
+// 5 to 13 % on FP32 batches.
+template <typename T, int COH>
+__device__ __forceinline__ void team_update(const TopoD<T> &tp, const BufsD<T> &B, const InstState *s, int rank, int W,
+                                            NodeCg<T> &c) {
     const double rz = uni<COH>(s->rz);
     const T beta = uni<COH>((T)s->beta);
     const int cg_first = uni<COH>((int)(s->cg_it == 0));
@@ -2389,8 +2397,6 @@ __device__ __forceinline__ void team_update(const TopoD<T> &tp, const BufsD<T> &
     if (rank >= nb) return;
     double acc[2] = {0.0, 0.0};
     const double *const part[1] = {B.red + RS_PQ * B.red_stride};
-    NodeCg<T> c;
-    c.template request<COH, false>(tp, B, rank * kBlock + (int)threadIdx.x);
     double sum[1];
     wave_sums_partials<COH, 1>(part, min(W, tp.ntile + tp.ncb), sum);
     const double pq = uni<COH>(sum[0]);
@@ -2402,7 +2408,7 @@ __device__ __forceinline__ void team_update(const TopoD<T> &tp, const BufsD<T> &
         c.template gather<COH>(tp, B);
         NodeCg<T> n;
         n.template request<COH, false>(tp, B, (more ? blk + W : blk) * kBlock + (int)threadIdx.x);
-        c.template form<DYN, COH, false>(tp, B, s, beta, cg_first);
+        c.template form<true, COH, false>(tp, B, s, beta, cg_first);
         c.template apply<COH>(tp, B, alpha, negcurv, cg_first, acc);
         if (!more) break;
         blk += W;
@@ -2422,8 +2428,10 @@ __device__ __forceinline__ bool running_phase(int ph) { return ph != PH_IDLE && 
 
 // LAWS: constitutive laws among the jobs (1 Neo-Hookean, 2 co-rotational, 3
 // both). COH: kXcd, or kChip with teams over `span` XCDs each.
+// At least 4 (FP32) and 2 (FP64) wavefronts per SIMD, as many as it needs
+// registers for; teams are as large as fit at once.
 template <typename T, int LAWS, int COH>
-__global__ __launch_bounds__(kBlock) void k_team(const Topo<T> *topos, const InstBufs<T> *bufs, const int2 *jobs,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) void k_team(const Topo<T> *topos, const InstBufs<T> *bufs, const int2 *jobs,
                                                  const TeamDesc *teams, const XcdDesc *xcds, TeamCtl *ctl,
                                                  TeamStat *stat, const SolveParams *P, int span, int steps,
                                                  unsigned steps_base, int stop_early, unsigned stop_at) {
@@ -2490,16 +2498,18 @@ __global__ __launch_bounds__(kBlock) void k_team(const Topo<T> *topos, const Ins
                     }
                 }
                 team_arrive(ts, ++ph, W, rank, ask);
-                r = team_wait(ts, ph, sh, stat);
-                if (r < 0) break;
-                stop = r > 0;
                 if (phase == PH_CG) {
                     const JobView<T> V(topos, bufs, job);
-                    if (S.mdt2 > 0.0)
-                        team_update<T, true, COH>(V.tp, V.B, &S, rank, W);
-                    else
-                        team_update<T, false, COH>(V.tp, V.B, &S, rank, W);
+                    NodeCg<T> first;
+                    first.template request<COH, false>(V.tp, V.B, rank * kBlock + (int)threadIdx.x);
+                    r = team_wait(ts, ph, sh, stat);
+                    if (r < 0) break;
+                    stop = r > 0;
+                    team_update<T, COH>(V.tp, V.B, &S, rank, W, first);
                 } else {
+                    r = team_wait(ts, ph, sh, stat);
+                    if (r < 0) break;
+                    stop = r > 0;
                     for (int i = rank; i < nnb; i += W)
                         node_block<T, true, COH>([&] { return JobView<T>(topos, bufs, job); }, &S, i, min(W, blocks),
                                                  P->block_jacobi);
