@@ -112,6 +112,7 @@ struct TeamPlan {
     bool valid = false;       // and the team kernel takes these jobs
     int blocks = 0, laws = 0;
     int span = 1;             // XCDs of a team
+    int wider = 0;   // with at most so many jobs running, teams could span more XCDs than these
 };
 
 // Events for the cross-stream order of one captured or launched round.
@@ -980,6 +981,7 @@ int plan_teams(fem_batch *B, int laws) {
     B->t_xcds = (const XcdDesc *)(base + o_x);
     B->t_jobs = (const int2 *)(base + o_lv);
     plan.span = span;
+    plan.wider = items(jobs[0]) > kTeamSpanItems ? B->xcds / (2 * span) : 0;
     plan.blocks = ceil_div(need, span) * B->xcds;
     plan.valid = true;
     return FEM_OK;
@@ -1039,19 +1041,27 @@ int run_impl(fem_batch *B, int max_rounds, int *n_running) {
         bool team = !no_team && team_usable(B) && !(timing && B->timer.rounds % B->timer.every == 0);
         if (team) {
             const int laws = kernel_variant(B) & 3;
-            if (!B->plan.tried || B->plan.laws != laws) TRY(plan_teams<T>(B, laws));
+            if (!B->plan.tried || B->plan.laws != laws || running <= B->plan.wider) TRY(plan_teams<T>(B, laws));
             team = B->plan.valid;
         }
         if (team) {
-            // as many rounds in one launch as may run without the host; to the
-            // end, only a quarter of the jobs being done ends a launch early,
-            // so that the others can spread out
+            // As many rounds in one launch as may run without the host. To the
+            // end, a launch ends early only for the others to spread out:
+            // once a quarter of the jobs are done, or, with no more jobs than
+            // XCDs, once the rest's teams may span twice as many of them
+            // (the last 7 of 48 jobs on three fingertips, the 50k one's teams
+            // over 2, 4 and 8 XCDs: 2.7 -> 1.9 ms of 12).
+            int stop_after = 0;
+            if (max_rounds == 0 && running > B->xcds)
+                stop_after = ceil_div(running, 4);
+            else if (max_rounds == 0 && B->plan.wider > 0)
+                stop_after = running - B->plan.wider;
             int n = 1, steps = timing ? chunk : kTeamSteps;
             if (max_rounds > 0) {
                 n = timing ? 1 : std::max(1, std::min(max_rounds - rounds, kTeamSteps / chunk));
                 steps = n * chunk;
             }
-            TRY(launch_teams<T>(B, steps, max_rounds > 0 || running <= B->xcds ? 0 : ceil_div(running, 4)));
+            TRY(launch_teams<T>(B, steps, stop_after));
             TRY(sync(B));
             const TeamStat now = *(const TeamStat *)(B->h_states + B->capacity), was = B->stat_seen;
             B->stat_seen = now;

@@ -106,6 +106,16 @@ def test_mixed_laws_friction_and_time_steps(precision):
 
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_large_jobs_that_end_apart(precision):
+    """Six jobs on 50k tets of 1, 1, 2, 3, 4 and 6 load steps: the teams of
+    those still running go from one XCD over two and four to eight."""
+    print("case", precision, flush=True)
+    mesh = W.fingertip_mesh(50000)
+    jobs = [[jobs_on(mesh, 1, k)[0] for k in (1, 1, 2, 3, 4, 6)]]
+    compare(solve([mesh], jobs, precision, 1), solve([mesh], jobs, precision, 0), precision)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
 def test_meshes_smaller_than_the_team_they_share(precision):
     """Jobs of one cell, 5k and 20k tets on every XCD: the larger meshes set
     the team's size, so most members have no tile of the small ones, whose
