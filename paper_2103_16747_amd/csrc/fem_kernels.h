@@ -19,14 +19,15 @@
 // sees no atomics in the solve kernels.
 //
 // Control: each instance runs a Newton / PCG / line-search state machine on
-// the device. Work kernels write one FP64 partial per block and per reduced
-// quantity; a finalize kernel (one wavefront per instance) sums them in a
-// fixed order and takes the transition, so no kernel needs cross-block
-// synchronisation (an agent-scope fence per block costs an L2 write-back on
-// this part). A solver step is a tile pass, a node pass and a finalize over
-// every running instance; each instance advances by one phase per step
-// (a CG iteration, a line-search trial, a Newton init), whatever phase the
-// others are in.
+// the device. The passes write one FP64 partial per block and per reduced
+// quantity; a finalize (one wavefront per instance) sums them in a fixed order
+// and takes the transition. A solver step is a tile pass, a node pass and a
+// finalize; each instance advances by one phase per step (a CG iteration, a
+// line-search trial, a Newton init), whatever phase the others are in. The
+// team kernel (k_team) runs all steps of all jobs in one launch, teams of
+// workgroups meeting at barriers in the L2; the step kernels (k_tile, k_node,
+// k_finalize) run one pass of every job per launch and need no cross-block
+// synchronisation.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -1353,11 +1354,11 @@ __device__ __forceinline__ double contact_hessvec(const TopoD<T> &tp, const Bufs
 // p.q is accumulated element by element (and over contact blocks), so alpha
 // is known to the node pass without a pass over q.
 // ---------------------------------------------------------------------------
-template <typename T, int LAW, bool DET, int COH = kAlone>
+template <typename T, int LAW, bool DET>
 __device__ __forceinline__ void tile_hessvec(const TopoD<T> &tp, const BufsD<T> &B, const InstState *s, int blk,
                                              double *pool) {
-    const T beta = uni<COH>((T)s->beta);
-    const T mu = uni<COH>((T)s->mu), lam = uni<COH>((T)s->lam);
+    const T beta = uni<kAlone>((T)s->beta);
+    const T mu = uni<kAlone>((T)s->mu), lam = uni<kAlone>((T)s->lam);
     double acc[1] = {0.0};
     double unused = 0.0;
     if (blk < tp.ntile) {
@@ -1370,7 +1371,7 @@ __device__ __forceinline__ void tile_hessvec(const TopoD<T> &tp, const BufsD<T> 
         const int k0 = tp.tile_tet[t], nk = tp.tile_tet[t + 1] - k0;
         // Implicit steps add (m_i / dt^2) |p_i|^2 to p.q, taken once per node
         // (on its first entry).
-        const double cm = uni<COH>(s->mdt2);
+        const double cm = uni<kAlone>(s->mdt2);
         double pq = 0.0;
         // This thread's first tet record is fetched before the staging
         // barrier, so its latency overlaps the staging loads.
@@ -1381,9 +1382,9 @@ __device__ __forceinline__ void tile_hessvec(const TopoD<T> &tp, const BufsD<T> 
         if ((int)threadIdx.x < ne) {
             const int gid = tp.ent_node[e0 + threadIdx.x];
             T pv[3], uv[3], pp[3], zv[3];
-            ld_vec<COH>(B.u, tp.n, gid, uv);
-            ld_vec<COH>(B.p, tp.n, gid, pp);
-            ld_vec<COH>(B.z, tp.n, gid, zv);
+            ld_vec<kAlone>(B.u, tp.n, gid, uv);
+            ld_vec<kAlone>(B.p, tp.n, gid, pp);
+            ld_vec<kAlone>(B.z, tp.n, gid, zv);
 #pragma unroll
             for (int d = 0; d < 3; d++) {
                 su[kSw * sl + d] = uv[d];
@@ -1422,7 +1423,7 @@ __device__ __forceinline__ void tile_hessvec(const TopoD<T> &tp, const BufsD<T> 
                 T out[3];
 #pragma unroll
                 for (int d = 0; d < 3; d++) out[d] = (T)sa[3 * sl + d];
-                st_vec<COH>(B.pq, tp.nent, e0 + (int)threadIdx.x, out);
+                st_vec<kAlone>(B.pq, tp.nent, e0 + (int)threadIdx.x, out);
             }
         } else {
             // Deterministic: each chunk of kBlock tets stores its nodal
@@ -1456,11 +1457,11 @@ __device__ __forceinline__ void tile_hessvec(const TopoD<T> &tp, const BufsD<T> 
                 for (int d = 0; d < 3; d++) B.pq[3 * (e0 + threadIdx.x) + d] = (T)qa[d];
         }
     } else {
-        acc[0] = contact_hessvec<T, COH>(tp, B, (blk - tp.ntile) * kBlock + (int)threadIdx.x, beta);
+        acc[0] = contact_hessvec<T, kAlone>(tp, B, (blk - tp.ntile) * kBlock + (int)threadIdx.x, beta);
     }
     block_reduce<1, false>(acc, unused);
     const int streams[1] = {RS_PQ};
-    store_partials<COH>(B.red, B.red_stride, streams, blk, acc);
+    store_partials<kAlone>(B.red, B.red_stride, streams, blk, acc);
 }
 
 // ---------------------------------------------------------------------------
