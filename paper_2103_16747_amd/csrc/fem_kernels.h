@@ -2583,8 +2583,8 @@ __global__ void k_xcds(unsigned *out) {
 // gradient, phi; and its count and FP64 resultant into its head. With lists =
 // false only the heads. The signed distance takes some hundred FP64
 // instructions a node, so the nodes are spread over as many CUs as there are
-// blocks: 47 us for a count and resultant of 3757 nodes when one block walked
-// them and two copies followed.
+// blocks. A call for the count and resultant of 3757 nodes took 47 us when one
+// block walked them and two copies followed; it takes 17 us, 4 of them the kernel.
 // ---------------------------------------------------------------------------
 struct PatchHead {
     double F[3];
