@@ -134,6 +134,7 @@ struct TopoRec {
 struct InstRec {
     bool live = false;
     bool in_tables = false;   // has blocks in the current work tables
+    bool planned = false;     // and a team in the current plan
     long long sent = -1;      // fem_batch::syncs when a kernel that reads the mirror's state was enqueued
     int topo = -1;
     void *arena = nullptr;
@@ -905,8 +906,11 @@ int plan_teams(fem_batch *B, int laws) {
         return out;
     };
     std::vector<int> jobs;
-    for (int i = 0; i < B->capacity; i++)
-        if (B->insts[i].in_tables && host_running(B->h_states[i].phase)) jobs.push_back(i);
+    for (int i = 0; i < B->capacity; i++) {
+        InstRec &R = B->insts[i];
+        R.planned = R.in_tables && host_running(B->h_states[i].phase);
+        if (R.planned) jobs.push_back(i);
+    }
     // the team kernel's buffer accesses have 32-bit byte offsets
     if (jobs.empty()) return FEM_OK;
     for (int i : jobs)
@@ -1016,7 +1020,7 @@ int run_impl(fem_batch *B, int max_rounds, int *n_running) {
     for (;;) {
         running = 0;
         int single = -1, dead = 0;
-        bool missing = false;
+        bool missing = false, unplanned = false;
         for (int i = 0; i < B->capacity; i++) {
             const InstRec &R = B->insts[i];
             if (!R.live) continue;
@@ -1024,6 +1028,7 @@ int run_impl(fem_batch *B, int max_rounds, int *n_running) {
                 running++;
                 single = i;
                 missing = missing || !R.in_tables;
+                unplanned = unplanned || !R.planned;
             } else if (R.in_tables) {
                 dead += B->topos[R.topo].ntile + B->topos[R.topo].ncb;
             }
@@ -1041,7 +1046,10 @@ int run_impl(fem_batch *B, int max_rounds, int *n_running) {
         bool team = !no_team && team_usable(B) && !(timing && B->timer.rounds % B->timer.every == 0);
         if (team) {
             const int laws = kernel_variant(B) & 3;
-            if (!B->plan.tried || B->plan.laws != laws || running <= B->plan.wider) TRY(plan_teams<T>(B, laws));
+            // A plan holds the jobs that ran when it was made: one restarted
+            // since then needs a new one.
+            if (!B->plan.tried || B->plan.laws != laws || unplanned || running <= B->plan.wider)
+                TRY(plan_teams<T>(B, laws));
             team = B->plan.valid;
         }
         if (team) {
