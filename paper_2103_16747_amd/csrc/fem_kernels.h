@@ -2117,7 +2117,9 @@ struct TeamSync {
     TeamLine group[kTeamGroups];    // arrivals of members
 };
 constexpr int kMaxXcds = 16;
-// Counters that only grow; the host takes differences between launches.
+// done, calledoff and stuck only grow, and the host takes differences between
+// launches, which hold when they wrap; steps, a maximum over the teams, is the
+// launch's own: the last workgroup to leave clears it.
 struct TeamStat {
     unsigned done, calledoff, stuck, steps;
 };
@@ -2435,7 +2437,7 @@ template <typename T, int LAWS, int COH>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) void k_team(const Topo<T> *topos, const InstBufs<T> *bufs, const int2 *jobs,
                                                  const TeamDesc *teams, const XcdDesc *xcds, TeamCtl *ctl,
                                                  TeamStat *stat, const SolveParams *P, int span, int steps,
-                                                 unsigned steps_base, int stop_early, unsigned stop_at) {
+                                                 int stop_early, unsigned stop_at) {
     using Lds = TileLds<T, false>;
     __shared__ __attribute__((aligned(32))) double pool[Lds::kDoubles > Lds::kTeamHv ? Lds::kDoubles : Lds::kTeamHv];
     __shared__ InstState S;
@@ -2543,7 +2545,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
             }
         }
         if (rank == 0 && threadIdx.x == 0)
-            __hip_atomic_fetch_max(&stat->steps, steps_base + (unsigned)most, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_fetch_max(&stat->steps, (unsigned)most, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     // the last workgroup to leave hands the launch's counters to the host
     // (this thread's own additions to them have arrived before it leaves) and
@@ -2555,6 +2557,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
         stat_mirror->calledoff = ag_load(&stat->calledoff);
         stat_mirror->stuck = ag_load(&stat->stuck);
         stat_mirror->steps = ag_load(&stat->steps);
+        ag_store(&stat->steps, 0u);
         for (int x = 0; x < kMaxXcds; x++) {
             const XcdDesc Y = ld_table<XcdDesc>(xcds, x);
             for (int t = Y.team0; t < Y.team0 + Y.nteam; t++) {

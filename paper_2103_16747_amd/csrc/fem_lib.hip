@@ -162,6 +162,7 @@ struct fem_batch {
     InstState *d_states = nullptr;  // capacity states, then the team kernel's TeamStat
     InstState *h_states = nullptr;  // pinned mirror
     TeamStat stat_seen{};           // counters as of the last launch
+    long long team_launches = 0, step_rounds = 0;   // launches of the team kernel, rounds of the step kernels
     int xcds = 0, cus = 0;          // of the device; xcds = 0: no team kernel
     TeamPlan plan;
     void *d_team = nullptr;         // team, XCD and job tables of the plan
@@ -1002,10 +1003,11 @@ int launch_teams(fem_batch *B, int steps, int stop_after) {
     const SolveParams *P = (const SolveParams *)B->d_params;
     const dim3 grid(B->plan.blocks), block(kBlock);
     const int early = stop_after > 0 ? 1 : 0;
-    const unsigned at = B->stat_seen.done + (unsigned)stop_after, s0 = B->stat_seen.steps;
+    const unsigned at = B->stat_seen.done + (unsigned)stop_after;
+    B->team_launches++;
     with_team_kernel<T>(B->plan.laws, B->plan.span, [&](auto kernel) {
         kernel<<<grid, block, 0, B->stream>>>(tp, bf, B->t_jobs, B->t_teams, B->t_xcds, B->d_team_ctl, stat, P,
-                                              B->plan.span, steps, s0, early, at);
+                                              B->plan.span, steps, early, at);
         return 0;
     });
     return launch_check("k_team");
@@ -1076,11 +1078,11 @@ int run_impl(fem_batch *B, int max_rounds, int *n_running) {
             if (now.stuck != was.stuck) return fail(FEM_E_DEVICE, "a team barrier did not come about");
             if (timing) {
                 B->timer.rounds++;
-                for (int k = 0; k < KernelTimer::kKinds; k++) B->timer.seen[k] += (long long)(now.steps - was.steps);
+                for (int k = 0; k < KernelTimer::kKinds; k++) B->timer.seen[k] += now.steps;
             }
             // a team that did not meet, or none that moved: the step kernels
             // take over until the next run
-            no_team = now.calledoff != was.calledoff || now.steps == was.steps;
+            no_team = now.calledoff != was.calledoff || now.steps == 0;
             if (!no_team) {
                 rounds += n;
                 continue;
@@ -1093,6 +1095,7 @@ int run_impl(fem_batch *B, int max_rounds, int *n_running) {
         }
         TRY(launch_round<T>(B, chunk));
         TRY(read_states(B));
+        B->step_rounds++;
         rounds++;
     }
     if (n_running) *n_running = running;
@@ -2238,6 +2241,29 @@ int fem_batch_mesh_info(const fem_batch *B, int32_t mesh_id, fem_mesh_layout *in
     info->n_tiles = tp.ntile;
     info->n_entries = tp.nent;
     info->n_eligible = tp.nc;
+    return FEM_OK;
+}
+
+// ---------------------------------------------------------------------------
+// Not part of include/fem.h: how the library's tests see which kernels took a
+// run, and put a batch where hours of solving would.
+// ---------------------------------------------------------------------------
+// Launches of the team kernel and rounds of the step kernels so far.
+int fem_debug_team_launches(const fem_batch *B, int64_t *teams, int64_t *step_rounds) {
+    if (!B || !teams || !step_rounds) return fail(FEM_E_INVALID, "null argument");
+    *teams = B->team_launches;
+    *step_rounds = B->step_rounds;
+    return FEM_OK;
+}
+
+// The team kernel's growing counters, as after that many events each.
+int fem_debug_team_counters(fem_batch *B, uint32_t value) {
+    if (!B) return fail(FEM_E_INVALID, "null argument");
+    TRY(set_device(B));
+    const TeamStat stat{value, value, value, 0u};
+    HIP_TRY(hipMemcpyAsync(B->d_states + B->capacity, &stat, sizeof stat, hipMemcpyHostToDevice, B->stream));
+    TRY(sync(B));
+    B->stat_seen = stat;
     return FEM_OK;
 }
 

@@ -1,0 +1,72 @@
+"""Which kernels take a run, and the counters that decide it (runs on an MI355X).
+
+Results are held to the step kernels' as in the team kernel's own tests: 1e-9
+of the largest displacement in FP64.
+"""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+from paper_2103_16747_amd import fem, workload as W
+
+pytestmark = pytest.mark.gpu
+
+
+def block_jobs(count, steps):
+    mesh = W.cube_block_mesh()
+    return mesh, [W.Indentation(W.SPHERE, np.array([3e-3]), np.eye(3), np.array([5e-3, 5e-3, 13e-3]),
+                                np.array([0.0, 0.0, -1.0]), 4e-5 * steps * (1 + i % 3), steps) for i in range(count)]
+
+
+class Batch:
+    def __init__(self, mesh, inds, graphs=1):
+        self.b = fem.FemBatch(len(inds), "fp64")
+        self.b.set_graphs(graphs)
+        self.P = self.b.default_params(newton_rtol=1e-10, cg_rtol=1e-10)
+        mid = self.b.add_mesh(mesh.X, mesh.tets, mesh.fixed)
+        self.inds, self.ids = inds, [self.b.add_job(mid, ind) for ind in inds]
+
+    def restart(self):
+        for j, ind in zip(self.ids, self.inds):
+            self.b.restart_job(j, ind)
+
+    def launches(self):
+        t, s = C.c_int64(), C.c_int64()
+        assert fem.load().fem_debug_team_launches(self.b.h, C.byref(t), C.byref(s)) == 0
+        return t.value, s.value
+
+    def displacements(self):
+        return [self.b.displacements(j) for j in self.ids]
+
+
+def reference(mesh, inds):
+    r = Batch(mesh, inds, graphs=0)
+    assert r.b.run(r.P) == 0
+    u = r.displacements()
+    r.b.close()
+    return u
+
+
+def close_to(us, refs):
+    for u, ref in zip(us, refs):
+        assert np.abs(u - ref).max() <= 1e-9 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("jobs", [1, 12])
+def test_counters_that_wrap(jobs):
+    """Counters just below 2^32 wrap in the first run; it and the next are
+    taken by the team kernel alone and give what the step kernels give."""
+    mesh, inds = block_jobs(jobs, 2)
+    ref = reference(mesh, inds)
+    t = Batch(mesh, inds)
+    assert fem.load().fem_debug_team_counters(t.b.h, C.c_uint32(2**32 - 1 - jobs // 2)) == 0
+    for k in range(3):
+        print("case", jobs, k, flush=True)
+        before = t.launches()
+        assert t.b.run(t.P) == 0
+        close_to(t.displacements(), ref)
+        after = t.launches()
+        assert after[0] > before[0] and after[1] == before[1]
+        t.restart()
+    t.b.close()
