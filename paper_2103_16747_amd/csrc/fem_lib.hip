@@ -812,6 +812,12 @@ int kernel_variant(fem_batch *B) {
            (B->deterministic ? 8 : 0);
 }
 
+// Solver steps of a captured round: multiples of 4 up to 32, of 8 up to 64.
+int graph_steps(int chunk) {
+    const int c = std::max(4, std::min(64, chunk));
+    return c <= 32 ? (c + 3) / 4 * 4 : (c + 7) / 8 * 8;
+}
+
 // Launches a round, replaying a captured graph for its length when graphs are
 // on (lengths rounded up to a multiple of 4, of 8 above 32; at most 64 solver
 // steps). With kernel timing on, every `every`-th round is launched kernel by
@@ -832,9 +838,7 @@ int launch_round(fem_batch *B, int chunk) {
             for (int k = 0; k < KernelTimer::kKinds; k++) tm.seen[k] += (long long)c * B->ngroups;
         return FEM_OK;
     }
-    // graph lengths: multiples of 4 up to 32, of 8 up to 64
-    int c = std::max(4, std::min(64, chunk));
-    c = c <= 32 ? (c + 3) / 4 * 4 : (c + 7) / 8 * 8;
+    const int c = graph_steps(chunk);
     int gi = -1;
     for (int i = 0; i < (int)B->graphs.size(); i++)
         if (B->graphs[i].chunk == c && B->graphs[i].variant == variant && B->graphs[i].groups == B->ngroups) gi = i;
@@ -1043,6 +1047,13 @@ int run_impl(fem_batch *B, int max_rounds, int *n_running) {
         // its current Newton iteration is expected to need (CG iterations of
         // the previous solve, plus the line-search trial and the init).
         int chunk = B->chunk > 0 ? B->chunk : 16;
+        const bool fixed_length = B->chunk > 0 || running > 1;
+        if (!fixed_length) {
+            const InstState &s = B->h_states[single];
+            const int expect = s.last_cg > 0 ? s.last_cg : 16;
+            chunk = s.phase == PH_CG ? expect - s.cg_it + 2 : expect + 3;
+            if (B->use_graphs) chunk = graph_steps(chunk);
+        }
         // rounds that record kernel times run the step kernels
         const bool timing = B->timer.every > 0;
         bool team = !no_team && team_usable(B) && !(timing && B->timer.rounds % B->timer.every == 0);
@@ -1068,7 +1079,8 @@ int run_impl(fem_batch *B, int max_rounds, int *n_running) {
                 stop_after = running - B->plan.wider;
             int n = 1, steps = timing ? chunk : kTeamSteps;
             if (max_rounds > 0) {
-                n = timing ? 1 : std::max(1, std::min(max_rounds - rounds, kTeamSteps / chunk));
+                // several rounds at once where one's end does not set the next's length
+                n = timing || !fixed_length ? 1 : std::max(1, std::min(max_rounds - rounds, kTeamSteps / chunk));
                 steps = n * chunk;
             }
             TRY(launch_teams<T>(B, steps, stop_after));
@@ -1087,11 +1099,6 @@ int run_impl(fem_batch *B, int max_rounds, int *n_running) {
                 rounds += n;
                 continue;
             }
-        }
-        if (running == 1 && B->chunk <= 0) {
-            const InstState &s = B->h_states[single];
-            const int expect = s.last_cg > 0 ? s.last_cg : 16;
-            chunk = s.phase == PH_CG ? expect - s.cg_it + 2 : expect + 3;
         }
         TRY(launch_round<T>(B, chunk));
         TRY(read_states(B));

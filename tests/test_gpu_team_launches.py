@@ -70,3 +70,27 @@ def test_counters_that_wrap(jobs):
         assert after[0] > before[0] and after[1] == before[1]
         t.restart()
     t.b.close()
+
+
+def test_round_of_a_single_job():
+    """One job's round has the expected length of its Newton iteration: 16 CG
+    iterations before the first solve, then those of the solve before, and
+    three steps more at the start of an iteration, rounded up to the lengths of
+    captured rounds, 4 to 64 solver steps. At the FP64 tolerance solves take
+    more than 40 iterations on this mesh, so such rounds are among them. A round
+    that ends between a trial and its init is counted one off."""
+    mesh, inds = block_jobs(1, 3)
+    t = Batch(mesh, inds)
+
+    def steps():   # CG iterations, gradients and trials, and the inits behind accepted trials
+        info = t.b.job_info(t.ids[0])
+        return info["hv_products"] + info["grad_passes"] + info["newton_iters"]
+
+    took, last = [], 0
+    while t.b.run(t.P, max_rounds=1):
+        took.append(steps() - last)
+        last = steps()
+    print("rounds", took, flush=True)
+    assert abs(took[0] - 20) <= 1
+    assert min(took) >= 3 and 40 <= max(took) <= 65
+    t.b.close()
