@@ -93,7 +93,8 @@ struct InstState {
     double mdt2;                              // rho / dt^2 (0: quasi-static)
     double gbest;                             // smallest |g_free| of the load step so far
     int stall, steps_floor;                   // accepted iterations without halving gbest
-    int model, pad3;                          // constitutive law (LAW_NH, LAW_CR)
+    int model;                                // constitutive law (LAW_NH, LAW_CR)
+    unsigned launch;                          // the last launch of the team kernel that took the job (0: none)
     double mu_f, eps_f;                       // Coulomb friction coefficient (0: none), slip smoothing length
     double c_lag[3];                          // indenter centre of the friction lag state
     int lag_ok, after_lag;                    // 1: a lag state exists (u at the step start, c_lag);
@@ -2437,7 +2438,7 @@ template <typename T, int LAWS, int COH>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) void k_team(const Topo<T> *topos, const InstBufs<T> *bufs, const int2 *jobs,
                                                  const TeamDesc *teams, const XcdDesc *xcds, TeamCtl *ctl,
                                                  TeamStat *stat, const SolveParams *P, int span, int steps,
-                                                 int stop_early, unsigned stop_at) {
+                                                 int stop_early, unsigned stop_at, unsigned launch) {
     using Lds = TileLds<T, false>;
     __shared__ __attribute__((aligned(32))) double pool[Lds::kDoubles > Lds::kTeamHv ? Lds::kDoubles : Lds::kTeamHv];
     __shared__ InstState S;
@@ -2537,7 +2538,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
             }
             most = max(most, c);
             if (rank == 0 && r >= 0) {
-                if (threadIdx.x == 0 && c > 0 && !running_phase(phase)) ag_add(&stat->done, 1u);
+                if (threadIdx.x == 0) {
+                    if (c > 0 && !running_phase(phase)) ag_add(&stat->done, 1u);
+                    S.launch = launch;
+                }
+                __syncthreads();
                 const JobView<T> V(topos, bufs, job);
                 unsigned long long *gs = (unsigned long long *)(InstState *)V.B.s;
                 unsigned long long *hs = (unsigned long long *)(ctl->mirror + job);

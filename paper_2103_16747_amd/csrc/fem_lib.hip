@@ -165,6 +165,7 @@ struct fem_batch {
     long long team_launches = 0, step_rounds = 0;   // launches of the team kernel, rounds of the step kernels
     int xcds = 0, cus = 0;          // of the device; xcds = 0: no team kernel
     TeamPlan plan;
+    int absent = 0;                 // workgroups left out of each launch of teams (for tests)
     void *d_team = nullptr;         // team, XCD and job tables of the plan
     size_t team_bytes = 0, team_ctl_bytes = 0;
     TeamCtl *d_team_ctl = nullptr;
@@ -1005,16 +1006,32 @@ int launch_teams(fem_batch *B, int steps, int stop_after) {
     const InstBufs<T> *bf = (const InstBufs<T> *)B->d_bufs;
     TeamStat *stat = (TeamStat *)(B->d_states + B->capacity);
     const SolveParams *P = (const SolveParams *)B->d_params;
-    const dim3 grid(B->plan.blocks), block(kBlock);
+    const dim3 grid(std::max(1, B->plan.blocks - B->absent)), block(kBlock);
     const int early = stop_after > 0 ? 1 : 0;
     const unsigned at = B->stat_seen.done + (unsigned)stop_after;
     B->team_launches++;
     with_team_kernel<T>(B->plan.laws, B->plan.span, [&](auto kernel) {
         kernel<<<grid, block, 0, B->stream>>>(tp, bf, B->t_jobs, B->t_teams, B->t_xcds, B->d_team_ctl, stat, P,
-                                              B->plan.span, steps, early, at);
+                                              B->plan.span, steps, early, at,
+                                              (unsigned)B->team_launches);
         return 0;
     });
     return launch_check("k_team");
+}
+
+// Rounds of the step kernels for the running jobs that the last launch of
+// teams did not take, so that they are as far as the others.
+template <typename T>
+int catch_up(fem_batch *B, int rounds, int chunk) {
+    for (int i = 0; i < B->capacity; i++)
+        if (B->h_states[i].launch == (unsigned)B->team_launches) B->insts[i].in_tables = false;
+    B->work_built = false;
+    for (int k = 0; k < rounds; k++) {
+        TRY(launch_round<T>(B, chunk));
+        TRY(read_states(B));
+        B->step_rounds++;
+    }
+    return rebuild_tables<T>(B);
 }
 
 // Advances every running job until all are done or max_rounds rounds ran.
@@ -1092,10 +1109,17 @@ int run_impl(fem_batch *B, int max_rounds, int *n_running) {
                 B->timer.rounds++;
                 for (int k = 0; k < KernelTimer::kKinds; k++) B->timer.seen[k] += now.steps;
             }
-            // a team that did not meet, or none that moved: the step kernels
-            // take over until the next run
+            // A team that did not meet, or none that moved: the step kernels
+            // take over until the next run. In a run of so many rounds they
+            // take the jobs left behind through those that the other teams have
+            // taken.
             no_team = now.calledoff != was.calledoff || now.steps == 0;
             if (!no_team) {
+                rounds += n;
+                continue;
+            }
+            if (now.steps > 0) {
+                if (max_rounds > 0) TRY(catch_up<T>(B, n, chunk));
                 rounds += n;
                 continue;
             }
@@ -2271,6 +2295,14 @@ int fem_debug_team_counters(fem_batch *B, uint32_t value) {
     HIP_TRY(hipMemcpyAsync(B->d_states + B->capacity, &stat, sizeof stat, hipMemcpyHostToDevice, B->stream));
     TRY(sync(B));
     B->stat_seen = stat;
+    return FEM_OK;
+}
+
+// Workgroups that the next launches of the team kernel leave out, so that
+// teams don't meet (0: none).
+int fem_debug_team_absent(fem_batch *B, int32_t workgroups) {
+    if (!B || workgroups < 0) return fail(FEM_E_INVALID, "bad argument");
+    B->absent = workgroups;
     return FEM_OK;
 }
 

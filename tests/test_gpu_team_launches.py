@@ -94,3 +94,33 @@ def test_round_of_a_single_job():
     assert abs(took[0] - 20) <= 1
     assert min(took) >= 3 and 40 <= max(took) <= 65
     t.b.close()
+
+
+def absent(t, workgroups):
+    assert fem.load().fem_debug_team_absent(t.b.h, C.c_int32(workgroups)) == 0
+
+
+def test_teams_that_do_not_meet_in_a_run_of_rounds():
+    """Twelve jobs, two teams on four of the XCDs, one on the others; launches
+    leave out one workgroup per XCD, so that the second team of an XCD does not
+    meet. Every job still takes the solver steps of its rounds, no fewer and no
+    more, and ends as the step kernels end it."""
+    mesh, inds = block_jobs(12, 3)
+    ref = reference(mesh, inds)
+    t = Batch(mesh, inds)
+    absent(t, 8)
+
+    def steps(j):
+        info = t.b.job_info(j)
+        return info["hv_products"] + info["grad_passes"], info["newton_iters"], info["step"]
+
+    for rounds in (2, 3):
+        before = [steps(j) for j in t.ids]
+        assert t.b.run(t.P, max_rounds=rounds) == 12
+        print("rounds", rounds, t.launches(), flush=True)
+        for j, old in zip(t.ids, before):
+            new = steps(j)
+            assert 16 * rounds - 2 * (new[1] - old[1]) - 2 * (new[2] - old[2]) - 2 <= new[0] - old[0] <= 16 * rounds
+    assert t.b.run(t.P) == 0
+    close_to(t.displacements(), ref)
+    t.b.close()
