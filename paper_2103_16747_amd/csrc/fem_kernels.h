@@ -2093,7 +2093,8 @@ __global__ __launch_bounds__(64) void k_finalize(const Topo<T> *topos, const Ins
 // member that has waited kMeetTicks for the rest calls the team off, once and
 // for all, by a bit in the counter that only an incomplete team can get; no
 // job state has been touched by then and the host runs those jobs through the
-// other kernels. A team that has met is resident as a whole, runs the same
+// other kernels. Teams that gather after that in the same launch, in the
+// places of others that left, don't wait again. A team that has met is resident as a whole, runs the same
 // sequence of barriers in every member, and is never waited for by another
 // team. A barrier that should not come about for kStuckTicks all the same
 // ends the launch and is reported.
@@ -2137,7 +2138,10 @@ constexpr unsigned kCalledOff = 0xffffffffu;
 constexpr unsigned kCalledOffBit = 0x80000000u;
 constexpr unsigned kStopUnit = 1u << 24;                    // in the top counter, above any count of arrivals
 constexpr unsigned kArrivals = kStopUnit - 1;
-constexpr unsigned long long kMeetTicks = 20000000ull;      // 0.2 s of the 100 MHz clock
+// 20 ms of the 100 MHz clock: on a free device the workgroups of a launch are
+// all there within tens of microseconds, behind another kernel's last blocks
+// within that kernel's tail.
+constexpr unsigned long long kMeetTicks = 2000000ull;
 constexpr unsigned long long kStuckTicks = 2000000000ull;   // 20 s
 
 template <class U> __device__ __forceinline__ U ag_load(const U *p) {
@@ -2231,8 +2235,9 @@ __device__ __forceinline__ int team_wait(TeamSync *ts, unsigned ph, int *sh, Tea
 }
 
 // First meeting of a team (thread 0 of each member): true once all W members
-// are there. It leaves the counters as after barrier 1.
-__device__ __forceinline__ bool team_meet(TeamSync *ts, unsigned W, unsigned rank, TeamStat *stat) {
+// are there. It leaves the counters as after barrier 1. calledoff: the count
+// of teams called off before this launch.
+__device__ __forceinline__ bool team_meet(TeamSync *ts, unsigned W, unsigned rank, TeamStat *stat, unsigned calledoff) {
     const TeamGroup g(W, rank);
     bool last = true;
     if (g.many > 1) last = ag_add(&ts->group[g.index].v, 1u) + 1 == g.size;
@@ -2244,13 +2249,13 @@ __device__ __forceinline__ bool team_meet(TeamSync *ts, unsigned W, unsigned ran
             return true;
         }
     }
-    const unsigned long long t0 = wall_clock64();
+    const unsigned long long t0 = wall_clock64(), limit = ag_load(&stat->calledoff) == calledoff ? kMeetTicks : 0;
     for (;;) {
         const unsigned v = ag_load(&ts->flag.v);
         if (v == kCalledOff) return false;
         if (v >= 2u) return true;
         __builtin_amdgcn_s_sleep(8);
-        if (wall_clock64() - t0 > kMeetTicks) {
+        if (wall_clock64() - t0 > limit) {
             unsigned a = ag_load(&ts->top.v);
             while (a < g.many_top) {   // incomplete and not called off
                 if (__hip_atomic_compare_exchange_strong(&ts->top.v, &a, a | kCalledOffBit, __ATOMIC_RELAXED,
@@ -2438,7 +2443,8 @@ template <typename T, int LAWS, int COH>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) void k_team(const Topo<T> *topos, const InstBufs<T> *bufs, const int2 *jobs,
                                                  const TeamDesc *teams, const XcdDesc *xcds, TeamCtl *ctl,
                                                  TeamStat *stat, const SolveParams *P, int span, int steps,
-                                                 int stop_early, unsigned stop_at, unsigned launch) {
+                                                 int stop_early, unsigned stop_at, unsigned calledoff,
+                                                 unsigned launch) {
     using Lds = TileLds<T, false>;
     __shared__ __attribute__((aligned(32))) double pool[Lds::kDoubles > Lds::kTeamHv ? Lds::kDoubles : Lds::kTeamHv];
     __shared__ InstState S;
@@ -2451,7 +2457,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
     if (threadIdx.x == 0) {
         int place = (int)ag_add(&ctl->ticket[xcd / span].v, 1u);
         if (place >= X.nteam * X.W ||
-            !team_meet(&ctl->sync[X.team0 + place / X.W], (unsigned)X.W, (unsigned)(place % X.W), stat))
+            !team_meet(&ctl->sync[X.team0 + place / X.W], (unsigned)X.W, (unsigned)(place % X.W), stat, calledoff))
             place = -1;
         sh[0] = place;
     }

@@ -106,6 +106,11 @@ struct JobGroup {
     int tile_off = 0, tile_n = 0, node_off = 0, node_n = 0, live_off = 0, live_n = 0;
 };
 
+// A meeting that fails costs 20 ms. The rounds that follow it without teams
+// take 0.1 to 3 ms each, and as many again each time that the next meeting
+// fails too (a stream with a CU mask, say, on which teams never fit).
+constexpr int kTeamOff = 64, kTeamOffMost = 65536;
+
 // Launch shape of the team kernel for the jobs in the work tables.
 struct TeamPlan {
     bool tried = false;       // made for the current work tables
@@ -165,6 +170,9 @@ struct fem_batch {
     long long team_launches = 0, step_rounds = 0;   // launches of the team kernel, rounds of the step kernels
     int xcds = 0, cus = 0;          // of the device; xcds = 0: no team kernel
     TeamPlan plan;
+    // After a team that did not meet, rounds that the step kernels take before
+    // teams are tried again, and the same for the next time.
+    int team_off = 0, team_off_next = kTeamOff;
     int absent = 0;                 // workgroups left out of each launch of teams (for tests)
     void *d_team = nullptr;         // team, XCD and job tables of the plan
     size_t team_bytes = 0, team_ctl_bytes = 0;
@@ -1012,7 +1020,7 @@ int launch_teams(fem_batch *B, int steps, int stop_after) {
     B->team_launches++;
     with_team_kernel<T>(B->plan.laws, B->plan.span, [&](auto kernel) {
         kernel<<<grid, block, 0, B->stream>>>(tp, bf, B->t_jobs, B->t_teams, B->t_xcds, B->d_team_ctl, stat, P,
-                                              B->plan.span, steps, early, at,
+                                              B->plan.span, steps, early, at, B->stat_seen.calledoff,
                                               (unsigned)B->team_launches);
         return 0;
     });
@@ -1038,7 +1046,6 @@ int catch_up(fem_batch *B, int rounds, int chunk) {
 template <typename T>
 int run_impl(fem_batch *B, int max_rounds, int *n_running) {
     int rounds = 0, running = 0;
-    bool no_team = false;
     // the mirror of the states is current: every launch ends with its update
     for (;;) {
         running = 0;
@@ -1073,7 +1080,7 @@ int run_impl(fem_batch *B, int max_rounds, int *n_running) {
         }
         // rounds that record kernel times run the step kernels
         const bool timing = B->timer.every > 0;
-        bool team = !no_team && team_usable(B) && !(timing && B->timer.rounds % B->timer.every == 0);
+        bool team = B->team_off == 0 && team_usable(B) && !(timing && B->timer.rounds % B->timer.every == 0);
         if (team) {
             const int laws = kernel_variant(B) & 3;
             // A plan holds the jobs that ran when it was made: one restarted
@@ -1109,15 +1116,16 @@ int run_impl(fem_batch *B, int max_rounds, int *n_running) {
                 B->timer.rounds++;
                 for (int k = 0; k < KernelTimer::kKinds; k++) B->timer.seen[k] += now.steps;
             }
-            // A team that did not meet, or none that moved: the step kernels
-            // take over until the next run. In a run of so many rounds they
-            // take the jobs left behind through those that the other teams have
-            // taken.
-            no_team = now.calledoff != was.calledoff || now.steps == 0;
-            if (!no_team) {
+            if (now.calledoff == was.calledoff && now.steps > 0) {
+                B->team_off_next = kTeamOff;
                 rounds += n;
                 continue;
             }
+            // A team that did not meet (or none that moved): the step kernels
+            // take over for a while. In a run of so many rounds they take the
+            // jobs left behind through those that the other teams have taken.
+            B->team_off = B->team_off_next;
+            B->team_off_next = std::min(2 * B->team_off_next, kTeamOffMost);
             if (now.steps > 0) {
                 if (max_rounds > 0) TRY(catch_up<T>(B, n, chunk));
                 rounds += n;
@@ -1127,6 +1135,7 @@ int run_impl(fem_batch *B, int max_rounds, int *n_running) {
         TRY(launch_round<T>(B, chunk));
         TRY(read_states(B));
         B->step_rounds++;
+        if (B->team_off > 0) B->team_off--;
         rounds++;
     }
     if (n_running) *n_running = running;

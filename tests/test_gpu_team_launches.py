@@ -124,3 +124,35 @@ def test_teams_that_do_not_meet_in_a_run_of_rounds():
     assert t.b.run(t.P) == 0
     close_to(t.displacements(), ref)
     t.b.close()
+
+
+def test_teams_that_never_meet_are_left_alone():
+    """The only team of a job lacks a member: the step kernels take the job,
+    teams are not tried again for a number of rounds, and then they are."""
+    mesh, inds = block_jobs(1, 2)
+    ref = reference(mesh, inds)
+    t = Batch(mesh, inds)
+    absent(t, 8)
+    for k in range(40):   # short runs, each of which would wait for the meeting
+        assert t.b.run(t.P, max_rounds=1) == 1
+        t.restart()
+    tries, rounds = t.launches()
+    print("tries", tries, "rounds", rounds, flush=True)
+    assert tries == 1 and rounds == 40
+    assert t.b.run(t.P) == 0
+    close_to(t.displacements(), ref)
+    t.restart()
+    tries = t.launches()[0]
+    absent(t, 0)
+    for k in range(200):
+        assert t.b.run(t.P) == 0
+        close_to(t.displacements(), ref)
+        t.restart()
+        if t.launches()[0] > tries:
+            break
+    before = t.launches()
+    assert before[0] > tries
+    assert t.b.run(t.P) == 0
+    close_to(t.displacements(), ref)
+    assert t.launches()[0] > before[0] and t.launches()[1] == before[1]
+    t.b.close()
