@@ -1837,18 +1837,18 @@ __device__ __forceinline__ void node_lag(const TopoD<T> &tp, const BufsD<T> &B, 
 template <typename T, bool FRIC, int COH, class View>
 __device__ __forceinline__ void node_block(View view, const InstState *s, int blk, int npq, int block_jacobi) {
     const int phase = uni<COH>((int)s->phase);
-    if (phase == PH_CG || phase == PH_EVAL_HV) {
+    if (phase == PH_EVAL_HV) {
         const auto V = view();
-        // (the team kernel's CG updates go through team_update)
+        node_update<T, true, true, COH>(V.tp, V.B, s, blk, npq ? npq : V.tp.ntile + V.tp.ncb);
+    } else if (COH == kAlone && phase == PH_CG) {   // the team kernel's CG updates go through team_update
+        const auto V = view();
         // a CG update changes free nodes only: blocks of fixed nodes (numbered
         // last) have nothing to do; block 0 always runs (it records p.q)
-        if (phase == PH_CG && blk > 0 && blk * kBlock >= V.tp.n_free) return;
-        // the inertial term and the evaluation as separate instances keep them
-        // out of the quasi-static CG update
-        const int np = npq ? npq : V.tp.ntile + V.tp.ncb;
-        if (phase == PH_EVAL_HV)
-            node_update<T, true, true, COH>(V.tp, V.B, s, blk, np);
-        else if (s->mdt2 > 0.0)
+        if (blk > 0 && blk * kBlock >= V.tp.n_free) return;
+        // the inertial term as a separate instance keeps it out of the
+        // quasi-static CG update
+        const int np = V.tp.ntile + V.tp.ncb;
+        if (s->mdt2 > 0.0)
             node_update<T, true, false, COH>(V.tp, V.B, s, blk, np);
         else
             node_update<T, false, false, COH>(V.tp, V.B, s, blk, np);
@@ -2271,18 +2271,18 @@ __device__ __forceinline__ bool team_meet(TeamSync *ts, unsigned W, unsigned ran
 }
 
 // Word i of a table that the launch does not change, by a scalar load.
-__device__ __forceinline__ int ld_int(glob_ptr<const int> p, int i) {
-    return ((const __attribute__((address_space(4))) int *)(const int *)p)[i];
+__device__ __forceinline__ int ld_int(const int *p, int i) {
+    return ((const __attribute__((address_space(4))) int *)p)[i];
 }
 
 // Entries and tets of one tile.
 template <typename T> struct TileSpan {
     int e0, ne, k0, nk;
     __device__ __forceinline__ TileSpan(const TopoD<T> &tp, int t) {
-        e0 = ld_int(tp.tile_ent, t);
-        ne = ld_int(tp.tile_ent, t + 1) - e0;
-        k0 = ld_int(tp.tile_tet, t);
-        nk = ld_int(tp.tile_tet, t + 1) - k0;
+        e0 = ld_int((const int *)tp.tile_ent, t);
+        ne = ld_int((const int *)tp.tile_ent, t + 1) - e0;
+        k0 = ld_int((const int *)tp.tile_tet, t);
+        nk = ld_int((const int *)tp.tile_tet, t + 1) - k0;
     }
 };
 
@@ -2440,7 +2440,7 @@ __device__ __forceinline__ bool running_phase(int ph) { return ph != PH_IDLE && 
 // At least 4 (FP32) and 2 (FP64) wavefronts per SIMD, as many as it needs
 // registers for; teams are as large as fit at once.
 template <typename T, int LAWS, int COH>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) void k_team(const Topo<T> *topos, const InstBufs<T> *bufs, const int2 *jobs,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) void k_team(const Topo<T> *topos, const InstBufs<T> *bufs, const int *jobs,
                                                  const TeamDesc *teams, const XcdDesc *xcds, TeamCtl *ctl,
                                                  TeamStat *stat, const SolveParams *P, int span, int steps,
                                                  int stop_early, unsigned stop_at, unsigned calledoff,
@@ -2470,7 +2470,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
         unsigned ph = 1;
         int most = 0, r = 0;
         for (int q = 0; q < D.job_n && r >= 0; q++) {
-            const int job = ld_table<int2>(jobs + D.job_off, q).x;
+            const int job = ld_int(jobs, D.job_off + q);
             // The state as the host or the last launch left it; member 0
             // writes it back at the end.
             unsigned long long *ls = (unsigned long long *)&S;

@@ -179,7 +179,7 @@ struct fem_batch {
     TeamCtl *d_team_ctl = nullptr;
     const TeamDesc *t_teams = nullptr;
     const XcdDesc *t_xcds = nullptr;
-    const int2 *t_jobs = nullptr;
+    const int *t_jobs = nullptr;
     void *d_topos = nullptr, *d_bufs = nullptr;
     int2 *d_work_tile = nullptr, *d_work_node = nullptr;
     int nwork_tile = 0, nwork_node = 0, cap_work_tile = 0, cap_work_node = 0;
@@ -944,7 +944,7 @@ int plan_teams(fem_batch *B, int laws) {
     const auto per_xcd = deal(jobs, places);
     std::vector<TeamDesc> teams;
     std::vector<XcdDesc> xd(kMaxXcds, XcdDesc{0, 0, 1, 0});
-    std::vector<int2> lv;
+    std::vector<int> lv;
     int need = 0;
     for (int x = 0; x < places; x++) {
         const int nj = (int)per_xcd[x].size();
@@ -957,7 +957,7 @@ int plan_teams(fem_batch *B, int laws) {
         for (const std::vector<int> &mem : parts) {
             TeamDesc D{(int)lv.size(), (int)mem.size()};
             for (int i : mem) {
-                lv.push_back(make_int2(i, 0));
+                lv.push_back(i);
                 most = std::max(most, items(i));
             }
             teams.push_back(D);
@@ -966,7 +966,7 @@ int plan_teams(fem_batch *B, int laws) {
         need = std::max(need, nt * xd[x].W);
     }
     Arena A;
-    const size_t o_t = A.take<TeamDesc>(teams.size()), o_x = A.take<XcdDesc>(xd.size()), o_lv = A.take<int2>(lv.size());
+    const size_t o_t = A.take<TeamDesc>(teams.size()), o_x = A.take<XcdDesc>(xd.size()), o_lv = A.take<int>(lv.size());
     if (A.off > B->team_bytes) {
         if (B->d_team) (void)hipFree(B->d_team);
         B->d_team = nullptr;
@@ -991,13 +991,13 @@ int plan_teams(fem_batch *B, int laws) {
     std::vector<char> image(A.off);
     std::memcpy(image.data() + o_t, teams.data(), teams.size() * sizeof(TeamDesc));
     std::memcpy(image.data() + o_x, xd.data(), xd.size() * sizeof(XcdDesc));
-    std::memcpy(image.data() + o_lv, lv.data(), lv.size() * sizeof(int2));
+    std::memcpy(image.data() + o_lv, lv.data(), lv.size() * sizeof(int));
     HIP_TRY(hipMemcpyAsync(B->d_team, image.data(), image.size(), hipMemcpyHostToDevice, B->stream));
     TRY(sync(B));
     char *base = (char *)B->d_team;
     B->t_teams = (const TeamDesc *)(base + o_t);
     B->t_xcds = (const XcdDesc *)(base + o_x);
-    B->t_jobs = (const int2 *)(base + o_lv);
+    B->t_jobs = (const int *)(base + o_lv);
     plan.span = span;
     plan.wider = items(jobs[0]) > kTeamSpanItems ? B->xcds / (2 * span) : 0;
     plan.blocks = ceil_div(need, span) * B->xcds;
