@@ -2094,7 +2094,7 @@ __global__ __launch_bounds__(64) void k_finalize(const Topo<T> *topos, const Ins
 // for all, by a bit in the counter that only an incomplete team can get; no
 // job state has been touched by then and the host runs those jobs through the
 // other kernels. Teams that gather after that in the same launch, in the
-// places of others that left, don't wait again. A team that has met is resident as a whole, runs the same
+// places of others that left, hardly wait again. A team that has met is resident as a whole, runs the same
 // sequence of barriers in every member, and is never waited for by another
 // team. A barrier that should not come about for kStuckTicks all the same
 // ends the launch and is reported.
@@ -2249,13 +2249,16 @@ __device__ __forceinline__ bool team_meet(TeamSync *ts, unsigned W, unsigned ran
             return true;
         }
     }
-    const unsigned long long t0 = wall_clock64(), limit = ag_load(&stat->calledoff) == calledoff ? kMeetTicks : 0;
+    const unsigned long long t0 = wall_clock64();
     for (;;) {
         const unsigned v = ag_load(&ts->flag.v);
         if (v == kCalledOff) return false;
         if (v >= 2u) return true;
         __builtin_amdgcn_s_sleep(8);
-        if (wall_clock64() - t0 > limit) {
+        const unsigned long long waited = wall_clock64() - t0;
+        // (the count is asked for late: 1000 workgroups reading one address at
+        // once took 40 us of each launch)
+        if (waited > kMeetTicks || (waited > kMeetTicks / 100 && ag_load(&stat->calledoff) != calledoff)) {
             unsigned a = ag_load(&ts->top.v);
             while (a < g.many_top) {   // incomplete and not called off
                 if (__hip_atomic_compare_exchange_strong(&ts->top.v, &a, a | kCalledOffBit, __ATOMIC_RELAXED,
