@@ -2120,10 +2120,11 @@ struct TeamSync {
 };
 constexpr int kMaxXcds = 16;
 // done, calledoff and stuck only grow, and the host takes differences between
-// launches, which hold when they wrap; steps, a maximum over the teams, is the
-// launch's own: the last workgroup to leave clears it.
+// launches, which hold when they wrap; gone (a team has been called off) and
+// steps, a maximum over the teams, are the launch's own: the last workgroup to
+// leave clears them.
 struct TeamStat {
-    unsigned done, calledoff, stuck, steps;
+    unsigned done, calledoff, stuck, steps, gone;
 };
 struct TeamCtl {
     TeamLine ticket[kMaxXcds];   // places taken, per `span` XCDs
@@ -2235,9 +2236,8 @@ __device__ __forceinline__ int team_wait(TeamSync *ts, unsigned ph, int *sh, Tea
 }
 
 // First meeting of a team (thread 0 of each member): true once all W members
-// are there. It leaves the counters as after barrier 1. calledoff: the count
-// of teams called off before this launch.
-__device__ __forceinline__ bool team_meet(TeamSync *ts, unsigned W, unsigned rank, TeamStat *stat, unsigned calledoff) {
+// are there. It leaves the counters as after barrier 1.
+__device__ __forceinline__ bool team_meet(TeamSync *ts, unsigned W, unsigned rank, TeamStat *stat) {
     const TeamGroup g(W, rank);
     bool last = true;
     if (g.many > 1) last = ag_add(&ts->group[g.index].v, 1u) + 1 == g.size;
@@ -2256,14 +2256,13 @@ __device__ __forceinline__ bool team_meet(TeamSync *ts, unsigned W, unsigned ran
         if (v >= 2u) return true;
         __builtin_amdgcn_s_sleep(8);
         const unsigned long long waited = wall_clock64() - t0;
-        // (the count is asked for late: 1000 workgroups reading one address at
-        // once took 40 us of each launch)
-        if (waited > kMeetTicks || (waited > kMeetTicks / 100 && ag_load(&stat->calledoff) != calledoff)) {
+        if (waited > kMeetTicks || (waited > kMeetTicks / 100 && ag_load(&stat->gone) != 0)) {
             unsigned a = ag_load(&ts->top.v);
             while (a < g.many_top) {   // incomplete and not called off
                 if (__hip_atomic_compare_exchange_strong(&ts->top.v, &a, a | kCalledOffBit, __ATOMIC_RELAXED,
                                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
                     ag_add(&stat->calledoff, 1u);
+                    ag_store(&stat->gone, 1u);
                     ag_store(&ts->flag.v, kCalledOff);
                     return false;
                 }
@@ -2446,8 +2445,7 @@ template <typename T, int LAWS, int COH>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) void k_team(const Topo<T> *topos, const InstBufs<T> *bufs, const int *jobs,
                                                  const TeamDesc *teams, const XcdDesc *xcds, TeamCtl *ctl,
                                                  TeamStat *stat, const SolveParams *P, int span, int steps,
-                                                 int stop_early, unsigned stop_at, unsigned calledoff,
-                                                 unsigned launch) {
+                                                 int stop_early, unsigned stop_at, unsigned launch) {
     using Lds = TileLds<T, false>;
     __shared__ __attribute__((aligned(32))) double pool[Lds::kDoubles > Lds::kTeamHv ? Lds::kDoubles : Lds::kTeamHv];
     __shared__ InstState S;
@@ -2460,7 +2458,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
     if (threadIdx.x == 0) {
         int place = (int)ag_add(&ctl->ticket[xcd / span].v, 1u);
         if (place >= X.nteam * X.W ||
-            !team_meet(&ctl->sync[X.team0 + place / X.W], (unsigned)X.W, (unsigned)(place % X.W), stat, calledoff))
+            !team_meet(&ctl->sync[X.team0 + place / X.W], (unsigned)X.W, (unsigned)(place % X.W), stat))
             place = -1;
         sh[0] = place;
     }
@@ -2572,6 +2570,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
         stat_mirror->stuck = ag_load(&stat->stuck);
         stat_mirror->steps = ag_load(&stat->steps);
         ag_store(&stat->steps, 0u);
+        ag_store(&stat->gone, 0u);
         for (int x = 0; x < kMaxXcds; x++) {
             const XcdDesc Y = ld_table<XcdDesc>(xcds, x);
             for (int t = Y.team0; t < Y.team0 + Y.nteam; t++) {

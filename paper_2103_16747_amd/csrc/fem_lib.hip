@@ -1020,7 +1020,7 @@ int launch_teams(fem_batch *B, int steps, int stop_after) {
     B->team_launches++;
     with_team_kernel<T>(B->plan.laws, B->plan.span, [&](auto kernel) {
         kernel<<<grid, block, 0, B->stream>>>(tp, bf, B->t_jobs, B->t_teams, B->t_xcds, B->d_team_ctl, stat, P,
-                                              B->plan.span, steps, early, at, B->stat_seen.calledoff,
+                                              B->plan.span, steps, early, at,
                                               (unsigned)B->team_launches);
         return 0;
     });
@@ -2300,7 +2300,7 @@ int fem_debug_team_launches(const fem_batch *B, int64_t *teams, int64_t *step_ro
 int fem_debug_team_counters(fem_batch *B, uint32_t value) {
     if (!B) return fail(FEM_E_INVALID, "null argument");
     TRY(set_device(B));
-    const TeamStat stat{value, value, value, 0u};
+    const TeamStat stat{value, value, value, 0u, 0u};
     HIP_TRY(hipMemcpyAsync(B->d_states + B->capacity, &stat, sizeof stat, hipMemcpyHostToDevice, B->stream));
     TRY(sync(B));
     B->stat_seen = stat;
