@@ -25,7 +25,13 @@
  *   - return value 0 = FEM_OK, negative = error (no exception crosses the
  *     ABI); fem_last_error() then describes the failure (thread-local);
  *     positive = a usable result with a warning (FEM_W_FLOOR);
- *   - a handle is not thread-safe; distinct handles are independent.
+ *   - a handle is not thread-safe; distinct handles are independent. Handles in
+ *     use at a time on one device share it: a run that has the device to itself
+ *     among the runs of this process keeps its jobs on it for up to 20 ms (in a
+ *     run of so many rounds 128 solver steps) at a
+ *     time, ends such a launch within 16 solver steps when another handle
+ *     waits, and beside other runs takes no more than its share of the chip or
+ *     lets their kernels in between two of its own.
  */
 #ifndef LIBFEM_FEM_H
 #define LIBFEM_FEM_H

@@ -2102,8 +2102,14 @@ __global__ __launch_bounds__(64) void k_finalize(const Topo<T> *topos, const Ins
 struct TeamDesc {
     int job_off, job_n;         // its jobs in the list
 };
+// One place of the plan: an XCD, or several consecutive ones that its teams span.
 struct XcdDesc {
-    int team0, nteam, W, pad;   // teams team0 .. team0 + nteam - 1 of W workgroups each, per `span` XCDs
+    int team0, nteam, W, pad;   // teams team0 .. team0 + nteam - 1 of W workgroups each
+};
+// The launch's XCDs among the device's `count`: places begin at XCD `first` and
+// are 1 << shift XCDs each.
+struct XcdMap {
+    int first, count, shift;
 };
 // Arrivals are counted in groups of kTeamGroup members, the last of a group
 // arriving for it at the team's counter: arrivals at one address are served
@@ -2120,19 +2126,26 @@ struct TeamSync {
 };
 constexpr int kMaxXcds = 16;
 // done, calledoff and stuck only grow, and the host takes differences between
-// launches, which hold when they wrap; gone (a team has been called off) and
-// steps, a maximum over the teams, are the launch's own: the last workgroup to
-// leave clears them.
-struct TeamStat {
-    unsigned done, calledoff, stuck, steps, gone;
+// launches, which hold when they wrap; over (a team has seen that the launch is
+// to end), gone (a team has been called off) and steps, a maximum over the
+// teams, are the launch's own: the last workgroup to leave clears them.
+struct alignas(8) TeamStat {
+    unsigned done, over;   // read together
+    unsigned calledoff, stuck, steps, gone;
+};
+// Pinned: the kernel's counters as of its last launch, and the host's wish that
+// the launch in flight ends.
+struct TeamHost {
+    TeamStat stat;
+    unsigned yield;
 };
 struct TeamCtl {
-    TeamLine ticket[kMaxXcds];   // places taken, per `span` XCDs
+    TeamLine ticket[kMaxXcds];   // memberships taken, per place of the plan
     TeamLine leave;              // workgroups that have left
-    // the host's mirror of the states and of TeamStat (pinned); here, not in
+    // the host's mirror of the states, and its words (pinned); here, not in
     // the arguments, which would hold scalar registers throughout
     InstState *mirror;
-    TeamStat *stat_mirror;
+    TeamHost *host;
     TeamSync sync[1];            // one per team
 };
 constexpr unsigned kCalledOff = 0xffffffffu;
@@ -2144,6 +2157,13 @@ constexpr unsigned kArrivals = kStopUnit - 1;
 // within that kernel's tail.
 constexpr unsigned long long kMeetTicks = 2000000ull;
 constexpr unsigned long long kStuckTicks = 2000000000ull;   // 20 s
+// A launch to the end holds its XCDs for 20 ms at most, since other streams'
+// kernels wait for it. Every kTeamPoll solver steps (2.4 ms of the largest
+// batch) a team looks at the clock, and every millisecond at the host's wish, a
+// read over the bus; the first to see an end tells the others.
+constexpr unsigned long long kLaunchTicks = 2000000ull, kLookTicks = 100000ull;
+constexpr int kTeamPoll = 16;
+enum : int { kStopDone = 1, kStopPoll = 2 };                // reasons to end early: see k_team
 
 template <class U> __device__ __forceinline__ U ag_load(const U *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -2209,6 +2229,32 @@ __device__ __forceinline__ void team_arrive(TeamSync *ts, unsigned ph, unsigned 
         }
     }
 }
+
+// Whether a launch to the end is over, looked up by a thread of member 0 while
+// thread 0 waits at the second barrier of a step, where no loads are in flight
+// whose waits a branch would make strict (at the first, behind the node pass's
+// requests, it cost 0.5 of 11.7 us a step). Its request is in the L2 before
+// member 0 arrives at the first barrier of the next step, whose flag tells all
+// members. In LDS: arguments kept in scalar registers throughout would be
+// spilled.
+struct TeamLook {
+    unsigned long long end, next;   // when the launch is over, and when to look again
+    TeamStat *stat;
+    const unsigned *yield;
+    int on;
+    unsigned launch;
+    __device__ __forceinline__ void look_up(TeamSync *ts, int c) {
+        if (threadIdx.x != kBlock - 64 || on == 0 || c % kTeamPoll != kTeamPoll - 1) return;
+        const unsigned long long now = wall_clock64();
+        if (now < next) return;
+        next = now + kLookTicks;
+        if (now < end && __hip_atomic_load(yield, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == 0) return;
+        ag_store(&stat->over, 1u);
+        ag_add(&ts->top.v, kStopUnit);
+        // both arrive before this workgroup can leave: the last one clears them
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+};
 
 // Returns 0, 1 (stop) or -1 (the barrier did not come about).
 __device__ __forceinline__ int team_wait(TeamSync *ts, unsigned ph, int *sh, TeamStat *stat) {
@@ -2438,32 +2484,40 @@ __device__ __forceinline__ void team_update(const TopoD<T> &tp, const BufsD<T> &
 __device__ __forceinline__ bool running_phase(int ph) { return ph != PH_IDLE && ph != PH_DONE; }
 
 // LAWS: constitutive laws among the jobs (1 Neo-Hookean, 2 co-rotational, 3
-// both). COH: kXcd, or kChip with teams over `span` XCDs each.
+// both). COH: kXcd, or kChip with teams over several XCDs each. stop_on: with
+// kStopDone the launch ends once `done` has reached stop_at or a team has said
+// so, with kStopPoll after kLaunchTicks or at the host's wish; otherwise each
+// job takes `steps` solver steps or ends.
 // At least 4 (FP32) and 2 (FP64) wavefronts per SIMD, as many as it needs
 // registers for; teams are as large as fit at once.
 template <typename T, int LAWS, int COH>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) void k_team(const Topo<T> *topos, const InstBufs<T> *bufs, const int *jobs,
                                                  const TeamDesc *teams, const XcdDesc *xcds, TeamCtl *ctl,
-                                                 TeamStat *stat, const SolveParams *P, int span, int steps,
-                                                 int stop_early, unsigned stop_at, unsigned launch) {
+                                                 TeamStat *stat, const SolveParams *P, XcdMap map, int steps, int stop_on,
+                                                 unsigned stop_at, unsigned launch) {
     using Lds = TileLds<T, false>;
     __shared__ __attribute__((aligned(32))) double pool[Lds::kDoubles > Lds::kTeamHv ? Lds::kDoubles : Lds::kTeamHv];
     __shared__ InstState S;
     __shared__ int sh[1];
+    __shared__ TeamLook L;
     static_assert(sizeof(InstState) % 8 == 0, "copied as 8-byte words");
     constexpr int kStateWords = sizeof(InstState) / 8;
     // hardware register 20: XCC_ID, low four bits
     const int xcd = __builtin_amdgcn_readfirstlane((int)(__builtin_amdgcn_s_getreg(20 | (3 << 11)) & 15u));
-    const XcdDesc X = ld_table<XcdDesc>(xcds, xcd / span);
+    const int at = (xcd >= map.first ? xcd - map.first : xcd - map.first + map.count) >> map.shift;
+    int place = 0;
+    if (threadIdx.x == 0) place = (int)ag_add(&ctl->ticket[at].v, 1u);
+    const XcdDesc X = ld_table<XcdDesc>(xcds, at);
     if (threadIdx.x == 0) {
-        int place = (int)ag_add(&ctl->ticket[xcd / span].v, 1u);
         if (place >= X.nteam * X.W ||
             !team_meet(&ctl->sync[X.team0 + place / X.W], (unsigned)X.W, (unsigned)(place % X.W), stat))
             place = -1;
         sh[0] = place;
+        const unsigned long long now = wall_clock64();
+        L = {now + kLaunchTicks, now + kLookTicks, stat, &ctl->host->yield, stop_on & kStopPoll, launch};
     }
     __syncthreads();
-    const int place = __builtin_amdgcn_readfirstlane(sh[0]);
+    place = __builtin_amdgcn_readfirstlane(sh[0]);
     if (place >= 0) {
         const int team = X.team0 + place / X.W, rank = place % X.W, W = X.W;
         const TeamDesc D = ld_table<TeamDesc>(teams, team);
@@ -2490,7 +2544,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
             bool stop = false;
             for (; c < steps && running_phase(phase) && !stop; c++) {
                 bool ask = false;
-                if (stop_early && rank == 0 && threadIdx.x == 0) ask = (int)(ag_load(&stat->done) - stop_at) >= 0;
+                if ((stop_on & kStopDone) && rank == 0 && threadIdx.x == 0) {
+                    const unsigned long long both = ag_load((const unsigned long long *)&stat->done);
+                    ask = (int)((unsigned)both - stop_at) >= 0 || (both >> 32) != 0;
+                }
                 if (phase == PH_CG || phase == PH_EVAL_HV) {
                     const JobView<T> V(topos, bufs, job);
                     if ((LAWS & 1) && nh)
@@ -2526,6 +2583,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
                                                  P->block_jacobi);
                 }
                 team_arrive(ts, ++ph, W, rank, false);
+                if (rank == 0) L.look_up(ts, c);
                 r = team_wait(ts, ph, sh, stat);
                 if (r < 0) break;
                 if (threadIdx.x < 64) {
@@ -2547,7 +2605,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
             if (rank == 0 && r >= 0) {
                 if (threadIdx.x == 0) {
                     if (c > 0 && !running_phase(phase)) ag_add(&stat->done, 1u);
-                    S.launch = launch;
+                    S.launch = L.launch;
                 }
                 __syncthreads();
                 const JobView<T> V(topos, bufs, job);
@@ -2564,13 +2622,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
     // clears the teams' for the next launch
     if (threadIdx.x == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if (threadIdx.x == 0 && ag_add(&ctl->leave.v, 1u) == gridDim.x - 1) {
-        TeamStat *stat_mirror = ctl->stat_mirror;
+        TeamStat *stat_mirror = &ctl->host->stat;
         stat_mirror->done = ag_load(&stat->done);
         stat_mirror->calledoff = ag_load(&stat->calledoff);
         stat_mirror->stuck = ag_load(&stat->stuck);
         stat_mirror->steps = ag_load(&stat->steps);
         ag_store(&stat->steps, 0u);
         ag_store(&stat->gone, 0u);
+        ag_store(&stat->over, 0u);
         for (int x = 0; x < kMaxXcds; x++) {
             const XcdDesc Y = ld_table<XcdDesc>(xcds, x);
             for (int t = Y.team0; t < Y.team0 + Y.nteam; t++) {

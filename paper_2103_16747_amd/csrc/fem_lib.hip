@@ -117,6 +117,7 @@ struct TeamPlan {
     bool valid = false;       // and the team kernel takes these jobs
     int blocks = 0, laws = 0;
     int span = 1;             // XCDs of a team
+    int xcds = 0;             // XCDs in use, consecutive ones
     int wider = 0;   // with at most so many jobs running, teams could span more XCDs than these
 };
 
@@ -165,7 +166,7 @@ struct fem_batch {
     std::vector<TopoRec> topos;
     std::vector<InstRec> insts;     // size capacity
     InstState *d_states = nullptr;  // capacity states, then the team kernel's TeamStat
-    InstState *h_states = nullptr;  // pinned mirror
+    InstState *h_states = nullptr;  // pinned mirror, then TeamHost
     TeamStat stat_seen{};           // counters as of the last launch
     long long team_launches = 0, step_rounds = 0;   // launches of the team kernel, rounds of the step kernels
     int xcds = 0, cus = 0;          // of the device; xcds = 0: no team kernel
@@ -173,6 +174,8 @@ struct fem_batch {
     // After a team that did not meet, rounds that the step kernels take before
     // teams are tried again, and the same for the next time.
     int team_off = 0, team_off_next = kTeamOff;
+    fem_batch *next_run = nullptr;  // runs in flight on the device (DeviceShare)
+    unsigned held = 0;              // XCDs of the launch of teams in flight
     int absent = 0;                 // workgroups left out of each launch of teams (for tests)
     void *d_team = nullptr;         // team, XCD and job tables of the plan
     size_t team_bytes = 0, team_ctl_bytes = 0;
@@ -234,6 +237,94 @@ int set_device(const fem_batch *B) {
     return FEM_OK;
 }
 
+// The states and, behind them, the team kernel's counters (in the mirror they
+// begin its TeamHost).
+size_t states_bytes(const fem_batch *B) { return B->capacity * sizeof(InstState) + sizeof(TeamStat); }
+TeamHost *team_host(const fem_batch *B) { return (TeamHost *)(B->h_states + B->capacity); }
+
+// ---------------------------------------------------------------------------
+// The device among the batches of this process. The teams of a launch hold
+// their XCDs until it ends, where the step kernels of other streams get in
+// between two passes. So a launch of teams takes at most its share, the XCDs
+// over the runs in flight, of those that no other launch holds; a run that
+// needs more takes the step kernels while others run. Whoever comes to wait
+// for the device asks launches that hold more to end.
+// ---------------------------------------------------------------------------
+struct DeviceShare {
+    fem_batch *runs = nullptr;   // runs in flight
+    unsigned held = 0;           // XCDs of the launches of teams in flight
+};
+DeviceShare g_share[kMaxDevices];   // under g_device_mu
+
+int runs_in_flight(const fem_batch *B) {
+    int n = 0;
+    for (const fem_batch *r = g_share[B->device].runs; r; r = r->next_run) n++;
+    return n;
+}
+
+// Before B waits for its stream, or starts a run: every other launch that
+// holds more XCDs than its share, B counted in, is asked to end. (Under
+// g_device_mu.)
+void ask_for_room(const fem_batch *B) {
+    const DeviceShare &D = g_share[B->device];
+    if (D.held == 0) return;
+    int others = 0;
+    for (const fem_batch *r = D.runs; r; r = r->next_run) others += r != B;
+    for (fem_batch *r = D.runs; r; r = r->next_run)
+        if (r != B && __builtin_popcount(r->held) * (others + 1) > r->xcds)
+            __atomic_store_n(&team_host(r)->yield, 1u, __ATOMIC_RELAXED);
+}
+
+// A run in flight.
+struct RunScope {
+    fem_batch *B;
+    explicit RunScope(fem_batch *b) : B(b) {
+        std::lock_guard<std::mutex> lock(g_device_mu);
+        ask_for_room(B);
+        B->next_run = g_share[B->device].runs;
+        g_share[B->device].runs = B;
+    }
+    ~RunScope() {
+        std::lock_guard<std::mutex> lock(g_device_mu);
+        fem_batch **at = &g_share[B->device].runs;
+        while (*at != B) at = &(*at)->next_run;
+        *at = B->next_run;
+        B->next_run = nullptr;
+    }
+    RunScope(const RunScope &) = delete;
+    RunScope &operator=(const RunScope &) = delete;
+};
+
+// The XCDs of one launch of teams: `want` consecutive ones from `first`, or
+// none (first < 0).
+struct XcdHold {
+    fem_batch *B;
+    int first = -1;
+    XcdHold(fem_batch *b, int want) : B(b) {
+        std::lock_guard<std::mutex> lock(g_device_mu);
+        DeviceShare &D = g_share[B->device];
+        const int n = B->xcds;
+        if (want * runs_in_flight(B) > n) return;
+        for (int x = 0; x < n && first < 0; x++) {
+            unsigned mask = 0;
+            for (int k = 0; k < want; k++) mask |= 1u << (x + k) % n;
+            if (D.held & mask) continue;
+            first = x;
+            B->held = mask;
+            D.held |= mask;
+            __atomic_store_n(&team_host(B)->yield, 0u, __ATOMIC_RELAXED);
+        }
+    }
+    ~XcdHold() { release(); }
+    void release() {
+        std::lock_guard<std::mutex> lock(g_device_mu);
+        g_share[B->device].held &= ~B->held;
+        B->held = 0;
+    }
+    XcdHold(const XcdHold &) = delete;
+    XcdHold &operator=(const XcdHold &) = delete;
+};
+
 int stage(fem_batch *B, size_t bytes) {
     if (B->h_stage_bytes >= bytes) return FEM_OK;
     if (B->h_stage) (void)hipHostFree(B->h_stage);
@@ -282,6 +373,10 @@ void timer_harvest(fem_batch *B) {
 }
 
 int sync(fem_batch *B) {
+    {
+        std::lock_guard<std::mutex> lock(g_device_mu);
+        ask_for_room(B);
+    }
     HIP_TRY(hipStreamSynchronize(B->stream));
     B->syncs++;
     if (B->timer.used) timer_harvest(B);
@@ -719,9 +814,6 @@ int params_to_device(fem_batch *B, const fem_solve_params &P) {
     return FEM_OK;
 }
 
-// The states and, behind them, the team kernel's counters.
-size_t states_bytes(const fem_batch *B) { return B->capacity * sizeof(InstState) + sizeof(TeamStat); }
-
 int read_states(fem_batch *B) {
     HIP_TRY(hipMemcpyAsync(B->h_states, B->d_states, states_bytes(B), hipMemcpyDeviceToHost, B->stream));
     return sync(B);
@@ -878,6 +970,9 @@ int launch_round(fem_batch *B, int chunk) {
 // Team kernel
 // ---------------------------------------------------------------------------
 constexpr int kTeamSteps = 2048;   // most solver steps of one launch
+// The same in a run of so many rounds, whose launches end by their steps alone
+// and not when another batch waits for the device: 19 ms of the largest batch.
+constexpr int kTeamRoundSteps = 128;
 
 // f(kernel) with the instance for the laws present and the teams' reach.
 template <typename T, class F> auto with_team_kernel(int laws, int span, F f) {
@@ -943,7 +1038,7 @@ int plan_teams(fem_batch *B, int laws) {
     const int places = B->xcds / span;
     const auto per_xcd = deal(jobs, places);
     std::vector<TeamDesc> teams;
-    std::vector<XcdDesc> xd(kMaxXcds, XcdDesc{0, 0, 1, 0});
+    std::vector<XcdDesc> xd(kMaxXcds, XcdDesc{0, 0, 1, 0});   // by place
     std::vector<int> lv;
     int need = 0;
     for (int x = 0; x < places; x++) {
@@ -984,7 +1079,7 @@ int plan_teams(fem_batch *B, int laws) {
         HIP_TRY(hipMemsetAsync(B->d_team_ctl, 0, ctl, B->stream));   // the kernel leaves it cleared
         TeamCtl head{};   // all zero but the mirror
         head.mirror = B->h_states;
-        head.stat_mirror = (TeamStat *)(B->h_states + B->capacity);
+        head.host = team_host(B);
         HIP_TRY(hipMemcpyAsync(B->d_team_ctl, &head, sizeof head, hipMemcpyHostToDevice, B->stream));
         TRY(sync(B));
     }
@@ -999,6 +1094,7 @@ int plan_teams(fem_batch *B, int laws) {
     B->t_xcds = (const XcdDesc *)(base + o_x);
     B->t_jobs = (const int *)(base + o_lv);
     plan.span = span;
+    plan.xcds = span * std::min(places, (int)jobs.size());
     plan.wider = items(jobs[0]) > kTeamSpanItems ? B->xcds / (2 * span) : 0;
     plan.blocks = ceil_div(need, span) * B->xcds;
     plan.valid = true;
@@ -1006,22 +1102,24 @@ int plan_teams(fem_batch *B, int laws) {
 }
 
 // One launch of the team kernel: up to `steps` solver steps of every running
-// job; with stop_after > 0 it hands back once so many jobs have ended. The
-// kernel writes the states and counters to the host's mirror as well.
+// job, on the XCDs from `first`. With stop_after > 0 it hands back once so many
+// jobs have ended, and, unless the jobs take whole rounds, after a time or when
+// another batch waits for the device. The kernel writes the states and counters
+// to the host's mirror as well.
 template <typename T>
-int launch_teams(fem_batch *B, int steps, int stop_after) {
+int launch_teams(fem_batch *B, int first, int steps, int stop_after, bool whole_rounds) {
     const Topo<T> *tp = (const Topo<T> *)B->d_topos;
     const InstBufs<T> *bf = (const InstBufs<T> *)B->d_bufs;
     TeamStat *stat = (TeamStat *)(B->d_states + B->capacity);
     const SolveParams *P = (const SolveParams *)B->d_params;
     const dim3 grid(std::max(1, B->plan.blocks - B->absent)), block(kBlock);
-    const int early = stop_after > 0 ? 1 : 0;
+    const int stop_on = (stop_after > 0 ? kStopDone : 0) | (whole_rounds ? 0 : kStopPoll);
     const unsigned at = B->stat_seen.done + (unsigned)stop_after;
+    const XcdMap map{first, B->xcds, __builtin_ctz(B->plan.span)};
     B->team_launches++;
     with_team_kernel<T>(B->plan.laws, B->plan.span, [&](auto kernel) {
-        kernel<<<grid, block, 0, B->stream>>>(tp, bf, B->t_jobs, B->t_teams, B->t_xcds, B->d_team_ctl, stat, P,
-                                              B->plan.span, steps, early, at,
-                                              (unsigned)B->team_launches);
+        kernel<<<grid, block, 0, B->stream>>>(tp, bf, B->t_jobs, B->t_teams, B->t_xcds, B->d_team_ctl, stat, P, map,
+                                              steps, stop_on, at, (unsigned)B->team_launches);
         return 0;
     });
     return launch_check("k_team");
@@ -1089,7 +1187,8 @@ int run_impl(fem_batch *B, int max_rounds, int *n_running) {
                 TRY(plan_teams<T>(B, laws));
             team = B->plan.valid;
         }
-        if (team) {
+        XcdHold hold(B, team ? B->plan.xcds : 0);
+        if (team && hold.first >= 0) {
             // As many rounds in one launch as may run without the host. To the
             // end, a launch ends early only for the others to spread out:
             // once a quarter of the jobs are done, or, with no more jobs than
@@ -1104,12 +1203,13 @@ int run_impl(fem_batch *B, int max_rounds, int *n_running) {
             int n = 1, steps = timing ? chunk : kTeamSteps;
             if (max_rounds > 0) {
                 // several rounds at once where one's end does not set the next's length
-                n = timing || !fixed_length ? 1 : std::max(1, std::min(max_rounds - rounds, kTeamSteps / chunk));
+                n = timing || !fixed_length ? 1 : std::max(1, std::min(max_rounds - rounds, kTeamRoundSteps / chunk));
                 steps = n * chunk;
             }
-            TRY(launch_teams<T>(B, steps, stop_after));
+            TRY(launch_teams<T>(B, hold.first, steps, stop_after, max_rounds > 0));
             TRY(sync(B));
-            const TeamStat now = *(const TeamStat *)(B->h_states + B->capacity), was = B->stat_seen;
+            hold.release();
+            const TeamStat now = team_host(B)->stat, was = B->stat_seen;
             B->stat_seen = now;
             if (now.stuck != was.stuck) return fail(FEM_E_DEVICE, "a team barrier did not come about");
             if (timing) {
@@ -1143,6 +1243,7 @@ int run_impl(fem_batch *B, int max_rounds, int *n_running) {
 }
 
 int run(fem_batch *B, int max_rounds, int *n_running) {
+    const RunScope scope(B);
     return B->precision == FEM_PREC_FP32 ? run_impl<float>(B, max_rounds, n_running)
                                          : run_impl<double>(B, max_rounds, n_running);
 }
@@ -1327,10 +1428,10 @@ int batch_create(const fem_config *cfg, int capacity, fem_batch **out) {
     if (!rc && hipMalloc(&B->d_bufs, bufs_bytes) != hipSuccess) rc = fail(FEM_E_OOM, "views");
     if (!rc && hipMalloc(&B->d_params, sizeof(SolveParams)) != hipSuccess) rc = fail(FEM_E_OOM, "params");
     if (!rc && hipMalloc(&B->d_live, capacity * sizeof(int)) != hipSuccess) rc = fail(FEM_E_OOM, "live list");
-    if (!rc && hipHostMalloc(&B->h_states, states_bytes(B)) != hipSuccess) rc = fail(FEM_E_OOM, "pinned");
+    if (!rc && hipHostMalloc(&B->h_states, capacity * sizeof(InstState) + sizeof(TeamHost)) != hipSuccess) rc = fail(FEM_E_OOM, "pinned");
     if (!rc && hipHostMalloc(&B->h_params, sizeof(SolveParams)) != hipSuccess) rc = fail(FEM_E_OOM, "pinned");
     if (!rc) {
-        std::memset(B->h_states, 0, states_bytes(B));
+        std::memset(B->h_states, 0, capacity * sizeof(InstState) + sizeof(TeamHost));
         std::memset(B->h_params, 0, sizeof(SolveParams));
         rc = stage(B, 4096);
     }
@@ -2300,7 +2401,7 @@ int fem_debug_team_launches(const fem_batch *B, int64_t *teams, int64_t *step_ro
 int fem_debug_team_counters(fem_batch *B, uint32_t value) {
     if (!B) return fail(FEM_E_INVALID, "null argument");
     TRY(set_device(B));
-    const TeamStat stat{value, value, value, 0u, 0u};
+    const TeamStat stat{value, 0u, value, value, 0u, 0u};
     HIP_TRY(hipMemcpyAsync(B->d_states + B->capacity, &stat, sizeof stat, hipMemcpyHostToDevice, B->stream));
     TRY(sync(B));
     B->stat_seen = stat;
