@@ -2084,9 +2084,9 @@ __global__ __launch_bounds__(64) void k_finalize(const Topo<T> *topos, const Ins
 // may have written is loaded past the CU's vector cache (ld_vec, ld_one).
 // Over several XCDs the stores go through to memory as well (kChip): 2.0 us
 // for a barrier with stores before and loads after it, 0.65 us on one XCD.
-// A workgroup reads the XCD it runs on from the hardware and takes the next
-// place of the teams there, so a team is where its kind needs it however
-// workgroups were dealt; places that stay empty make their team give up at its first meeting,
+// A workgroup reads the XCD it runs on from the hardware and is a member of a
+// team there, so a team is where its kind needs it however workgroups were
+// dealt; members that don't come make their team give up at its first meeting,
 // below.
 //
 // Every wait ends. A team first meets: its members are counted in, and a
@@ -2123,6 +2123,7 @@ struct TeamSync {
     TeamLine flag;                  // 2 * (last complete barrier) + stop, or kCalledOff
     TeamLine top;                   // arrivals of groups, and the stop request
     TeamLine group[kTeamGroups];    // arrivals of members
+    unsigned member[kTeamGroup * kTeamGroups];   // the last launch in which a workgroup was this member
 };
 constexpr int kMaxXcds = 16;
 // done, calledoff and stuck only grow, and the host takes differences between
@@ -2140,7 +2141,7 @@ struct TeamHost {
     unsigned yield;
 };
 struct TeamCtl {
-    TeamLine ticket[kMaxXcds];   // memberships taken, per place of the plan
+    TeamLine ticket[kMaxXcds];   // kChip: memberships taken, per place of the plan
     TeamLine leave;              // workgroups that have left
     // the host's mirror of the states, and its words (pinned); here, not in
     // the arguments, which would hold scalar registers throughout
@@ -2505,12 +2506,26 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
     // hardware register 20: XCC_ID, low four bits
     const int xcd = __builtin_amdgcn_readfirstlane((int)(__builtin_amdgcn_s_getreg(20 | (3 << 11)) & 15u));
     const int at = (xcd >= map.first ? xcd - map.first : xcd - map.first + map.count) >> map.shift;
-    int place = 0;
-    if (threadIdx.x == 0) place = (int)ag_add(&ctl->ticket[at].v, 1u);
     const XcdDesc X = ld_table<XcdDesc>(xcds, at);
+    // Workgroups are dealt to the XCDs, and on each to its CUs, in turn, so
+    // consecutive rows of the grid are consecutive CUs, and a team on one XCD
+    // stands on as many as it has members. By the order in which workgroups came
+    // to a counter, teams of 21 stood on 8 to 21 of the 32, by what else the
+    // kernel does before it counts (48 jobs on three fingertips: 11.8 to 12.4 ms,
+    // by rows 11.6; 256 jobs on the 50k one 127 -> 121 ms). Were they ever dealt
+    // otherwise, a member would be there twice: it gives up the second time, and
+    // the team that lacks another does not meet. Teams over several XCDs take
+    // members as they come: by rows the FP64 step of the 50k fingertip took 2.5 %
+    // more, and with the rows of one XCD after those of another three FP32 jobs 3 %
+    // more (their node blocks, fewer than the members, on half of the XCDs).
+    int place = (int)blockIdx.y;
     if (threadIdx.x == 0) {
+        if constexpr (COH == kChip) place = (int)ag_add(&ctl->ticket[at].v, 1u);
+        TeamSync *ts = &ctl->sync[X.team0 + place / X.W];
         if (place >= X.nteam * X.W ||
-            !team_meet(&ctl->sync[X.team0 + place / X.W], (unsigned)X.W, (unsigned)(place % X.W), stat))
+            (COH != kChip && __hip_atomic_exchange(&ts->member[place % X.W], launch, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT) == launch) ||
+            !team_meet(ts, (unsigned)X.W, (unsigned)(place % X.W), stat))
             place = -1;
         sh[0] = place;
         const unsigned long long now = wall_clock64();
@@ -2621,7 +2636,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
     // (this thread's own additions to them have arrived before it leaves) and
     // clears the teams' for the next launch
     if (threadIdx.x == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (threadIdx.x == 0 && ag_add(&ctl->leave.v, 1u) == gridDim.x - 1) {
+    if (threadIdx.x == 0 && ag_add(&ctl->leave.v, 1u) == gridDim.x * gridDim.y - 1) {
         TeamStat *stat_mirror = &ctl->host->stat;
         stat_mirror->done = ag_load(&stat->done);
         stat_mirror->calledoff = ag_load(&stat->calledoff);
@@ -2637,7 +2652,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
                 ag_store(&ctl->sync[t].top.v, 0u);
                 for (int g = 0; kTeamGroup * g < Y.W; g++) ag_store(&ctl->sync[t].group[g].v, 0u);
             }
-            ag_store(&ctl->ticket[x].v, 0u);
+            if (COH == kChip) ag_store(&ctl->ticket[x].v, 0u);
         }
         ag_store(&ctl->leave.v, 0u);
     }

@@ -115,7 +115,7 @@ constexpr int kTeamOff = 64, kTeamOffMost = 65536;
 struct TeamPlan {
     bool tried = false;       // made for the current work tables
     bool valid = false;       // and the team kernel takes these jobs
-    int blocks = 0, laws = 0;
+    int rows = 0, laws = 0;   // workgroups on each XCD
     int span = 1;             // XCDs of a team
     int xcds = 0;             // XCDs in use, consecutive ones
     int wider = 0;   // with at most so many jobs running, teams could span more XCDs than these
@@ -176,7 +176,7 @@ struct fem_batch {
     int team_off = 0, team_off_next = kTeamOff;
     fem_batch *next_run = nullptr;  // runs in flight on the device (DeviceShare)
     unsigned held = 0;              // XCDs of the launch of teams in flight
-    int absent = 0;                 // workgroups left out of each launch of teams (for tests)
+    int absent = 0;                 // workgroups left out on each XCD by launches of teams (for tests)
     void *d_team = nullptr;         // team, XCD and job tables of the plan
     size_t team_bytes = 0, team_ctl_bytes = 0;
     TeamCtl *d_team_ctl = nullptr;
@@ -1096,7 +1096,7 @@ int plan_teams(fem_batch *B, int laws) {
     plan.span = span;
     plan.xcds = span * std::min(places, (int)jobs.size());
     plan.wider = items(jobs[0]) > kTeamSpanItems ? B->xcds / (2 * span) : 0;
-    plan.blocks = ceil_div(need, span) * B->xcds;
+    plan.rows = ceil_div(need, span);
     plan.valid = true;
     return FEM_OK;
 }
@@ -1112,7 +1112,7 @@ int launch_teams(fem_batch *B, int first, int steps, int stop_after, bool whole_
     const InstBufs<T> *bf = (const InstBufs<T> *)B->d_bufs;
     TeamStat *stat = (TeamStat *)(B->d_states + B->capacity);
     const SolveParams *P = (const SolveParams *)B->d_params;
-    const dim3 grid(std::max(1, B->plan.blocks - B->absent)), block(kBlock);
+    const dim3 grid(B->xcds, std::max(1, B->plan.rows - B->absent)), block(kBlock);
     const int stop_on = (stop_after > 0 ? kStopDone : 0) | (whole_rounds ? 0 : kStopPoll);
     const unsigned at = B->stat_seen.done + (unsigned)stop_after;
     const XcdMap map{first, B->xcds, __builtin_ctz(B->plan.span)};
@@ -2408,8 +2408,8 @@ int fem_debug_team_counters(fem_batch *B, uint32_t value) {
     return FEM_OK;
 }
 
-// Workgroups that the next launches of the team kernel leave out, so that
-// teams don't meet (0: none).
+// Workgroups that the next launches of the team kernel leave out on each XCD,
+// so that teams don't meet (0: none).
 int fem_debug_team_absent(fem_batch *B, int32_t workgroups) {
     if (!B || workgroups < 0) return fail(FEM_E_INVALID, "bad argument");
     B->absent = workgroups;

@@ -108,7 +108,7 @@ def test_teams_that_do_not_meet_in_a_run_of_rounds():
     mesh, inds = block_jobs(12, 3)
     ref = reference(mesh, inds)
     t = Batch(mesh, inds)
-    absent(t, 8)
+    absent(t, 1)
 
     def steps(j):
         info = t.b.job_info(j)
@@ -132,7 +132,7 @@ def test_teams_that_never_meet_are_left_alone():
     mesh, inds = block_jobs(1, 2)
     ref = reference(mesh, inds)
     t = Batch(mesh, inds)
-    absent(t, 8)
+    absent(t, 1)
     for k in range(40):   # short runs, each of which would wait for the meeting
         assert t.b.run(t.P, max_rounds=1) == 1
         t.restart()
