@@ -982,11 +982,14 @@ template <typename T, class F> auto with_team_kernel(int laws, int span, F f) {
 }
 
 // A team spans several XCDs only on meshes with more tile and contact blocks
-// than this. On one XCD a solver step of the 50k fingertip (112 blocks, FP64)
-// takes 20 us, its 32 CUs being short of arithmetic, over eight 11.7 us; the 5k
-// one (14 blocks, FP32) takes 7.8 us on one XCD and 9.5 over eight, whose
-// barriers cost 2 us instead of 0.65.
-constexpr int kTeamSpanItems = 64;
+// than this: over eight, the barriers cost 2 us instead of 0.65, and on one its
+// 32 CUs run short of arithmetic. One load step of one job, on one XCD and over
+// eight (ms, fingertips of 5k to 120k tets, Neo-Hookean): FP64 14 blocks
+// 2.4 / 3.0, 36 1.9 / 2.2, 49 3.8 / 3.8, 53 2.50 / 2.55, 63 3.1 / 2.9, 84 6.4 / 4.7,
+// 112 10.1 / 5.6, 267 23.3 / 9.7; FP32 14 0.81 / 0.88, 49 1.07 / 1.15, 63 1.60 / 1.60,
+// 84 1.44 / 1.34, 112 1.75 / 1.50, 267 4.1 / 2.3. The co-rotational law's lines lie
+// there too (63 blocks FP64 6.7 / 5.7, FP32 1.05 / 1.14).
+int team_span_items(const fem_batch *B) { return B->precision == FEM_PREC_FP64 ? 56 : 64; }
 
 // The kernels that record events per launch, sum in a fixed order or split the
 // jobs in two groups are the step kernels; so are launches one by one.
@@ -1028,7 +1031,7 @@ int plan_teams(fem_batch *B, int laws) {
     // XCDs of a team: one, unless there are fewer jobs than XCDs and their
     // meshes have more tiles than one XCD takes at once
     int span = 1;
-    while (2 * span * (int)jobs.size() <= B->xcds && items(jobs[0]) > kTeamSpanItems) span *= 2;
+    while (2 * span * (int)jobs.size() <= B->xcds && items(jobs[0]) > team_span_items(B)) span *= 2;
     int occ = 0;
     HIP_TRY(with_team_kernel<T>(laws, span, [&](auto k) {
         return hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, (const void *)k, kBlock, 0);
@@ -1095,7 +1098,7 @@ int plan_teams(fem_batch *B, int laws) {
     B->t_jobs = (const int *)(base + o_lv);
     plan.span = span;
     plan.xcds = span * std::min(places, (int)jobs.size());
-    plan.wider = items(jobs[0]) > kTeamSpanItems ? B->xcds / (2 * span) : 0;
+    plan.wider = items(jobs[0]) > team_span_items(B) ? B->xcds / (2 * span) : 0;
     plan.rows = ceil_div(need, span);
     plan.valid = true;
     return FEM_OK;
