@@ -27,11 +27,12 @@
  *     positive = a usable result with a warning (FEM_W_FLOOR);
  *   - a handle is not thread-safe; distinct handles are independent. Handles in
  *     use at a time on one device share it: a run that has the device to itself
- *     among the runs of this process keeps its jobs on it for up to 20 ms (in a
- *     run of so many rounds 128 solver steps) at a
- *     time, ends such a launch within 16 solver steps when another handle
- *     waits, and beside other runs takes no more than its share of the chip or
- *     lets their kernels in between two of its own.
+ *     among the runs of this process keeps its jobs on it for up to 20 ms at a
+ *     time (in a run of so many rounds, 128 solver steps) and ends such a launch
+ *     soon after another handle begins to wait for the device (16 solver steps
+ *     or a millisecond, whichever is later); beside other runs it takes no more
+ *     than its share of the chip, or lets their kernels in between two of its
+ *     own.
  */
 #ifndef LIBFEM_FEM_H
 #define LIBFEM_FEM_H
@@ -400,7 +401,9 @@ int fem_batch_get_contact_patch(fem_batch *batch, int32_t job_id, int32_t *ids, 
  * contact-eligible node of the largest), and the entries are ordered in the
  * caller's arrays. Limits and errors, in
  * addition to those of fem_batch_get_contact_patch: FEM_E_INVALID if the
- * job's mesh has more than FEM_NOALLOC_MAX_CONTACT contact-eligible nodes, or
+ * job's mesh has more than FEM_NOALLOC_MAX_CONTACT contact-eligible nodes (the
+ * staging grows with the mesh, but the entries are ordered in place by the host,
+ * which a caller of this variant waits for), or
  * if f or phi is requested without ids (the ids order the entries);
  * FEM_E_STATE if jobs were added, restarted or removed since the last
  * fem_batch_run (updating the launch tables would allocate). */
@@ -419,8 +422,12 @@ int fem_batch_get_kernel_launches(const fem_batch *batch, int32_t kernel, int64_
  * solver steps between two host polls, a team of workgroups per job, and
  * rounds that it does not serve (deterministic sums, two job groups) are
  * captured once per round length into a HIP graph and replayed; 0 launches
- * the tile, node and finalize kernels of each solver step one by one. Results
- * are the same either way. */
+ * the tile, node and finalize kernels of each solver step one by one. A job
+ * takes the same steps either way; the order of the sums of element
+ * contributions and the compiler's contraction of the same expressions may
+ * differ in the last bits, and with them whether a load step at the rounding
+ * floor ends FEM_OK or FEM_W_FLOOR (displacements within 1e-9 of the largest in
+ * FP64 and 1e-5 in FP32 where the steps end alike). */
 int fem_set_graphs(fem_mesh *mesh, int32_t enable);
 int fem_batch_set_graphs(fem_batch *batch, int32_t enable);
 
