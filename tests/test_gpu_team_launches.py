@@ -7,6 +7,7 @@ import ctypes as C
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2103_16747_amd import fem, workload as W
 
@@ -156,3 +157,20 @@ def test_teams_that_never_meet_are_left_alone():
     close_to(t.displacements(), ref)
     assert t.launches()[0] > before[0] and t.launches()[1] == before[1]
     t.b.close()
+
+
+def test_streams_of_the_caller():
+    """Two batches on streams that the program made, one after another."""
+    mesh, inds = block_jobs(3, 2)
+    ref = reference(mesh, inds)
+    for stream in (torch.cuda.Stream(), torch.cuda.current_stream()):
+        b = fem.FemBatch(len(inds), "fp64", stream=stream)
+        P = b.default_params(newton_rtol=1e-10, cg_rtol=1e-10)
+        mid = b.add_mesh(mesh.X, mesh.tets, mesh.fixed)
+        ids = [b.add_job(mid, ind) for ind in inds]
+        for _ in range(2):
+            assert b.run(P) == 0
+            close_to([b.displacements(j) for j in ids], ref)
+            for j, ind in zip(ids, inds):
+                b.restart_job(j, ind)
+        b.close()
