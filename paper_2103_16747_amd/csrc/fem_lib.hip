@@ -275,16 +275,25 @@ void ask_for_room(const fem_batch *B) {
             __atomic_store_n(&team_host(r)->yield, 1u, __ATOMIC_RELAXED);
 }
 
-// A run in flight.
+// A run in flight, or a call that allocates or frees device or pinned memory:
+// those wait for whatever runs on the device, several times over. One in another
+// does nothing.
 struct RunScope {
     fem_batch *B;
-    explicit RunScope(fem_batch *b) : B(b) {
+    explicit RunScope(fem_batch *b) : B(b->device < kMaxDevices ? b : nullptr) {
+        if (!B) return;
         std::lock_guard<std::mutex> lock(g_device_mu);
+        for (const fem_batch *r = g_share[B->device].runs; r; r = r->next_run)
+            if (r == b) {
+                B = nullptr;
+                return;
+            }
         ask_for_room(B);
         B->next_run = g_share[B->device].runs;
         g_share[B->device].runs = B;
     }
     ~RunScope() {
+        if (!B) return;
         std::lock_guard<std::mutex> lock(g_device_mu);
         fem_batch **at = &g_share[B->device].runs;
         while (*at != B) at = &(*at)->next_run;
@@ -327,6 +336,7 @@ struct XcdHold {
 
 int stage(fem_batch *B, size_t bytes) {
     if (B->h_stage_bytes >= bytes) return FEM_OK;
+    const RunScope scope(B);
     if (B->h_stage) (void)hipHostFree(B->h_stage);
     B->h_stage = nullptr;
     B->h_stage_bytes = 0;
@@ -495,6 +505,7 @@ int add_topology(fem_batch *B, const double *X_in, int n, const int32_t *tets_in
     std::vector<uint8_t> owner(std::max(L.nent, 1), 0);
     for (int i = 0; i < n; i++)
         if (L.node_ent_off[i + 1] > L.node_ent_off[i]) owner[L.node_ent[L.node_ent_off[i]]] = 1;
+    const RunScope scope(B);
     HIP_TRY(hipMalloc(&R.arena, A.off));
     char *base = (char *)R.arena;
     auto up = [&](size_t off, const void *src, size_t bytes) -> int {
@@ -693,6 +704,7 @@ int rebuild_tables(fem_batch *B) {
     B->work_built = false;
     B->plan.tried = B->plan.valid = false;
     if (B->tables_dirty) {
+        const RunScope scope(B);
         std::vector<Topo<T>> tv;
         for (TopoRec &R : B->topos) tv.push_back(topo_view<T>(R));
         TRY(sync(B));
@@ -1331,9 +1343,9 @@ int download_velocity(fem_batch *B, int slot, double *v) {
 // ---------------------------------------------------------------------------
 // Batch life cycle
 // ---------------------------------------------------------------------------
-void batch_release(fem_batch *B) {
-    if (!B) return;
-    (void)hipSetDevice(B->device);
+// What a batch owns, but itself.
+void batch_free(fem_batch *B) {
+    const RunScope scope(B);
     if (B->stream) (void)hipStreamSynchronize(B->stream);
     drop_graphs(B);
     for (int i = 0; i < (int)B->insts.size(); i++) free_instance(B, i);
@@ -1356,6 +1368,12 @@ void batch_release(fem_batch *B) {
     if (B->stream2) (void)hipStreamDestroy(B->stream2);
     if (B->xev_created)
         for (hipEvent_t e : B->xev) (void)hipEventDestroy(e);
+}
+
+void batch_release(fem_batch *B) {
+    if (!B) return;
+    (void)hipSetDevice(B->device);
+    batch_free(B);
     delete B;
 }
 
@@ -1390,23 +1408,12 @@ int xcd_count(fem_batch *B) {
     return FEM_OK;
 }
 
-int batch_create(const fem_config *cfg, int capacity, fem_batch **out) {
-    *out = nullptr;
-    fem_config c = {FEM_PREC_FP64, 0, nullptr};
-    if (cfg) c = *cfg;
-    if (c.precision != FEM_PREC_FP64 && c.precision != FEM_PREC_FP32) return fail(FEM_E_INVALID, "bad precision");
-    if (capacity < 1 || capacity > 65536) return fail(FEM_E_INVALID, "max_jobs must be in 1..65536");
-    int ndev = 0;
-    if (hipGetDeviceCount(&ndev) != hipSuccess || ndev <= 0) return fail(FEM_E_DEVICE, "no HIP device");
-    if (c.device < 0 || c.device >= ndev) return fail(FEM_E_INVALID, "bad device ordinal");
-    fem_batch *B = new (std::nothrow) fem_batch();
-    if (!B) return fail(FEM_E_OOM, "host allocation failed");
-    B->precision = c.precision;
-    B->device = c.device;
-    B->capacity = capacity;
-    B->insts.resize(capacity);
+// The streams, events and memory of a new batch.
+int batch_setup(fem_batch *B, const fem_config &c) {
+    const int capacity = B->capacity;
     int rc = set_device(B);
     if (!rc && B->device >= kMaxDevices) rc = fail(FEM_E_INVALID, "device ordinal beyond the device table");
+    const RunScope scope(B);
     if (!rc) {
         if (c.stream) {
             B->stream = (hipStream_t)c.stream;
@@ -1438,6 +1445,25 @@ int batch_create(const fem_config *cfg, int capacity, fem_batch **out) {
         std::memset(B->h_params, 0, sizeof(SolveParams));
         rc = stage(B, 4096);
     }
+    return rc;
+}
+
+int batch_create(const fem_config *cfg, int capacity, fem_batch **out) {
+    *out = nullptr;
+    fem_config c = {FEM_PREC_FP64, 0, nullptr};
+    if (cfg) c = *cfg;
+    if (c.precision != FEM_PREC_FP64 && c.precision != FEM_PREC_FP32) return fail(FEM_E_INVALID, "bad precision");
+    if (capacity < 1 || capacity > 65536) return fail(FEM_E_INVALID, "max_jobs must be in 1..65536");
+    int ndev = 0;
+    if (hipGetDeviceCount(&ndev) != hipSuccess || ndev <= 0) return fail(FEM_E_DEVICE, "no HIP device");
+    if (c.device < 0 || c.device >= ndev) return fail(FEM_E_INVALID, "bad device ordinal");
+    fem_batch *B = new (std::nothrow) fem_batch();
+    if (!B) return fail(FEM_E_OOM, "host allocation failed");
+    B->precision = c.precision;
+    B->device = c.device;
+    B->capacity = capacity;
+    B->insts.resize(capacity);
+    const int rc = batch_setup(B, c);
     if (rc) {
         std::string msg = g_last_error;
         batch_release(B);
@@ -1674,6 +1700,7 @@ bool job_ok(const fem_batch *B, int job) { return B && job >= 0 && job < B->capa
 
 int outbuf(fem_batch *B, size_t bytes) {
     if (B->outbuf_bytes >= bytes) return FEM_OK;
+    const RunScope scope(B);
     if (B->outbuf) (void)hipFree(B->outbuf);
     B->outbuf = nullptr;
     B->outbuf_bytes = 0;
@@ -2130,7 +2157,10 @@ int fem_batch_remove_job(fem_batch *B, int32_t job) {
     if (!job_ok(B, job)) return fail(FEM_E_INVALID, "unknown job");
     TRY(set_device(B));
     TRY(sync(B));
-    free_instance(B, job);
+    {
+        const RunScope scope(B);
+        free_instance(B, job);
+    }
     std::memset(B->h_states + job, 0, sizeof(InstState));
     return write_state(B, job);
 }

@@ -150,3 +150,31 @@ def test_single_jobs_at_once(count):
         assert np.abs(b.displacements(0) - u).max() <= 1e-9 * np.abs(u).max()
         assert launches(b.h)[1] == 0
         b.close()
+
+
+def test_handles_made_beside_a_batch():
+    """Making and closing a handle allocates and frees, which waits for the
+    device several times; each of them takes little longer than alone."""
+    mesh = W.cube_block_mesh()
+    u = W.random_displacement(mesh, 5, 0.005)
+
+    def life():
+        t = [time.perf_counter()]
+        d = evaluation(mesh, u)
+        t.append(time.perf_counter())
+        d.close()
+        return t[1] - t[0], time.perf_counter() - t[1]
+
+    life()
+    alone = life()
+    big = BigBatch()
+    big.start()
+    took = [life()]
+    while big.thread.is_alive():
+        took.append(life())
+    big.join()
+    print("made and closed, ms: alone", [round(1e3 * t, 1) for t in alone], "beside",
+          [[round(1e3 * t, 1) for t in x] for x in took], flush=True)
+    for made, closed in took:
+        assert made < alone[0] + SOON and closed < alone[1] + SOON
+    big.b.close()
